@@ -1205,12 +1205,14 @@ hqa_status hqa_md_hamiltonian(hqa_md *md, int32_t instance, double *H, int32_t d
     if ((size_t)I.N * 8 + 8192 > (size_t)md->max_lds)
         return fail(HQA_EUNSUPPORTED, "binary64 Hamiltonian: N = %d exceeds the LDS capacity", I.N);
     double *buf = H;
-    if (dst_mem == HQA_HOST) HIPCHK(dalloc(&buf, (size_t)md->R));
-    HIPCHK(launch_hamiltonian(md, I, buf, md->stream));
+    DevBufs B;
+    uint8_t *scr;
+    HIPCHK(B.get(&scr, hamiltonian_scratch_bytes(I, md->R)));
+    if (dst_mem == HQA_HOST) HIPCHK(B.get(&buf, (size_t)md->R));
+    HIPCHK(launch_hamiltonian(md, I, buf, scr, md->stream));
     if (dst_mem == HQA_HOST)
         HIPCHK(hipMemcpyAsync(H, buf, (size_t)md->R * 8, hipMemcpyDeviceToHost, md->stream));
     HIPCHK(hipStreamSynchronize(md->stream));
-    if (dst_mem == HQA_HOST) dfree(buf);
     return HQA_OK;
 }
 

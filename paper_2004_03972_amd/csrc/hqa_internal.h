@@ -160,7 +160,8 @@ int batch_form(const hqa_md *md, int instance);
 bool csr_resident_fits(hqa_md *md, Instance &I);
 hipError_t launch_md_csr_resident(hqa_md *md, Instance &I, int64_t q0, int64_t q1);
 hipError_t launch_field(hqa_md *md, Instance &I, double *u, hipStream_t st);
-hipError_t launch_hamiltonian(hqa_md *md, Instance &I, double *H, hipStream_t st);
+size_t hamiltonian_scratch_bytes(const Instance &I, int R);
+hipError_t launch_hamiltonian(hqa_md *md, Instance &I, double *H, void *scratch, hipStream_t st);
 
 // read-out
 hipError_t launch_select(const Instance &I, int R, int prec, int W, int n, int32_t *amb,
