@@ -1594,13 +1594,15 @@ hqa_status hqa_md_features(hqa_md *md, int32_t instance, float *feat, int32_t ds
 struct hqa_es {
     hipStream_t stream = nullptr;
     float *P = nullptr, *m = nullptr, *v = nullptr, *g = nullptr, *acc = nullptr;
+    float *part = nullptr;            // the gradient kernel's partial sums
+    size_t part_bytes = 0;
     int64_t t = 0;
 };
 
 void hqa_es_destroy(hqa_es *es) {
     if (!es) return;
     (void)hipStreamSynchronize(es->stream);
-    dfree(es->P); dfree(es->m); dfree(es->v); dfree(es->g); dfree(es->acc);
+    dfree(es->P); dfree(es->m); dfree(es->v); dfree(es->g); dfree(es->acc); dfree(es->part);
     delete es;
 }
 
@@ -1667,6 +1669,19 @@ static hqa_status es_inputs(hqa_es *es, DevBufs &B, const float *x, const int32_
     return HQA_OK;
 }
 
+// The gradient scratch for n samples, kept with the classifier.
+static hqa_status es_part(hqa_es *es, int64_t n) {
+    const size_t need = mlp_grad_scratch_bytes(n);
+    if (need <= es->part_bytes) return HQA_OK;
+    HIPCHK(hipStreamSynchronize(es->stream));
+    dfree(es->part);
+    es->part = nullptr;
+    es->part_bytes = 0;
+    HIPCHK(dev_malloc((void **)&es->part, need));
+    es->part_bytes = need;
+    return HQA_OK;
+}
+
 hqa_status hqa_es_grad(hqa_es *es, const float *x, const int32_t *y, int64_t n, const float *cw,
                        float *grad, float *loss, int32_t mem) {
     if (!es || !x || !y || !cw || n < 1) return fail(HQA_EINVAL, "bad arguments");
@@ -1675,7 +1690,9 @@ hqa_status hqa_es_grad(hqa_es *es, const float *x, const int32_t *y, int64_t n, 
     const int32_t *dy;
     hqa_status s = es_inputs(es, B, x, y, cw, n, mem, &dx, &dy, &dcw);
     if (s != HQA_OK) return s;
-    HIPCHK(launch_mlp_grad(es->P, n, dx, dy, dcw, es->g, es->acc, es->stream));
+    if ((s = es_part(es, n)) != HQA_OK) return s;
+    HIPCHK(launch_mlp_grad(es->P, n, dx, dy, dcw, es->g, es->acc, es->part, es->m, es->v, 0, 0.f,
+                           es->stream));
     if (grad) HIPCHK(hipMemcpyAsync(grad, es->g, sizeof(float) * HQA_ES_NPARAM, kind_out(mem), es->stream));
     if (loss) HIPCHK(hipMemcpyAsync(loss, es->acc + 2, sizeof(float), kind_out(mem), es->stream));
     HIPCHK(hipStreamSynchronize(es->stream));
@@ -1690,9 +1707,10 @@ hqa_status hqa_es_train_step(hqa_es *es, const float *x, const int32_t *y, int64
     const int32_t *dy;
     hqa_status s = es_inputs(es, B, x, y, cw, n, mem, &dx, &dy, &dcw);
     if (s != HQA_OK) return s;
-    HIPCHK(launch_mlp_grad(es->P, n, dx, dy, dcw, es->g, es->acc, es->stream));
+    if ((s = es_part(es, n)) != HQA_OK) return s;
+    HIPCHK(launch_mlp_grad(es->P, n, dx, dy, dcw, es->g, es->acc, es->part, es->m, es->v, es->t + 1, lr,
+                           es->stream));
     es->t += 1;
-    HIPCHK(launch_adam(es->P, es->g, es->m, es->v, es->t, lr, es->stream));
     if (loss) HIPCHK(hipMemcpyAsync(loss, es->acc + 2, sizeof(float), kind_out(mem), es->stream));
     if (mem == HQA_HOST || loss) HIPCHK(hipStreamSynchronize(es->stream));
     return HQA_OK;
