@@ -3,11 +3,8 @@
 //
 // Layout: the binary32 state is spin-major [N][Rp] (Rp = R padded to a multiple
 // of 4): row i holds spin i of every replica, so a neighbour's fluxes are one
-// contiguous run.  Each thread owns four consecutive replicas of one spin and
-// walks that spin's couplings in ascending column order; the column indices
-// and values are uniform across the threads of a row (scalar broadcasts) and
-// every flux gather is a coalesced 16-byte-per-lane read.  Per spin update the
-// kernel moves 16 bytes of state (read phi, read and write p, write phi').
+// contiguous run.  Per spin update the kernel moves 16 bytes of state (read phi,
+// read and write p, write phi') and gathers 4 bytes per coupling.
 #include "hqa_internal.h"
 #include "md_epilogue.h"
 
@@ -31,64 +28,136 @@ struct CsrArgs {
     const float *inv_n2;   // 1 / ||J_i||_2
 };
 
-// Workgroup b of a launch runs on XCD b mod 8, each XCD with its own L2.  The
-// remap gives XCD x the contiguous block range [x nb/8, (x+1) nb/8) (the last
-// nb mod 8 blocks keep their index), so rows whose neighbours are nearby in index
-// (lattices, banded graphs) find those neighbours' fluxes in their own L2 instead
-// of fetching them into a second and third one.
-__device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb) {
-    const int64_t per = nb / 8;
-    return b < per * 8 ? (b % 8) * per + b / 8 : b;
-}
-
-template <bool FIELD_ONLY>
-__global__ __launch_bounds__(256) void k_step_csr(CsrArgs a, int64_t q) {
-    int64_t t = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)a.N * a.Rq) return;
-    const int i = (int)(t / a.Rq), c4 = (int)(t % a.Rq);
-    const int Rp = a.Rq * 4;
-    const float4 *X = (const float4 *)a.phi_in;
-    float4 u = make_float4(0.f, 0.f, 0.f, 0.f);
-    const int e0 = a.rp[i], e1 = a.rp[i + 1];
-    for (int e = e0; e < e1; e++) {
-        const int j = a.ci[e];
-        const float w = a.v[e];
-        const float4 xj = X[(int64_t)j * a.Rq + c4];
-        u.x = fmaf(w, xj.x, u.x);
-        u.y = fmaf(w, xj.y, u.y);
-        u.z = fmaf(w, xj.z, u.z);
-        u.w = fmaf(w, xj.w, u.w);
+// One wavefront per (row, chunk of 64 VEC replicas), VEC consecutive replicas a lane; the
+// row's couplings are walked in ascending column order.
+//
+// What bounds it is the gather's latency and then its bytes from L2, so
+//  * the row is uniform over the wavefront: column indices and values come through scalar
+//    loads, eight at a time, and a gather is one vector load with a 32-bit offset (O;
+//    64-bit where the state reaches 4 GB);
+//  * 16 (then 8) gathers are in flight together; the last batch reads the last coupling
+//    again in place of those past the end and does not use it;
+//  * workgroup b runs on XCD b mod 8, each XCD with its own L2.  Sliced, an XCD serves one
+//    chunk of 64 replicas at a time (nchunk = 2, 4: 8 / nchunk XCDs split the rows of a
+//    chunk; multiples of 8: chunks x, x + 8, ... on XCD x), so the fluxes an XCD gathers
+//    from are 256 N bytes instead of all replicas'.  Otherwise each XCD has a contiguous
+//    range of rows, whose neighbours are nearby in lattices.
+//
+// Measured, us per step (a thread per row and 4 replicas, one gather at a time -> now):
+// G(10^4, mean degree 30) R = 16, 128, 512: 20.1, 24.8, 78.7 -> 7.6, 14.3, 42 (R = 128 is
+// 154 MB of gathers, 13 TB/s from the L2s beyond the launch; unsliced 16.0);
+// G(2000, 12) R = 128: 10.6 -> 4.6; the 16^3 lattice R = 128, 1024: 5.3, 16.9 -> 5.0, 16.7.
+template <int VEC, bool FIELD_ONLY, typename O>
+__global__ __launch_bounds__(256) void k_step_csr(CsrArgs a, int64_t q, uint32_t nchunk, int sliced) {
+    typedef float fv __attribute__((ext_vector_type(VEC)));
+    typedef int32_t i32x8 __attribute__((ext_vector_type(8), aligned(4)));
+    typedef float f32x8 __attribute__((ext_vector_type(8), aligned(4)));
+    // read-only for the whole launch and uniform: scalar loads
+    typedef const __attribute__((address_space(4))) int32_t cint;
+    typedef const __attribute__((address_space(4))) float cfloat;
+    typedef const __attribute__((address_space(4))) i32x8 cint8;
+    typedef const __attribute__((address_space(4))) f32x8 cfloat8;
+    const uint32_t nrb = ((uint32_t)a.N + 3) / 4, b = blockIdx.x, nb = gridDim.x;
+    uint32_t rb, chunk;
+    if (sliced) {
+        const uint32_t xcd = b % 8, k = b / 8;
+        if (nchunk < 8) {
+            const uint32_t share = 8 / nchunk, per = (nrb + share - 1) / share;
+            chunk = xcd / share;
+            rb = (xcd % share) * per + k;
+            if (k >= per) return;
+        } else {
+            chunk = xcd + 8 * (k / nrb);
+            rb = k % nrb;
+        }
+    } else {
+        // XCD x takes [x nb/8, (x+1) nb/8); the last nb mod 8 workgroups keep their index
+        const uint32_t per = nb / 8, t = b < per * 8 ? (b % 8) * per + b / 8 : b;
+        rb = t / nchunk;
+        chunk = t % nchunk;
     }
-    const int64_t base = (int64_t)i * Rp + 4 * c4;
+    const int i = __builtin_amdgcn_readfirstlane((int)(rb * 4 + (threadIdx.x >> 6)));
+    if (i >= a.N) return;
+    const uint32_t Rp = 4u * (uint32_t)a.Rq, c = (chunk * 64 + (threadIdx.x & 63)) * VEC;
+    if (c >= Rp) return;
+    const cint *rp = (const cint *)a.rp, *ci = (const cint *)a.ci;
+    const cfloat *wv = (const cfloat *)a.v;
+    const O pitch = 4 * (O)Rp, off = 4 * (O)c;
+    const char *X = (const char *)a.phi_in;
+    const int64_t base = (int64_t)i * Rp + c;
+    fv u = 0.f, x, p;
+    if constexpr (!FIELD_ONLY) {
+        x = *(const fv *)(a.phi_in + base);
+        p = *(const fv *)(a.p + base);
+    }
+    const int e1 = rp[i + 1];
+    int e = rp[i];
+    if constexpr (VEC <= 2) {   // four a lane: eight gathers are already 8 KB in flight
+        for (; e + 16 <= e1; e += 16) {
+            const i32x8 ja = *(cint8 *)(ci + e), jb = *(cint8 *)(ci + e + 8);
+            const f32x8 wa = *(cfloat8 *)(wv + e), wb = *(cfloat8 *)(wv + e + 8);
+            fv g[16];
+#pragma unroll
+            for (int k = 0; k < 8; k++) g[k] = *(const fv *)(X + ((O)ja[k] * pitch + off));
+#pragma unroll
+            for (int k = 0; k < 8; k++) g[8 + k] = *(const fv *)(X + ((O)jb[k] * pitch + off));
+#pragma unroll
+            for (int k = 0; k < 16; k++)
+#pragma unroll
+                for (int v = 0; v < VEC; v++) u[v] = fmaf(k < 8 ? wa[k & 7] : wb[k & 7], g[k][v], u[v]);
+        }
+    }
+    for (; e + 8 <= e1; e += 8) {
+        const i32x8 j = *(cint8 *)(ci + e);
+        const f32x8 w = *(cfloat8 *)(wv + e);
+        fv g[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) g[k] = *(const fv *)(X + ((O)j[k] * pitch + off));
+#pragma unroll
+        for (int k = 0; k < 8; k++)
+#pragma unroll
+            for (int v = 0; v < VEC; v++) u[v] = fmaf(w[k], g[k][v], u[v]);
+    }
+    if (e < e1) {
+        fv g[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) g[k] = *(const fv *)(X + ((O)ci[min(e + k, e1 - 1)] * pitch + off));
+#pragma unroll
+        for (int k = 0; k < 8; k++)
+            if (e + k < e1) {
+#pragma unroll
+                for (int v = 0; v < VEC; v++) u[v] = fmaf(wv[e + k], g[k][v], u[v]);
+            }
+    }
     if constexpr (FIELD_ONLY) {
-        *(float4 *)(a.u_out + base) = u;
+        *(fv *)(a.u_out + base) = u;
         return;
     } else {
-        const StepCoef c = step_coef(a.a32, a.b32, q, a.rg, a.M);
+        const StepCoef cf = step_coef(a.a32, a.b32, q, a.rg, a.M);
         const float hi = a.h[i];
-        float4 x = X[(int64_t)i * a.Rq + c4];
-        float4 p = *(const float4 *)(a.p + base);
-        float4 xn;
-        leapfrog(c, x.x, u.x, hi, p.x, xn.x);
-        leapfrog(c, x.y, u.y, hi, p.y, xn.y);
-        leapfrog(c, x.z, u.z, hi, p.z, xn.z);
-        leapfrog(c, x.w, u.w, hi, p.w, xn.w);
+        fv xn;
+        bool bad = false;
+#pragma unroll
+        for (int v = 0; v < VEC; v++) {
+            float pv = p[v], nv;
+            leapfrog(cf, x[v], u[v], hi, pv, nv);
+            p[v] = pv;
+            xn[v] = nv;
+            bad |= !isfinite(nv) || !isfinite(pv);
+        }
         if (a.st) {
             const float in2 = a.inv_n2[i];
-            es_accumulate(a.st, a.sst, base + 0, x.x, xn.x, u.x, p.x, in2);
-            es_accumulate(a.st, a.sst, base + 1, x.y, xn.y, u.y, p.y, in2);
-            es_accumulate(a.st, a.sst, base + 2, x.z, xn.z, u.z, p.z, in2);
-            es_accumulate(a.st, a.sst, base + 3, x.w, xn.w, u.w, p.w, in2);
+#pragma unroll
+            for (int v = 0; v < VEC; v++) es_accumulate(a.st, a.sst, base + v, x[v], xn[v], u[v], p[v], in2);
         }
-        *(float4 *)(a.phi_out + base) = xn;
-        *(float4 *)(a.p + base) = p;
+        *(fv *)(a.phi_out + base) = xn;
+        *(fv *)(a.p + base) = p;
         if (q + 1 >= a.T - a.W + 1) {
-            float4 s = *(const float4 *)(a.S + base);
-            s.x = s.x + xn.x; s.y = s.y + xn.y; s.z = s.z + xn.z; s.w = s.w + xn.w;
-            *(float4 *)(a.S + base) = s;
+            fv s = *(const fv *)(a.S + base);
+#pragma unroll
+            for (int v = 0; v < VEC; v++) s[v] = s[v] + xn[v];
+            *(fv *)(a.S + base) = s;
         }
-        bool bad = !isfinite(xn.x) || !isfinite(xn.y) || !isfinite(xn.z) || !isfinite(xn.w) ||
-                   !isfinite(p.x) || !isfinite(p.y) || !isfinite(p.z) || !isfinite(p.w);
         if (bad) atomicOr(a.err, ERR_NONFINITE);
     }
 }
@@ -104,23 +173,55 @@ static CsrArgs csr_args(hqa_md *md, Instance &I) {
     return a;
 }
 
+template <int VEC, bool FO>
+static void launch_vec(const CsrArgs &a, int64_t q, uint32_t nchunk, bool sliced, hipStream_t st) {
+    const uint32_t nrb = ((uint32_t)a.N + 3) / 4;
+    uint32_t grid = nrb * nchunk;
+    if (sliced && nchunk < 8) grid = 8 * ((nrb + 8 / nchunk - 1) / (8 / nchunk));
+    if ((uint64_t)a.N * a.Rq * 16 < (1ull << 32))
+        k_step_csr<VEC, FO, uint32_t><<<grid, 256, 0, st>>>(a, q, nchunk, sliced);
+    else
+        k_step_csr<VEC, FO, uint64_t><<<grid, 256, 0, st>>>(a, q, nchunk, sliced);
+}
+
+// Chunks and their XCDs, by what was fastest (us per step, one / two / four replicas a lane):
+//  * up to 64 replicas: one a lane (G(10^4, 30) R = 64: 9.9 / 14.4 / 14.8; 16^3: 4.0 / 4.5 / 4.6);
+//  * few couplings a row (mean degree below 10): wide lanes, the step being state traffic
+//    (16^3, R = 128: 5.5 / 5.0 / 5.1; R = 1024: 23.0 / - / 16.7; G(3000, 5) R = 256: 8.2 / - / 7.0);
+//  * else 64-replica chunks, sliced over the XCDs when the chunks fill them evenly (G(10^4, 30)
+//    R = 256: 24.3, unsliced 35.0, four a lane 34.6; R = 128: 14.6, 16.0, two a lane 16.2);
+//    an uneven number of chunks above three takes four a lane.
+template <bool FO>
+static void launch_csr(const CsrArgs &a, int64_t nnz, int64_t q, hipStream_t st) {
+    const uint32_t Rp = 4u * (uint32_t)a.Rq, nc = (Rp + 63) / 64;
+    if (nc == 1) {
+        launch_vec<1, FO>(a, q, 1, false, st);
+    } else if (nnz < 10 * (int64_t)a.N) {
+        if (Rp <= 128) launch_vec<2, FO>(a, q, 1, false, st);
+        else launch_vec<4, FO>(a, q, (Rp + 255) / 256, false, st);
+    } else if (nc == 2 || nc == 4 || nc % 8 == 0) {
+        launch_vec<1, FO>(a, q, nc, true, st);
+    } else if (nc == 3) {
+        launch_vec<1, FO>(a, q, nc, false, st);
+    } else {
+        launch_vec<4, FO>(a, q, (Rp + 255) / 256, false, st);
+    }
+}
+
 hipError_t launch_md_steps_csr(hqa_md *md, Instance &I, int64_t q0, int64_t q1) {
-    int64_t n = (int64_t)I.N * (I.Rp / 4);
-    unsigned blocks = (unsigned)((n + 255) / 256);
     for (int64_t q = q0; q < q1; q++) {
         CsrArgs a = csr_args(md, I);
         if (I.st && stats_step(md, q)) a.st = I.st;
-        k_step_csr<false><<<blocks, 256, 0, md->stream>>>(a, q);
+        launch_csr<false>(a, I.nnz, q, md->stream);
         I.cur ^= 1;
     }
     return hipGetLastError();
 }
 
 hipError_t launch_field_csr(hqa_md *md, Instance &I, float *u, hipStream_t st) {
-    int64_t n = (int64_t)I.N * (I.Rp / 4);
     CsrArgs a = csr_args(md, I);
     a.u_out = u;
-    k_step_csr<true><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(a, 0);
+    launch_csr<true>(a, I.nnz, 0, st);
     return hipGetLastError();
 }
 
