@@ -118,7 +118,7 @@ static void dfree(void *p) {
 
 static void free_instance(Instance &I) {
     dfree(I.J64); dfree(I.rp); dfree(I.ci); dfree(I.h64); dfree(I.h32); dfree(I.Js); dfree(I.v32);
-    for (int k = 0; k < 2; k++) { dfree(I.phi64[k]); dfree(I.phi32[k]); dfree(I.phib[k]); }
+    for (int k = 0; k < 2; k++) { dfree(I.phi64[k]); dfree(I.phi32[k]); dfree(I.phib[k]); dfree(I.xt[k]); }
     dfree(I.p64); dfree(I.S64); dfree(I.p32); dfree(I.S32); dfree(I.xch); dfree(I.Jt);
     dfree(I.Jbits);
     dfree(I.st); dfree(I.n1); dfree(I.inv_n2);

@@ -71,6 +71,7 @@ struct Instance {
     float *phi32[2] = {nullptr, nullptr};
     float *p32 = nullptr, *S32 = nullptr;
     bf16 *phib[2] = {nullptr, nullptr};
+    bf16 *xt[2] = {nullptr, nullptr};   // phib in MFMA operand order (tiled per-step plan, first use)
     int cur = 0;              // phi[cur] holds phi^(q)
     void *xch = nullptr;      // persistent-kernel exchange buffers (tagged words)
     size_t xch_bytes = 0;

@@ -50,7 +50,18 @@ struct DenseArgs {
     int32_t *err;
     const void *Jt;     // MFMA-tiled copy of a BF16 / FP8 J (tiled plans), else null
     int ntile, nrounds; // its row tiles (of 16) and 128-column groups
+    const bf16 *xt_in;  // tiled plans: the BF16 fluxes in operand order (see x_tiled)
+    bf16 *xt_out;
 };
+
+// Position of (replica r, column k) in the operand-order copy of the BF16 fluxes: per 16
+// replicas and 128-column group, the four chains' B fragments one after another, lane by
+// lane (lane = 16 (k % 32 / 8) + r % 16), eight columns a lane.  A wavefront's fragment is
+// then one contiguous kilobyte instead of 16 half lines of 16 rows.
+__device__ __forceinline__ int64_t x_tiled(int nrounds, int r, int k) {
+    const int64_t f = ((int64_t)(r >> 4) * nrounds + (k >> 7)) * 4 + ((k >> 5) & 3);
+    return (f * 64 + 16 * ((k >> 3) & 3) + (r & 15)) * 8 + (k & 7);
+}
 
 // Eight FP8 e4m3 codes to eight BF16 values (exact: e4m3 embeds in bf16).
 __device__ __forceinline__ bf16x8 fp8x8_to_bf16(uint2 raw) {
@@ -69,7 +80,11 @@ __device__ __forceinline__ bf16x8 fp8x8_to_bf16(uint2 raw) {
 // TM * TN MFMAs, so each fragment is reused across the block.  TJ: the A fragments
 // come from the MFMA-tiled copy of J (a 16-row x 128-column group is one contiguous
 // block whose four chunks the four wavefronts read together) instead of from the
-// row-major storage (16 rows of 64 or 32 bytes per load); same fragments.
+// row-major storage (16 rows of 64 or 32 bytes per load), and the B fragments from the
+// operand-order copy of the fluxes; same fragments.  At R = 16 a row tile's fluxes are as
+// many bytes as its couplings, and 16 half lines a fragment bound them: N = 10^4, BF16
+// (204 MB of J), 52.5 us per step with row-major fluxes, 41.9 with these (4.9 TB/s; the
+// couplings alone stream in 30).
 template <int JT, int TM, int TN, int CB, bool TJ = false>
 __device__ __forceinline__ void chain_block(const DenseArgs &a, int i0, int r0, int lane, int w,
                                             f32x4 (&acc)[TM][TN]) {
@@ -136,8 +151,14 @@ __device__ __forceinline__ void chain_block(const DenseArgs &a, int i0, int r0, 
                     }
                 }
 #pragma unroll
-                for (int tn = 0; tn < TN; tn++)
-                    B[m][tn] = *(const bf16x8 *)(a.xb_in + (int64_t)(r0 + 16 * tn + (lane & 15)) * a.ld + kk);
+                for (int tn = 0; tn < TN; tn++) {
+                    if constexpr (TJ)
+                        B[m][tn] = *(const bf16x8 *)(a.xt_in +
+                                                     ((((int64_t)(r0 / 16 + tn) * a.nrounds + m0 + m) * 4 + w) * 64 +
+                                                      lane) * 8);
+                    else
+                        B[m][tn] = *(const bf16x8 *)(a.xb_in + (int64_t)(r0 + 16 * tn + (lane & 15)) * a.ld + kk);
+                }
             }
 #pragma unroll
             for (int m = 0; m < CB; m++) {
@@ -174,6 +195,7 @@ __device__ __forceinline__ void load_tile_state(const DenseArgs &a, int64_t q, i
 }
 
 // Leapfrog of four consecutive rows (ib..ib+3) of replica col with field u.
+template <bool TJ>
 __device__ __forceinline__ void dense_update(const DenseArgs &a, int64_t q, int col, int ib,
                                              const f32x4 &u, const StepCoef &c, const TileState &ts) {
     const int64_t base = (int64_t)col * a.ld + ib;
@@ -193,11 +215,10 @@ __device__ __forceinline__ void dense_update(const DenseArgs &a, int64_t q, int 
     }
     *(float4 *)(a.phi_out + base) = make_float4(xn[0], xn[1], xn[2], xn[3]);
     *(float4 *)(a.p + base) = make_float4(ps[0], ps[1], ps[2], ps[3]);
-    if (a.xb_out) {
-        typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
-        bf16x4 b = {(bf16)xn[0], (bf16)xn[1], (bf16)xn[2], (bf16)xn[3]};
-        *(bf16x4 *)(a.xb_out + base) = b;
-    }
+    typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
+    const bf16x4 b = {(bf16)xn[0], (bf16)xn[1], (bf16)xn[2], (bf16)xn[3]};
+    if (a.xb_out) *(bf16x4 *)(a.xb_out + base) = b;
+    if constexpr (TJ) *(bf16x4 *)(a.xt_out + x_tiled(a.nrounds, col, ib)) = b;   // ib is a multiple of 4
     if (q + 1 >= a.T - a.W + 1) {
         float4 s = ts.s;
         s.x = s.x + xn[0]; s.y = s.y + xn[1]; s.z = s.z + xn[2]; s.w = s.w + xn[3];
@@ -250,7 +271,7 @@ __global__ __launch_bounds__(256) void k_step_block(DenseArgs a, int64_t q) {
         if constexpr (FIELD_ONLY) {
             *(float4 *)(a.u_out + (int64_t)col * a.ld + ib) = make_float4(u[0], u[1], u[2], u[3]);
         } else {
-            dense_update(a, q, col, ib, u, cf, ts[k]);
+            dense_update<TJ>(a, q, col, ib, u, cf, ts[k]);
         }
     }
 }
@@ -265,7 +286,34 @@ static DenseArgs dense_args(hqa_md *md, Instance &I) {
     a.p = I.p32; a.S = I.S32; a.u_out = nullptr; a.err = md->err; a.jt = I.jt;
     a.st = nullptr; a.sst = (int64_t)I.Rp * I.ld; a.inv_n2 = I.inv_n2;
     a.Jt = nullptr; a.ntile = (I.N + 15) / 16; a.nrounds = I.Np / 128;
+    a.xt_in = nullptr; a.xt_out = nullptr;
     return a;
+}
+
+// The operand-order copy of the BF16 fluxes [Rp][ld], eight columns a thread.
+__global__ __launch_bounds__(256) void k_tile_x(const bf16 *x, int Rp, int ld, bf16 *xt) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int per = ld / 8;
+    if (t >= (int64_t)Rp * per) return;
+    const int r = (int)(t / per), k = 8 * (int)(t % per);
+    *(bf16x8 *)(xt + x_tiled(ld / 128, r, k)) = *(const bf16x8 *)(x + (int64_t)r * ld + k);
+}
+
+// Both buffers of the operand-order copy, zero where no flux is ever written (padding).
+static hipError_t ensure_tiled_x(Instance &I, hipStream_t st) {
+    const size_t n = (size_t)I.Rp * I.ld;
+    for (int b = 0; b < 2; b++) {
+        if (I.xt[b]) continue;
+        hipError_t e = dev_malloc((void **)&I.xt[b], n * sizeof(bf16));
+        if (e != hipSuccess) return e;
+        e = hipMemsetAsync(I.xt[b], 0, n * sizeof(bf16), st);
+        if (e != hipSuccess) {
+            (void)hipFree(I.xt[b]);
+            I.xt[b] = nullptr;
+            return e;
+        }
+    }
+    return hipSuccess;
 }
 
 // Replica tiles per block: 4 (64 replicas) when they divide Rp, else 2, else 1.
@@ -318,13 +366,23 @@ hipError_t launch_md_steps_dense(hqa_md *md, Instance &I, int64_t q0, int64_t q1
                        : block_tn(I.Rp);
     const int tm = I.step_tm == 1 ? 1 : 2;   // Np is a multiple of 128: both divide it
     const int cb = I.step_cb == 8 ? 8 : 4;
-    if (I.step_tj) {
+    if (I.step_tj && q0 < q1) {
         hipError_t e = ensure_tiled_j(I, md->stream);
+        if (e == hipSuccess) e = ensure_tiled_x(I, md->stream);
         if (e != hipSuccess) return e;
+        const int64_t n = (int64_t)I.Rp * (I.ld / 8);
+        k_tile_x<<<(unsigned)((n + 255) / 256), 256, 0, md->stream>>>(I.phib[I.cur], I.Rp, I.ld, I.xt[0]);
     }
     for (int64_t q = q0; q < q1; q++) {
         DenseArgs a = dense_args(md, I);
-        if (I.step_tj) a.Jt = I.Jt;
+        if (I.step_tj) {
+            // the steps pass the operand copy on between the two tiled buffers; the last
+            // one also leaves the row-major copy the other plans start from
+            a.Jt = I.Jt;
+            a.xt_in = I.xt[(q - q0) & 1];
+            a.xt_out = I.xt[((q - q0) & 1) ^ 1];
+            if (q + 1 < q1) a.xb_out = nullptr;
+        }
         if (I.st && stats_step(md, q)) a.st = I.st;
         launch_one<false>(a, tm, tn, cb, q, md->stream);
         I.cur ^= 1;
