@@ -85,9 +85,9 @@ struct Instance {
     bool js_exact = false;    // dense: Js holds every coupling exactly
     // dense binary32 plan chosen by the tuner (0: not tuned) and its per-step tile width
     int32_t tuned_plan = 0;
-    int32_t step_tn = 0;      // replica tiles of 16 per per-step block (0: widest that divides Rp)
-    int32_t step_tm = 0;      // row tiles of 16 per per-step block (0: 2)
-    int32_t step_cb = 0;      // chunks per chain loaded together (0: 4)
+    int32_t step_tn = 0;      // replica tiles of 16 per per-step block (0: by size)
+    int32_t step_tm = 0;      // row tiles of 16 per per-step block (0: by size)
+    int32_t step_cb = 0;      // chunks per chain loaded together (0: by storage)
     int32_t step_tj = 0;      // per-step A fragments from the MFMA-tiled J (BF16 / FP8)
     int32_t max_deg = -1;     // CSR: largest row degree (computed on first need)
 };

@@ -10,10 +10,9 @@
 // consecutive rows of one replica, so the epilogue reads and writes 16-byte
 // vectors of the state.
 //
-// Workgroup: a block of TM x TN output tiles (16 TM rows x 16 TN replicas; the
-// tuner picks TM in {1, 2} and TN in {1, 2, 4}, by default 2 x the widest TN that
-// divides the padded replica count), K split over the four wavefronts by
-// accumulation chain.  The dense field is accumulated in four chains (K chunk c
+// Workgroup: a block of TM x TN output tiles (16 TM rows x 16 TN replicas, TM in
+// {1, 2} and TN in {1, 2, 4}, by the tuner or by default_block), K split over the
+// four wavefronts by accumulation chain.  The dense field is accumulated in four chains (K chunk c
 // of 32 columns for BF16 operands, 16 for FP32, feeds chain c mod 4; see
 // combine4), and wavefront w computes chain w of every tile of the block:
 // chunks w, w+4, w+8, ... in ascending order, four chunks' loads in flight
@@ -83,12 +82,14 @@ __device__ __forceinline__ bf16x8 fp8x8_to_bf16(uint2 raw) {
 // row-major storage (16 rows of 64 or 32 bytes per load), and the B fragments from the
 // operand-order copy of the fluxes; same fragments.  At R = 16 a row tile's fluxes are as
 // many bytes as its couplings, and 16 half lines a fragment bound them: N = 10^4, BF16
-// (204 MB of J), 52.5 us per step with row-major fluxes, 41.9 with these (4.9 TB/s; the
+// (204 MB of J), 52.5 us per step with row-major fluxes, 41.9 with these (the
 // couplings alone stream in 30).
-template <int JT, int TM, int TN, int CB, bool TJ = false>
+// state() requests the state of the update: first, or (LATE) before the last batch's loads.
+template <int JT, int TM, int TN, int CB, bool TJ, bool LATE, class F>
 __device__ __forceinline__ void chain_block(const DenseArgs &a, int i0, int r0, int lane, int w,
-                                            f32x4 (&acc)[TM][TN]) {
+                                            f32x4 (&acc)[TM][TN], F state) {
     const int kg = lane >> 4;
+    if constexpr (!LATE) state();
 #pragma unroll
     for (int tm = 0; tm < TM; tm++)
 #pragma unroll
@@ -130,6 +131,8 @@ __device__ __forceinline__ void chain_block(const DenseArgs &a, int i0, int r0, 
         constexpr int esz = JT == JT_BF16 ? 2 : 1;
         const int nch = a.Np / 128;
         for (int m0 = 0; m0 < nch; m0 += CB) {
+            if constexpr (LATE)
+                if (m0 + CB >= nch) state();
             AT A[CB][TM];
             bf16x8 B[CB][TN];
 #pragma unroll
@@ -177,8 +180,12 @@ __device__ __forceinline__ void chain_block(const DenseArgs &a, int i0, int r0, 
     }
 }
 
-// State of four consecutive rows (ib..ib+3) of one replica that the update reads,
-// loaded before the field so that its latency overlaps the field's loads.
+// State of four consecutive rows (ib..ib+3) of one replica that the update reads.  It is
+// requested first, so that its latency overlaps the field's loads, or (LATE, tiled 1 x 1
+// blocks from Np = 4608 on) with the chain's last batch: a wavefront's loads return in order,
+// and in front these scattered half lines hold up the first couplings, which costs more than
+// it hides once the chain has several batches (R = 16, first / last, us per step: N = 10^4
+// BF16 42.5 / 39.6, FP8 26.6 / 24.7; N = 5000 BF16 14.5 / 13.5; N = 4000 BF16 7.5 / 7.9).
 struct TileState {
     float4 x, p, s;
     float h[4];
@@ -229,9 +236,8 @@ __device__ __forceinline__ void dense_update(const DenseArgs &a, int64_t q, int 
 
 // Block of TM x TN output tiles (32 rows x 16 TN replicas for TM = 2): each
 // wavefront accumulates one chain of every tile; the partial tiles meet in LDS
-// and wavefront w combines and updates tiles w, w + 4, ... in chain order.  The
-// state these updates read is loaded first, together with the field operands.
-template <int JT, int TM, int TN, bool FIELD_ONLY, int CB = 4, bool TJ = false>
+// and wavefront w combines and updates tiles w, w + 4, ... in chain order.
+template <int JT, int TM, int TN, bool FIELD_ONLY, int CB = 4, bool TJ = false, bool LATE = false>
 __global__ __launch_bounds__(256) void k_step_block(DenseArgs a, int64_t q) {
     constexpr int NT = (TM * TN + 3) / 4;   // tiles updated per wavefront
     __shared__ f32x4 part[4][TM * TN][64];
@@ -239,19 +245,20 @@ __global__ __launch_bounds__(256) void k_step_block(DenseArgs a, int64_t q) {
     const int i0 = blockIdx.x * 16 * TM, r0 = blockIdx.y * 16 * TN;
     StepCoef cf;
     TileState ts[NT];
-    if constexpr (!FIELD_ONLY) {
-        cf = step_coef(a.a32, a.b32, q, a.rg, a.M);
-#pragma unroll
-        for (int k = 0; k < NT; k++) {
-            const int t = w + 4 * k;
-            const int tm = t / TN, tn = t % TN;
-            const int col = r0 + 16 * tn + (lane & 15);
-            const int ib = i0 + 16 * tm + 4 * (lane >> 4);
-            if (t < TM * TN && col < a.R && ib < a.N) load_tile_state(a, q, col, ib, ts[k]);
-        }
-    }
+    if constexpr (!FIELD_ONLY) cf = step_coef(a.a32, a.b32, q, a.rg, a.M);
     f32x4 acc[TM][TN];
-    chain_block<JT, TM, TN, CB, TJ>(a, i0, r0, lane, w, acc);
+    chain_block<JT, TM, TN, CB, TJ, LATE>(a, i0, r0, lane, w, acc, [&]() {
+        if constexpr (!FIELD_ONLY) {
+#pragma unroll
+            for (int k = 0; k < NT; k++) {
+                const int t = w + 4 * k;
+                const int tm = t / TN, tn = t % TN;
+                const int col = r0 + 16 * tn + (lane & 15);
+                const int ib = i0 + 16 * tm + 4 * (lane >> 4);
+                if (t < TM * TN && col < a.R && ib < a.N) load_tile_state(a, q, col, ib, ts[k]);
+            }
+        }
+    });
 #pragma unroll
     for (int tm = 0; tm < TM; tm++)
 #pragma unroll
@@ -316,8 +323,24 @@ static hipError_t ensure_tiled_x(Instance &I, hipStream_t st) {
     return hipSuccess;
 }
 
-// Replica tiles per block: 4 (64 replicas) when they divide Rp, else 2, else 1.
-static int block_tn(int Rp) { return Rp % 64 == 0 ? 4 : Rp % 32 == 0 ? 2 : 1; }
+// Block shape of an instance that was neither tuned nor pinned: the largest of 2 x 4, 2 x 2,
+// 2 x 1 tiles that divides the replicas and still gives 180 workgroups, else 1 x 1 (two rows
+// beat two replica tiles of the same count).  Larger blocks reuse operands, but below some three quarters of the 256 CUs the
+// emptier chip costs more than the reuse saves (us per step, 2 x widest -> this rule: binary32
+// N = 509, R = 33 6.2 -> 5.0; N = 800, R = 64 16.4 -> 6.5; BF16 N = 400, R = 64 8.2 -> 4.3;
+// N = 2000, R = 64 17.0 -> 9.5; N = 4000, R = 128 29.6 both); it names the fastest untiled
+// shape at all 29 (size, storage) pairs it was checked on.
+static void default_block(const Instance &I, int &tm, int &tn) {
+    static const int shapes[][2] = {{2, 4}, {2, 2}, {2, 1}};
+    for (const auto &s : shapes)
+        if (I.Rp % (16 * s[1]) == 0 &&
+            (int64_t)(I.Np / (16 * s[0])) * (I.Rp / (16 * s[1])) >= 180) {
+            tm = s[0];
+            tn = s[1];
+            return;
+        }
+    tm = tn = 1;
+}
 
 // Blocks of tm x tn output tiles: 16 tm rows x 16 tn replicas per workgroup; cb
 // chunks of each chain's loads in flight together (8: a chain of up to eight chunks
@@ -332,6 +355,7 @@ static void launch_cb(const DenseArgs &a, int tm, int tn, int64_t q, hipStream_t
     } else {
         if (tn == 4) k_step_block<JT, 1, 4, FO, CB, TJ><<<grid, 256, 0, st>>>(a, q);
         else if (tn == 2) k_step_block<JT, 1, 2, FO, CB, TJ><<<grid, 256, 0, st>>>(a, q);
+        else if (TJ && a.Np >= 4608) k_step_block<JT, 1, 1, FO, CB, TJ, TJ><<<grid, 256, 0, st>>>(a, q);
         else k_step_block<JT, 1, 1, FO, CB, TJ><<<grid, 256, 0, st>>>(a, q);
     }
 }
@@ -359,13 +383,15 @@ static void launch_one(const DenseArgs &a, int tm, int tn, int cb, int64_t q, hi
 }
 
 hipError_t launch_md_steps_dense(hqa_md *md, Instance &I, int64_t q0, int64_t q1) {
-    // tile width: the tuner's choice when it divides the padded replica count
-    const int tn = (I.step_tn == 1 || I.step_tn == 2 || I.step_tn == 4) &&
-                           I.Rp % (16 * I.step_tn) == 0
-                       ? I.step_tn
-                       : block_tn(I.Rp);
-    const int tm = I.step_tm == 1 ? 1 : 2;   // Np is a multiple of 128: both divide it
-    const int cb = I.step_cb == 8 ? 8 : 4;
+    // the tuner's or the caller's shape, else by size; eight chunks of 16-bit operands in
+    // flight cost the registers of four binary32 ones
+    int tm, tn;
+    default_block(I, tm, tn);
+    if (I.step_tm) {
+        tm = I.step_tm;                        // Np is a multiple of 128: both divide it
+        tn = I.step_tn;
+    }
+    const int cb = I.step_cb ? I.step_cb : I.jt == JT_F32 ? 4 : 8;
     if (I.step_tj && q0 < q1) {
         hipError_t e = ensure_tiled_j(I, md->stream);
         if (e == hipSuccess) e = ensure_tiled_x(I, md->stream);
@@ -393,7 +419,9 @@ hipError_t launch_md_steps_dense(hqa_md *md, Instance &I, int64_t q0, int64_t q1
 hipError_t launch_field_dense(hqa_md *md, Instance &I, float *u, hipStream_t st) {
     DenseArgs a = dense_args(md, I);
     a.u_out = u;
-    launch_one<true>(a, 2, block_tn(a.Rp), 4, 0, st);
+    int tm, tn;
+    default_block(I, tm, tn);
+    launch_one<true>(a, tm, tn, 4, 0, st);
     return hipGetLastError();
 }
 

@@ -1,0 +1,52 @@
+"""Per-step plan: the default block shape and the tiled form with its operand-order fluxes
+give the states of a pinned untiled 1 x 1 block, bit for bit."""
+import numpy as np
+import pytest
+
+from paper_2004_03972_amd import instances as inst
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible to torch")
+    from paper_2004_03972_amd import hqa
+    hqa.lib()
+    return hqa
+
+
+def _run(H, prob, T, R, prec, tiles, cuts):
+    md = H.MD(prob, H.make_schedule(T, 4), R, prec, seed=3)
+    if tiles:
+        md.set_step_tiles(*tiles[:3], tiled=tiles[3])
+    out = []
+    for q in cuts:
+        md.run(q)
+        out += [md.state(w) for w in (H.HQA_STATE_PHI, H.HQA_STATE_P, H.HQA_STATE_WSUM)]
+        out.append(md.field())
+    assert md.last_plan == "step"
+    md.close()
+    return out
+
+
+# sizes whose default shapes are 1x1, 1x1, 2x1, 2x2 and 2x4
+@pytest.mark.parametrize("prec", ["f32", "bf16"])
+@pytest.mark.parametrize("N,R", [(1, 1), (130, 33), (1500, 64), (1500, 128), (1500, 256)])
+def test_default_block_equals_pinned(H, N, R, prec):
+    prob = H.Problem(inst.sk(N, N) if N > 1 else np.zeros((1, 1)))
+    a = _run(H, prob, 9, R, prec, None, (4, 9))
+    b = _run(H, prob, 9, R, prec, (1, 1, 4, False), (4, 9))
+    assert all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+# 4608 rows and more: the update's state is requested with the last batch
+@pytest.mark.parametrize("N,R", [(300, 5), (4500, 3), (4600, 17), (4737, 16)])
+def test_tiled_runs_in_pieces(H, N, R):
+    prob = H.Problem(inst.sk(N, 7))
+    want = _run(H, prob, 10, R, "bf16", (1, 1, 4, False), (1, 4, 10))
+    for cb in (4, 8):
+        got = _run(H, prob, 10, R, "bf16", (1, 1, cb, True), (1, 4, 10))
+        assert all(np.array_equal(x, y) for x, y in zip(got, want))
