@@ -163,10 +163,11 @@ typedef struct hqa_md_opts {
  *   HQA_PLAN_STEP      one launch per MD step (any size).
  *   HQA_PLAN_CLUSTER   all steps in one cooperative launch; the workgroups of a
  *                      16-replica cluster own row blocks of J and exchange fluxes
- *                      every step through the L2 of the XCD they share (workgroup b
- *                      is assumed to run on XCD b mod 8, the dispatch order of a
- *                      single-partition MI355X).  A workgroup found on another XCD
- *                      aborts the launch, and the run (or hqa_md_sync) returns
+ *                      every step through the L2 of the XCD they share.  Clusters are
+ *                      formed from the XCD a workgroup finds itself on, for a device
+ *                      that deals workgroups out to eight XCDs in turn (a single-
+ *                      partition MI355X); a launch dealt out otherwise aborts, and the
+ *                      run (or hqa_md_sync) returns
  *                      HQA_EDEVICE naming the placement; the tuner then skips the
  *                      plan.  Every wait inside the launch is bounded.  With several
  *                      dense instances (BF16/FP8, N <= 2048), runs of up to 8

@@ -28,9 +28,9 @@
 // through, and the line stays in the L2 without a write-back to memory), and
 // consumers read it with agent-scope loads, which miss in the L1 and are served
 // by the L2.  Agent-scope stores would also write every entry through to memory,
-// which the exchange does not need.  Each workgroup checks at start that it runs
-// on the XCD its cluster assumes and otherwise aborts the launch (ERR_PLACEMENT);
-// an agent-scope acquire at start drops any copy of the cleared buffer that the
+// which the exchange does not need.  Clusters are formed from the XCD a workgroup
+// finds itself on; a launch whose workgroups were not dealt out to the XCDs in turn
+// aborts (ERR_PLACEMENT); an agent-scope acquire at start drops any copy of the cleared buffer that the
 // L2 may hold from an earlier launch.
 //
 // The binary32 update applies the same operation sequence as the per-step
@@ -117,18 +117,32 @@ __device__ __forceinline__ u32x4 ld16_agent(__amdgpu_buffer_rsrc_t r, int off) {
     return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 16);
 }
 
-// Aborts the launch unless the workgroup runs on XCD `xcd`; then drops stale L2
-// copies of the exchange buffer.  Returns false when the workgroup must leave.
-__device__ __forceinline__ bool check_placement(int32_t *abort_flag, int32_t *err, int xcd) {
+// The XCD this workgroup runs on.  Workgroups go to the eight XCDs in turn, so workgroup b
+// is on XCD (b + s) mod 8 for one s of the launch: usually 0, but it depends on what the
+// process dispatched before.  Clusters are formed by (XCD, b / 8), so members share an XCD
+// whatever s is; agree_rotation() aborts the launch if the workgroups' s differ.
+__device__ __forceinline__ int xcd_id() {
     uint32_t xcc;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
-    if ((int)(xcc & 0xfu) != xcd) {   // uniform over the workgroup
-        if (threadIdx.x == 0) {
+    return (int)(xcc & 0xfu);
+}
+
+// Every workgroup of the launch adds its s to a set (zeroed before the launch) and aborts
+// the launch when another one is in it, or when its XCD is none of the eight; then drops
+// stale L2 copies of the exchange buffer.  Returns false when the workgroup must leave.
+__device__ __forceinline__ bool agree_rotation(int32_t *rotations, int32_t *abort_flag, int32_t *err) {
+    __shared__ int s_bad;
+    if (threadIdx.x == 0) {
+        const int xcd = xcd_id(), bit = 1 << ((xcd - (int)blockIdx.x) & 7);
+        const int old = __hip_atomic_fetch_or(rotations, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_bad = xcd >= 8 || (old & ~bit) != 0;
+        if (s_bad) {
             __hip_atomic_store(abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             atomicOr(err, ERR_PLACEMENT);
         }
-        return false;
     }
+    __syncthreads();
+    if (s_bad) return false;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     return true;
 }
@@ -292,11 +306,11 @@ template <int JT, int TRW, bool JLDS>
 __global__ __launch_bounds__(256) void k_persist(PersistArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     // block -> (xcd, slot) -> (cluster, rank): cluster members share an XCD
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int xcd = xcd_id(), slot = blockIdx.x >> 3;
+    if (!agree_rotation(a.abort_flag - 1, a.abort_flag, a.err)) return;
     const int cl_in_xcd = slot / a.G, g = slot % a.G;
     const int c = cl_in_xcd * 8 + xcd;
     if (c >= a.C) return;
-    if (!check_placement(a.abort_flag, a.err, xcd)) return;
     __shared__ int s_dead;   // a thread gave up waiting
     if (threadIdx.x == 0) s_dead = 0;
     __syncthreads();
@@ -516,13 +530,13 @@ __device__ __forceinline__ PersistArgs for_instance(const PersistArgs &a0, int k
 template <int JT, int NG, int MP>
 __global__ __launch_bounds__(256) void k_persist_rj(PersistArgs a0) {
     __shared__ f32x4 part[2][4][4][64];   // [step parity][chain][row tile][lane]
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int xcd = xcd_id(), slot = blockIdx.x >> 3;
+    if (!agree_rotation(a0.abort_flag - 1, a0.abort_flag, a0.err)) return;
     const int cl_in_xcd = slot / a0.G, g = slot % a0.G;
     const int cg = cl_in_xcd * 8 + xcd;   // cluster of the launch
     if (cg >= a0.C) return;
     const int k = cg / a0.C1, c = cg - k * a0.C1;   // instance, cluster within it
     const PersistArgs a = for_instance(a0, k);
-    if (!check_placement(a.abort_flag, a.err, xcd)) return;
     __shared__ int s_dead[2];   // a thread gave up waiting (by step parity, like the partials)
     if (threadIdx.x < 2) s_dead[threadIdx.x] = 0;
     __syncthreads();
