@@ -1,5 +1,6 @@
 // k_readout.hip -- frozen/ambivalent sort, reduced problem, exact enumeration,
 // merge and exact Ising energies.
+#include <limits.h>
 #include <math.h>
 
 #include "exact_acc.h"
@@ -1520,17 +1521,29 @@ hipError_t launch_readout_batch(const std::vector<ReadoutJob> &jobs, int R, int 
 //   allowed when tabu_until[a] < t or D + d_a < D_best; a* = the allowed a with the
 //   smallest d_a (ties: smallest a); D += d_a*; f_b -= 2 J_a*b x_a* (old value) for
 //   b != a*; x_a* = -x_a*; tabu_until[a*] = t + tenure; if D < D_best keep x.
-// One workgroup of 1024 threads per replica, up to TABU_SPT spins per thread; J_ab is
-// read from the instance's binary64 couplings at the ambivalent indices.  The
-// operations are those of the definition in binary64 without contraction, so the
-// trajectory is the same whatever the launch shape.  Each move costs one workgroup
-// barrier (the wavefronts' candidates go to LDS slots double-buffered by parity).
+// One workgroup per replica.  A move is a chain of dependent latencies: the best candidate of
+// each thread, wavefront and workgroup, then one load of the chosen row's couplings, so the
+// search runs in few wavefronts with several spins a thread (one barrier per move, candidate
+// slots double-buffered by parity), and
+//  * k_tabu_int, for integral couplings and fields with small sums, keeps 2^13 d_a + (2 a +
+//    [x_a > 0]) in one signed 32-bit word, whose order is that of (gain, index), so that a
+//    reduction level is one minimum; J comes from the instance's compact exact copy where it
+//    has one (1 to 4 bytes a coupling: an L2's worth instead of the memory-side cache);
+//  * k_tabu, for real couplings, takes the minimum of the gains first and settles ties by
+//    index only among lanes that hold it.
+// The operations are those of the definition in binary64 without contraction (integers of
+// that size are exact in both), so the trajectory is the same whatever the launch shape.
+// Measured per move: K2000, R = 16, n = 1000: 1024 threads, candidates (gain, index) reduced as
+// pairs and binary64 couplings 1.66 us; k_tabu_int 0.67 us (256, 1024
+// threads 0.87, 0.85). Real couplings, N = 2000, n = 1000: 1.64 -> 1.13 us; n = 60: 1.37 -> 0.37 (0.26
+// integral).
 // ---------------------------------------------------------------------------
-#define TABU_SPT 4
 struct TabuArgs {
     int N, R, n, csr, tenure;
     int64_t iters;
     const double *J;
+    const void *Js;       // compact exact copy of J (k_tabu_int), row pitch ldj
+    int ldj;
     const int32_t *rp, *ci;
     const int32_t *amb;
     const int8_t *spins;
@@ -1550,144 +1563,331 @@ __device__ __forceinline__ double tabu_j(const TabuArgs &a, int i, int j) {
     return (lo < a.rp[i + 1] && a.ci[lo] == j) ? a.J[lo] : 0.0;
 }
 
-// The better of two candidates (gain d, key 2 index + [old spin > 0]): smaller d, ties
-// to the smaller index.  Indices are distinct, so this is a total order and any
-// reduction tree picks the same candidate.
-__device__ __forceinline__ void tabu_better(double &d, int &key, double d2, int key2) {
-    if (d2 < d || (d2 == d && key2 < key)) { d = d2; key = key2; }
-}
-
-// One reduction level between lane pairs given by a DPP pattern inside 16-lane rows
-// (quad permutations, half-row and row mirrors): register moves, no LDS.
+// Minimum over the wavefront, in every lane: quad xor 1 and 2, the half-row mirror (lane i
+// with 7 - i) and the row mirror (i with 15 - i), then the permlane swaps across rows.
 template <int CTRL>
-__device__ __forceinline__ void tabu_dpp(double &d, int &key) {
-    const int lo = __double2loint(d), hi = __double2hiint(d);
-    const int lo2 = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false);
-    const int hi2 = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false);
-    const int k2 = __builtin_amdgcn_update_dpp(key, key, CTRL, 0xF, 0xF, false);
-    tabu_better(d, key, __hiloint2double(hi2, lo2), k2);
+__device__ __forceinline__ int dpp_i32(int x) {
+    return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false);
 }
-
-// The level between lane l and l ^ 16 (ROW32 = false) or l ^ 32: the permlane swaps
-// hand every lane both members of its pair, and both take the better one.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+    return __hiloint2double(dpp_i32<CTRL>(__double2hiint(x)), dpp_i32<CTRL>(__double2loint(x)));
+}
+__device__ __forceinline__ int wave_min_i32(int x) {
+    x = min(x, dpp_i32<0xB1>(x));
+    x = min(x, dpp_i32<0x4E>(x));
+    x = min(x, dpp_i32<0x141>(x));
+    x = min(x, dpp_i32<0x140>(x));
+    const auto p = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)x, false, false);
+    x = min((int)p[0], (int)p[1]);
+    const auto q = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)x, false, false);
+    return min((int)q[0], (int)q[1]);
+}
 template <bool ROW32>
-__device__ __forceinline__ void tabu_swap(double &d, int &key) {
-    const unsigned lo = (unsigned)__double2loint(d), hi = (unsigned)__double2hiint(d);
+__device__ __forceinline__ double swap_min_f64(double x) {
+    const unsigned lo = (unsigned)__double2loint(x), hi = (unsigned)__double2hiint(x);
     const auto l = ROW32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
                          : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
     const auto h = ROW32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
                          : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    const auto k = ROW32 ? __builtin_amdgcn_permlane32_swap((unsigned)key, (unsigned)key, false, false)
-                         : __builtin_amdgcn_permlane16_swap((unsigned)key, (unsigned)key, false, false);
-    d = __hiloint2double((int)h[0], (int)l[0]);
-    key = (int)k[0];
-    tabu_better(d, key, __hiloint2double((int)h[1], (int)l[1]), (int)k[1]);
+    return fmin(__hiloint2double((int)h[0], (int)l[0]), __hiloint2double((int)h[1], (int)l[1]));
+}
+// NaN gains are never the minimum (fmin returns the number).
+__device__ __forceinline__ double wave_min_f64(double x) {
+    x = fmin(x, dpp_f64<0xB1>(x));
+    x = fmin(x, dpp_f64<0x4E>(x));
+    x = fmin(x, dpp_f64<0x141>(x));
+    x = fmin(x, dpp_f64<0x140>(x));
+    x = swap_min_f64<false>(x);
+    return swap_min_f64<true>(x);
 }
 
-// Best candidate of the 16 lanes of each row: quad xor 1 and 2, then the half-row
-// mirror (lane i with 7 - i) and the row mirror (i with 15 - i).
-__device__ __forceinline__ void tabu_row_min(double &d, int &key) {
-    tabu_dpp<0xB1>(d, key);    // quad_perm [1, 0, 3, 2]
-    tabu_dpp<0x4E>(d, key);    // quad_perm [2, 3, 0, 1]
-    tabu_dpp<0x141>(d, key);   // row_half_mirror
-    tabu_dpp<0x140>(d, key);   // row_mirror
+// Minimum over NW (2 .. 16) slots that lane v holds as slot v mod NW.
+template <int NW>
+__device__ __forceinline__ int slots_min_i32(int x) {
+    x = min(x, dpp_i32<0xB1>(x));
+    if (NW > 2) x = min(x, dpp_i32<0x4E>(x));
+    if (NW > 4) x = min(x, dpp_i32<0x141>(x));
+    if (NW > 8) x = min(x, dpp_i32<0x140>(x));
+    return x;
+}
+template <int NW>
+__device__ __forceinline__ double slots_min_f64(double x) {
+    x = fmin(x, dpp_f64<0xB1>(x));
+    if (NW > 2) x = fmin(x, dpp_f64<0x4E>(x));
+    if (NW > 4) x = fmin(x, dpp_f64<0x141>(x));
+    if (NW > 8) x = fmin(x, dpp_f64<0x140>(x));
+    return x;
 }
 
-__global__ __launch_bounds__(1024) void k_tabu(TabuArgs a) {
-    __shared__ int8_t sx[TABU_SPT * 1024];      // starting spins of the ambivalent set
-    __shared__ int32_t sA[TABU_SPT * 1024];     // their indices (a move reads one)
-    __shared__ double sd[2][16];
-    __shared__ int sk[2][16];
+enum { TABU_MAXN = 4096 };
+
+// Spins a = tid + TPB k, k < SPT.
+template <int TPB, int SPT>
+__global__ __launch_bounds__(TPB) void k_tabu(TabuArgs a) {
+    constexpr int NW = TPB / 64;
+    __shared__ int8_t sx[TPB * SPT];            // starting spins of the ambivalent set
+    __shared__ int32_t sA[TPB * SPT];           // their indices
+    __shared__ double sd[2][NW];
+    __shared__ int2 sk[2][NW];                  // (2 a + [x_a > 0], index of spin a)
     const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n = a.n, N = a.N;
     const int32_t *A = a.amb + (int64_t)r * n;
     const int8_t *s0 = a.spins + (int64_t)r * N;
-    for (int b = tid; b < n; b += 1024) {
+    for (int b = tid; b < n; b += TPB) {
         const int i = A[b];
         sA[b] = i;
         sx[b] = s0[i];
     }
     __syncthreads();
-    double f[TABU_SPT];
-    int x[TABU_SPT], xb[TABU_SPT], Ai[TABU_SPT];
-    int64_t until[TABU_SPT];
+    double f[SPT];
+    int x[SPT], xb[SPT], Ai[SPT];
+    int64_t until[SPT];
 #pragma unroll
-    for (int k = 0; k < TABU_SPT; k++) {
-        const int ai = tid + 1024 * k;
+    for (int k = 0; k < SPT; k++) {
+        const int ai = tid + TPB * k;
         f[k] = 0.0; x[k] = 1; xb[k] = 1; Ai[k] = 0; until[k] = 0;
         if (ai < n) {
             Ai[k] = sA[ai];
             x[k] = xb[k] = sx[ai];
-            double acc = a.h_eff[(int64_t)r * n + ai];
-            if (!a.csr) {
-                // the loads of a row are independent, so several are in flight; the
-                // sum itself keeps the order b = 0, 1, ...
-                const double *Jr = a.J + (int64_t)Ai[k] * N;
-#pragma unroll 8
-                for (int b = 0; b < n; b++) {
-                    const double J = Jr[sA[b]];
-                    if (b != ai) acc = acc + J * (double)sx[b];
-                }
-            } else {
-                for (int b = 0; b < n; b++)
-                    if (b != ai) acc = acc + tabu_j(a, Ai[k], sA[b]) * (double)sx[b];
-            }
-            f[k] = acc;
+            f[k] = a.h_eff[(int64_t)r * n + ai];
         }
+    }
+    // the loads of a row are independent, so several are in flight; each sum keeps the
+    // order b = 0, 1, ...
+    if (!a.csr) {
+#pragma unroll 8
+        for (int b = 0; b < n; b++) {
+            const int col = sA[b];
+            const double xd = (double)sx[b];
+#pragma unroll
+            for (int k = 0; k < SPT; k++) {
+                const double J = a.J[(int64_t)Ai[k] * N + col];
+                if (b != tid + TPB * k) f[k] = f[k] + J * xd;
+            }
+        }
+    } else {
+        for (int b = 0; b < n; b++)
+#pragma unroll
+            for (int k = 0; k < SPT; k++)
+                if (tid + TPB * k < n && b != tid + TPB * k)
+                    f[k] = f[k] + tabu_j(a, Ai[k], sA[b]) * (double)sx[b];
     }
     const int tenure = min(a.tenure, n - 1);
     double D = 0.0, Db = 0.0;
     for (int64_t t = 1; t <= a.iters; t++) {
         const int par = (int)(t & 1);
         double bd = INFINITY;
-        int bk = INT_MAX;
+        int2 bk = make_int2(INT_MAX, 0);
 #pragma unroll
-        for (int k = 0; k < TABU_SPT; k++) {
-            const int ai = tid + 1024 * k;
-            if (ai >= n) continue;
+        for (int k = 0; k < SPT; k++) {        // ascending index: the first of equals stays
+            const int ai = tid + TPB * k;
             const double d = x[k] > 0 ? -2.0 * f[k] : 2.0 * f[k];
-            if (until[k] < t || D + d < Db) tabu_better(bd, bk, d, 2 * ai + (x[k] > 0));
+            if (ai < n && (until[k] < t || D + d < Db) && (d < bd || (d == bd && bk.x == INT_MAX))) {
+                bd = d;
+                bk = make_int2(2 * ai + (x[k] > 0), Ai[k]);
+            }
         }
-        tabu_row_min(bd, bk);
-        tabu_swap<false>(bd, bk);
-        tabu_swap<true>(bd, bk);
-        if (lane == 0) { sd[par][w] = bd; sk[par][w] = bk; }
-        __syncthreads();
-        // each wavefront combines the 16 slots: lane v takes slot v mod 16
-        bd = sd[par][lane & 15];
-        bk = sk[par][lane & 15];
-        tabu_row_min(bd, bk);
-        const int bi = bk >> 1, bo = (bk & 1) ? 1 : -1;
+        const double m = wave_min_f64(bd);
+        // the owner of the wavefront's best: the smallest index among the lanes that hold it
+        const bool tied = bd == m && bk.x != INT_MAX;
+        const uint64_t mask = __ballot(tied);
+        bool own = tied;
+        if (mask & (mask - 1)) {   // uniform: the minimum needs every lane
+            const int first = wave_min_i32(tied ? bk.x : INT_MAX);
+            own = tied && bk.x == first;
+        }
+        if (NW == 1) {
+            // all in registers: the owner's lane is broadcast
+            const int src = mask ? __ffsll((unsigned long long)__ballot(own)) - 1 : 0;
+            bk.x = __builtin_amdgcn_readlane(bk.x, src);
+            bk.y = __builtin_amdgcn_readlane(bk.y, src);
+            bd = m;
+        } else {
+            if (own || (mask == 0 && lane == 0)) { sd[par][w] = bd; sk[par][w] = bk; }
+            __syncthreads();
+            // lane v takes slot v mod NW
+            bd = sd[par][lane & (NW - 1)];
+            bk = sk[par][lane & (NW - 1)];
+            const double mm = slots_min_f64<NW>(bd);
+            const bool tied2 = bd == mm && bk.x != INT_MAX;
+            uint64_t mask2 = __ballot(tied2) & ((1ull << NW) - 1ull);
+            if (mask2 & (mask2 - 1)) {
+                const int first = wave_min_i32(tied2 ? bk.x : INT_MAX);
+                mask2 = __ballot(tied2 && bk.x == first);
+            }
+            const int src = mask2 ? __ffsll((unsigned long long)mask2) - 1 : 0;
+            bk.x = __builtin_amdgcn_readlane(bk.x, src);
+            bk.y = __builtin_amdgcn_readlane(bk.y, src);
+            bd = mm;
+        }
+        const int bi = bk.x >> 1, bo = (bk.x & 1) ? 1 : -1;
         // At most tenure < n spins are tabu, so some move is allowed; only gains that
         // are all NaN (fields overflowed) leave none.  bi is the same in every thread.
-        if (bk == INT_MAX) break;
+        if (bk.x == INT_MAX) break;
         D = D + bd;
-        const int rowj = sA[bi];
+        const int rowj = __builtin_amdgcn_readfirstlane(bk.y);
+        double J[SPT];
 #pragma unroll
-        for (int k = 0; k < TABU_SPT; k++) {
-            const int ai = tid + 1024 * k;
-            if (ai >= n) continue;
+        for (int k = 0; k < SPT; k++) J[k] = tid + TPB * k < n ? tabu_j(a, rowj, Ai[k]) : 0.0;
+#pragma unroll
+        for (int k = 0; k < SPT; k++) {
+            const int ai = tid + TPB * k;
             if (ai == bi) {
                 x[k] = -x[k];
                 until[k] = t + tenure;
             } else {
-                const double J = tabu_j(a, rowj, Ai[k]);
-                f[k] = f[k] - (bo > 0 ? 2.0 * J : -2.0 * J);
+                f[k] = f[k] - (bo > 0 ? 2.0 * J[k] : -2.0 * J[k]);
             }
         }
         if (D < Db) {   // uniform
             Db = D;
 #pragma unroll
-            for (int k = 0; k < TABU_SPT; k++) xb[k] = x[k];
+            for (int k = 0; k < SPT; k++) xb[k] = x[k];
         }
     }
     int8_t *so_r = a.spins_out + (int64_t)r * N;
 #pragma unroll
-    for (int k = 0; k < TABU_SPT; k++) {
-        const int ai = tid + 1024 * k;
+    for (int k = 0; k < SPT; k++) {
+        const int ai = tid + TPB * k;
         if (ai < n) so_r[Ai[k]] = (int8_t)xb[k];
     }
     if (tid == 0) a.d_best[r] = Db;
+}
+
+// Integral coupling (i, j) from the storage JT (JT_BIT here: the binary64 J).
+template <int JT>
+__device__ __forceinline__ int tabu_ji(const TabuArgs &a, const uint8_t *row, int j) {
+    if constexpr (JT == JT_FP8) {
+        const uint32_t b = row[j];
+        return (int)__builtin_amdgcn_cvt_f32_fp8((int)b, 0);
+    } else if constexpr (JT == JT_BF16) {
+        return (int)__uint_as_float((uint32_t)((const uint16_t *)row)[j] << 16);
+    } else if constexpr (JT == JT_F32) {
+        return (int)((const float *)row)[j];
+    } else {
+        return (int)((const double *)row)[j];
+    }
+}
+
+template <int JT>
+__device__ __forceinline__ const uint8_t *tabu_row(const TabuArgs &a, int i) {
+    constexpr int esz = JT == JT_FP8 ? 1 : JT == JT_BF16 ? 2 : JT == JT_F32 ? 4 : 8;
+    return (const uint8_t *)(JT == JT_BIT ? (const void *)a.J : a.Js) +
+           (int64_t)i * (JT == JT_BIT ? a.N : a.ldj) * esz;
+}
+
+// Dense integral instances with 2 (N + 1) max(|J|, |h|) below 2^16 (see launch_tabu).  d[k]
+// holds the gain -2 x f; a flip of b adds 4 x_a x_b J_ab to the others and negates its own.
+template <int TPB, int SPT, int JT>
+__global__ __launch_bounds__(TPB) void k_tabu_int(TabuArgs a) {
+    constexpr int NW = TPB / 64;
+    __shared__ int8_t sx[TPB * SPT];
+    __shared__ int32_t sA[TPB * SPT];
+    __shared__ __align__(16) int2 sk[2][NW];    // (key, index of its spin)
+    const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int n = a.n, N = a.N;
+    const int32_t *A = a.amb + (int64_t)r * n;
+    const int8_t *s0 = a.spins + (int64_t)r * N;
+    for (int b = tid; b < n; b += TPB) {
+        const int i = A[b];
+        sA[b] = i;
+        sx[b] = s0[i];
+    }
+    __syncthreads();
+    int d[SPT], x[SPT], xb[SPT], Ai[SPT], until[SPT];
+#pragma unroll
+    for (int k = 0; k < SPT; k++) {
+        const int ai = tid + TPB * k;
+        d[k] = 0; x[k] = xb[k] = 1; Ai[k] = 0; until[k] = 0;
+        if (ai < n) {
+            Ai[k] = sA[ai];
+            x[k] = xb[k] = sx[ai];
+            d[k] = (int)a.h_eff[(int64_t)r * n + ai];
+        }
+    }
+    // d holds f_a here: J is symmetric, so row b is read along the threads' columns
+#pragma unroll 8
+    for (int b = 0; b < n; b++) {
+        const uint8_t *row = tabu_row<JT>(a, sA[b]);
+        const int xs = sx[b];
+#pragma unroll
+        for (int k = 0; k < SPT; k++) {
+            const int J = tabu_ji<JT>(a, row, Ai[k]);
+            d[k] += b != tid + TPB * k ? J * xs : 0;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < SPT; k++) d[k] = -2 * x[k] * d[k];
+    const int tenure = min(a.tenure, n - 1);
+    int D = 0, Db = 0;
+    for (int t = 1; t <= (int)a.iters; t++) {
+        const int par = t & 1;
+        int key = INT_MAX, ka = 0;
+#pragma unroll
+        for (int k = 0; k < SPT; k++) {
+            const int ai = tid + TPB * k;
+            const int kk = (d[k] << 13) + 2 * ai + (x[k] > 0);
+            if (ai < n && (until[k] < t || D + d[k] < Db) && kk < key) {
+                key = kk;
+                ka = Ai[k];
+            }
+        }
+        const int m = wave_min_i32(key);
+        int2 bk;
+        if (NW == 1) {
+            const uint64_t mask = __ballot(key == m);      // keys are distinct
+            bk.x = m;
+            bk.y = __builtin_amdgcn_readlane(ka, __ffsll((unsigned long long)mask) - 1);
+        } else {
+            if (key == m) sk[par][w] = make_int2(key, ka);
+            __syncthreads();
+            bk = sk[par][lane & (NW - 1)];
+            const int mm = slots_min_i32<NW>(bk.x);
+            bk.y = __builtin_amdgcn_readlane(bk.y, __ffsll((unsigned long long)__ballot(bk.x == mm)) - 1);
+            bk.x = mm;
+        }
+        const int key1 = __builtin_amdgcn_readfirstlane(bk.x);
+        if (key1 == INT_MAX) break;                        // not reached: tenure < n
+        const int bi = (key1 >> 1) & (TABU_MAXN - 1), bo4 = (key1 & 1) ? 4 : -4;
+        D += key1 >> 13;
+        const uint8_t *row = tabu_row<JT>(a, __builtin_amdgcn_readfirstlane(bk.y));
+        int J[SPT];
+#pragma unroll
+        for (int k = 0; k < SPT; k++) J[k] = tabu_ji<JT>(a, row, Ai[k]);
+#pragma unroll
+        for (int k = 0; k < SPT; k++) {
+            if (tid + TPB * k == bi) {
+                x[k] = -x[k];
+                d[k] = -d[k];
+                until[k] = t + tenure;
+            } else {
+                d[k] += x[k] * (bo4 * J[k]);
+            }
+        }
+        if (D < Db) {   // uniform
+            Db = D;
+#pragma unroll
+            for (int k = 0; k < SPT; k++) xb[k] = x[k];
+        }
+    }
+    int8_t *so_r = a.spins_out + (int64_t)r * N;
+#pragma unroll
+    for (int k = 0; k < SPT; k++) {
+        const int ai = tid + TPB * k;
+        if (ai < n) so_r[Ai[k]] = (int8_t)xb[k];
+    }
+    if (tid == 0) a.d_best[r] = (double)Db;
+}
+
+template <int TPB, int SPT>
+static void launch_tabu_int(const TabuArgs &a, int jt, hipStream_t st) {
+    switch (jt) {
+        case JT_FP8: k_tabu_int<TPB, SPT, JT_FP8><<<a.R, TPB, 0, st>>>(a); break;
+        case JT_BF16: k_tabu_int<TPB, SPT, JT_BF16><<<a.R, TPB, 0, st>>>(a); break;
+        case JT_F32: k_tabu_int<TPB, SPT, JT_F32><<<a.R, TPB, 0, st>>>(a); break;
+        default: k_tabu_int<TPB, SPT, JT_BIT><<<a.R, TPB, 0, st>>>(a); break;
+    }
 }
 
 hipError_t launch_tabu(const Instance &I, int R, int n, const int32_t *amb, const int8_t *spins,
@@ -1697,8 +1897,36 @@ hipError_t launch_tabu(const Instance &I, int R, int n, const int32_t *amb, cons
     a.N = I.N; a.R = R; a.n = n; a.csr = I.layout == HQA_CSR; a.tenure = tenure; a.iters = iters;
     a.J = I.J64; a.rp = I.rp; a.ci = I.ci; a.amb = amb; a.spins = spins; a.h_eff = h_eff;
     a.spins_out = spins_out; a.d_best = d_best;
+    a.Js = nullptr; a.ldj = 0;
     if (R == 0 || n == 0) return hipSuccess;
-    k_tabu<<<R, 1024, 0, st>>>(a);
+    // |f_a| <= (N + 1) 2^(msb + 1): gains below 2^17 leave 13 bits of a signed word to the
+    // index, |D| <= 2 (N + 1)^2 2^(msb + 1) stays below 2^31, and moves are counted in 32 bits
+    const double big = I.es.lsb != INT32_MIN ? std::ldexp((double)I.N + 1.0, I.es.msb + 2) : 1e300;
+    const bool ints = !a.csr && I.j_integral && big < 65536.0 &&
+                      big * ((double)I.N + 1.0) < 2147483648.0 && iters < (1ll << 30);
+    if (ints) {
+        int jt = JT_BIT;
+        if (I.js_exact && I.Js) {
+            jt = (int)I.jt;
+            a.Js = I.Js;
+            a.ldj = I.Np;
+        }
+        if (n <= 64) launch_tabu_int<64, 1>(a, jt, st);
+        else if (n <= 128) launch_tabu_int<128, 1>(a, jt, st);
+        else if (n <= 256) launch_tabu_int<256, 1>(a, jt, st);
+        else if (n <= 512) launch_tabu_int<512, 1>(a, jt, st);
+        else if (n <= 1024) launch_tabu_int<512, 2>(a, jt, st);
+        else if (n <= 2048) launch_tabu_int<512, 4>(a, jt, st);
+        else launch_tabu_int<1024, 4>(a, jt, st);
+    } else {
+        if (n <= 64) k_tabu<64, 1><<<R, 64, 0, st>>>(a);
+        else if (n <= 128) k_tabu<128, 1><<<R, 128, 0, st>>>(a);
+        else if (n <= 256) k_tabu<256, 1><<<R, 256, 0, st>>>(a);
+        else if (n <= 512) k_tabu<512, 1><<<R, 512, 0, st>>>(a);
+        else if (n <= 1024) k_tabu<512, 2><<<R, 512, 0, st>>>(a);
+        else if (n <= 2048) k_tabu<512, 4><<<R, 512, 0, st>>>(a);
+        else k_tabu<1024, 4><<<R, 1024, 0, st>>>(a);
+    }
     return hipGetLastError();
 }
 
