@@ -2,12 +2,12 @@
 //
 // A batch of uneven instances (sizes N_k, one shared schedule and replica count)
 // advances step by step; each step is one launch over a tile table of (instance, 128
-// rows, 64 replicas) tiles, whatever the storage type (FP32, BF16, FP8), so with 64
+// rows, 64 replicas) tiles (32 or 16 replicas in small batches), whatever the storage type (FP32, BF16, FP8), so with 64
 // replicas each J row block is read once per step.  An FP8 instance whose couplings are
 // all 0 or 1 (unit-weight MAX-CUT) is streamed from a copy with one bit per coupling,
-// expanded in registers to the same BF16 operands.  The tiles of an instance share
-// one XCD, and instances are placed longest-first (LPT by padded size), so the largest
-// instances start first and the short tiles fill the tail of the step.  The field
+// expanded in registers to the same BF16 operands.  In large batches the tiles of an
+// instance share one XCD; tiles are placed longest-first (LPT by padded size), so the
+// largest instances start first and the short tiles fill the tail of the step.  The field
 // uses the chunk-to-chain decomposition of the other dense kernels, and the update
 // the same binary32 sequence, so a batched instance evolves bit-identically to the
 // same instance run alone.
@@ -117,10 +117,20 @@ __device__ __forceinline__ bf16x8 a_chunk(const W *g, int j) {
     }
 }
 
-template <int JT>
+// RT replica tiles of 16 per workgroup (4, 2 or 1; see build_plan): 512 threads stage
+// 16 RT replicas x 128 columns, 8 RT bytes each.
+template <int RT>
+struct FluxStage {
+    typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned u32x2_b;
+    using V = typename std::conditional<RT == 1, u32x2_b, u32x4_b>::type;
+    static constexpr int NV = RT == 4 ? 2 : 1, TPR = 32 / RT, COLS = 4 * RT;
+    V v[NV];
+};
+
+template <int JT, int RT>
 __device__ __forceinline__ void batch_lds_tile(const BatchArgs &a, int64_t q, const BatchTile &tl,
                                                const BatchInst &I,
-                                               bf16 (&Bs)[2][BL_REPS][BL_LDB]) {
+                                               bf16 (&Bs)[2][16 * RT][BL_LDB]) {
     const int tid = threadIdx.x, lane = tid & 63, kg = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i0 = tl.i0 + 16 * w;
@@ -143,16 +153,19 @@ __device__ __forceinline__ void batch_lds_tile(const BatchArgs &a, int64_t q, co
     const int jtile = min(i0, I.N - 1) / 16;
     const auto *Jt = gld<JW>((const uint8_t *)I.Jt + (int64_t)jtile * I.nrounds * 64 * (int)sizeof(JW) * NA);
     const int jl = lane * NA;
-    // staging: thread -> (replica row, 16-column segment) of the 64 x 128 block
-    const int srow = tid >> 3, sseg = tid & 7;
-    const auto *Bsrc = gld<u32x4_b>(xb_in + (int64_t)r0 * I.ld);
-    const int sl = ((min(r0 + srow, a.R - 1) - r0) * I.ld + 16 * sseg) / 8;
-    u32x4_b *Bdst0 = (u32x4_b *)&Bs[0][srow][16 * sseg];
-    u32x4_b *Bdst1 = (u32x4_b *)&Bs[1][srow][16 * sseg];
+    // staging: thread -> (replica row, segment of COLS columns) of the 16 RT x 128 block
+    using FS = FluxStage<RT>;
+    using FV = typename FS::V;
+    const int srow = tid / FS::TPR, sseg = tid % FS::TPR;
+    const auto *Bsrc = gld<FV>(xb_in + (int64_t)r0 * I.ld);
+    constexpr int EV = (int)sizeof(FV) / 2;               // columns per vector
+    const int sl = ((min(r0 + srow, a.R - 1) - r0) * I.ld + FS::COLS * sseg) / EV;
+    FV *Bdst0 = (FV *)&Bs[0][srow][FS::COLS * sseg];
+    FV *Bdst1 = (FV *)&Bs[1][srow][FS::COLS * sseg];
 
-    f32x4 acc[4][4];
+    f32x4 acc[RT][4];
 #pragma unroll
-    for (int rt = 0; rt < 4; rt++)
+    for (int rt = 0; rt < RT; rt++)
 #pragma unroll
         for (int j = 0; j < 4; j++) acc[rt][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
@@ -163,21 +176,24 @@ __device__ __forceinline__ void batch_lds_tile(const BatchArgs &a, int64_t q, co
     // leaves the couplings in flight across the barrier.  At 128 VGPRs two workgroups
     // share a CU, and each covers the other's waits, prologue and epilogue.
     JW A0[NA], A1[NA];
-    u32x4_b S0a, S0b;
+    FS S0;
 #define HQA_LOAD_J(g, A)                                                              \
     do {                                                                              \
         _Pragma("unroll") for (int j = 0; j < NA; j++) A[j] = Jt[(g) * 64 * NA + jl + j]; \
     } while (0)
-#define HQA_LOAD_S(g, Sa, Sb)                                                         \
+#define HQA_LOAD_S(g, S)                                                              \
     do {                                                                              \
-        Sa = Bsrc[sl + 16 * (g)];                                                     \
-        Sb = Bsrc[sl + 16 * (g) + 1];                                                 \
+        _Pragma("unroll") for (int j = 0; j < FS::NV; j++) S.v[j] = Bsrc[sl + (128 / EV) * (g) + j]; \
+    } while (0)
+#define HQA_PUT_S(dst, S)                                                             \
+    do {                                                                              \
+        _Pragma("unroll") for (int j = 0; j < FS::NV; j++) dst[j] = S.v[j];          \
     } while (0)
 #define HQA_MFMA_GROUP(buf, A)                                                        \
     do {                                                                              \
         _Pragma("unroll") for (int j = 0; j < 4; j++) {                              \
             const bf16x8 av = a_chunk<JT>(A, j);                                      \
-            _Pragma("unroll") for (int rt = 0; rt < 4; rt++) {                       \
+            _Pragma("unroll") for (int rt = 0; rt < RT; rt++) {                      \
                 const bf16x8 bv = *(const bf16x8 *)&Bs[buf][16 * rt + (lane & 15)][32 * j + 8 * kg]; \
                 acc[rt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[rt][j], 0, 0, 0); \
             }                                                                         \
@@ -187,81 +203,76 @@ __device__ __forceinline__ void batch_lds_tile(const BatchArgs &a, int64_t q, co
     if constexpr (JT == JT_BIT) {
         // bit tiles hold two flux register sets (their couplings take one register per
         // set): the fluxes of group g + 2 are requested when group g begins
-        u32x4_b S1a, S1b;
-        HQA_LOAD_S(0, S0a, S0b);
+        FS S1;
+        HQA_LOAD_S(0, S0);
         HQA_LOAD_J(0, A0);
-        Bdst0[0] = S0a;
-        Bdst0[1] = S0b;
+        HQA_PUT_S(Bdst0, S0);
         __syncthreads();
-        HQA_LOAD_S(min(1, gl), S0a, S0b);
+        HQA_LOAD_S(min(1, gl), S0);
         for (int gi = 0; gi < ngroups; gi += 2) {
-            HQA_LOAD_S(min(gi + 2, gl), S1a, S1b);
+            HQA_LOAD_S(min(gi + 2, gl), S1);
             HQA_LOAD_J(min(gi + 1, gl), A1);
             __builtin_amdgcn_sched_barrier(0);
             HQA_MFMA_GROUP(0, A0);
-            Bdst1[0] = S0a;
-            Bdst1[1] = S0b;
+            HQA_PUT_S(Bdst1, S0);
             __syncthreads();
             if (gi + 1 >= ngroups) break;
-            HQA_LOAD_S(min(gi + 3, gl), S0a, S0b);
+            HQA_LOAD_S(min(gi + 3, gl), S0);
             HQA_LOAD_J(min(gi + 2, gl), A0);
             __builtin_amdgcn_sched_barrier(0);
             HQA_MFMA_GROUP(1, A1);
-            Bdst0[0] = S1a;
-            Bdst0[1] = S1b;
+            HQA_PUT_S(Bdst0, S1);
             __syncthreads();
         }
     } else {
-        HQA_LOAD_S(0, S0a, S0b);
+        HQA_LOAD_S(0, S0);
         HQA_LOAD_J(0, A0);
-        Bdst0[0] = S0a;
-        Bdst0[1] = S0b;
+        HQA_PUT_S(Bdst0, S0);
         __syncthreads();
         // even groups compute from A0 and LDS buffer 0, odd ones from A1 and buffer 1
         for (int gi = 0; gi < ngroups; gi += 2) {
-            HQA_LOAD_S(min(gi + 1, gl), S0a, S0b);
+            HQA_LOAD_S(min(gi + 1, gl), S0);
             HQA_LOAD_J(min(gi + 1, gl), A1);
             __builtin_amdgcn_sched_barrier(0);
             HQA_MFMA_GROUP(0, A0);
-            Bdst1[0] = S0a;
-            Bdst1[1] = S0b;
+            HQA_PUT_S(Bdst1, S0);
             __syncthreads();
             if (gi + 1 >= ngroups) break;
-            HQA_LOAD_S(min(gi + 2, gl), S0a, S0b);
+            HQA_LOAD_S(min(gi + 2, gl), S0);
             HQA_LOAD_J(min(gi + 2, gl), A0);
             __builtin_amdgcn_sched_barrier(0);
             HQA_MFMA_GROUP(1, A1);
-            Bdst0[0] = S0a;
-            Bdst0[1] = S0b;
+            HQA_PUT_S(Bdst0, S0);
             __syncthreads();
         }
     }
 #undef HQA_LOAD_J
 #undef HQA_LOAD_S
+#undef HQA_PUT_S
 #undef HQA_MFMA_GROUP
 
     // Epilogue with full-line accesses: the fields pass through LDS (the flux stages
-    // are free after the last barrier), and thread (replica t / 8, j = t % 8) updates
-    // rows 32 v + 4 j .. 32 v + 4 j + 3 for v = 0..3, so the eight threads of a replica
-    // read and write one whole 128-byte line of fluxes and momenta per instruction.
+    // are free after the last barrier), and thread (replica t / TPR, j = t % TPR)
+    // updates rows 4 TPR v + 4 j .. + 3 for v < RT, so the eight or more threads of a replica
+    // read and write whole 128-byte lines of fluxes and momenta per instruction.
     {
-        float *U = (float *)&Bs[0][0][0];                  // [64 replicas][136]
+        float *U = (float *)&Bs[0][0][0];                  // [16 RT replicas][136]
         constexpr int UL = 136;
 #pragma unroll
-        for (int rt = 0; rt < 4; rt++) {
+        for (int rt = 0; rt < RT; rt++) {
             const f32x4 parts[4] = {acc[rt][0], acc[rt][1], acc[rt][2], acc[rt][3]};
             const f32x4 u = combine4(parts);
             *(f32x4 *)&U[(16 * rt + (lane & 15)) * UL + 16 * w + 4 * kg] = u;
         }
         // the fluxes and momenta are requested before the barrier (the couplings'
         // registers are free by now), so their latency overlaps the exchange
-        const int rep = tid >> 3, j8 = tid & 7;
+        const int rep = tid / FS::TPR, j8 = tid % FS::TPR;
         const int col = r0 + rep;
-        f32x4 xv[4], pv[4];
+        f32x4 xv[RT], pv[RT];
         if (col < a.R) {
 #pragma unroll
-            for (int v = 0; v < 4; v++) {
-                const int ib = tl.i0 + 32 * v + 4 * j8;
+            for (int v = 0; v < RT; v++) {
+                const int ib = tl.i0 + 4 * FS::TPR * v + 4 * j8;
                 if (ib >= I.N) continue;
                 const int64_t base = (int64_t)col * I.ld + ib;
                 xv[v] = *gld<f32x4>(phi_in + base);
@@ -275,8 +286,8 @@ __device__ __forceinline__ void batch_lds_tile(const BatchArgs &a, int64_t q, co
         const auto *hg = gld<float>(I.h);
         if (col < a.R) {
 #pragma unroll
-            for (int v = 0; v < 4; v++) {
-                const int loc = 32 * v + 4 * j8;
+            for (int v = 0; v < RT; v++) {
+                const int loc = 4 * FS::TPR * v + 4 * j8;
                 const int ib = tl.i0 + loc;
                 if (ib >= I.N) continue;
                 const f32x4 u = *(const f32x4 *)&U[rep * UL + loc];
@@ -472,14 +483,25 @@ __device__ __forceinline__ void batch_f32_tile(const BatchArgs &a, int64_t q, co
 // One launch per MD step for every BF16 and FP8 instance of the batch: the storage
 // type is uniform per tile.  A tile with instance index -1 is a placeholder of the
 // XCD placement and does nothing.
-__global__ __launch_bounds__(512, 4) void k_step_batch_lds(BatchArgs a, int64_t q) {
-    __shared__ __align__(16) bf16 Bs[2][BL_REPS][BL_LDB];
+template <int RT>
+__device__ __forceinline__ void batch_lds_body(const BatchArgs &a, int64_t q) {
+    __shared__ __align__(16) bf16 Bs[2][16 * RT][BL_LDB];
     const BatchTile tl = a.tiles[blockIdx.x];
     if (tl.inst < 0) return;
     const BatchInst I = a.inst[tl.inst];
-    if (I.jt == JT_FP8) batch_lds_tile<JT_FP8>(a, q, tl, I, Bs);
-    else if (I.jt == JT_BIT) batch_lds_tile<JT_BIT>(a, q, tl, I, Bs);
-    else batch_lds_tile<JT_BF16>(a, q, tl, I, Bs);
+    if (I.jt == JT_FP8) batch_lds_tile<JT_FP8, RT>(a, q, tl, I, Bs);
+    else if (I.jt == JT_BIT) batch_lds_tile<JT_BIT, RT>(a, q, tl, I, Bs);
+    else batch_lds_tile<JT_BF16, RT>(a, q, tl, I, Bs);
+}
+
+__global__ __launch_bounds__(512, 4) void k_step_batch_lds(BatchArgs a, int64_t q) {
+    batch_lds_body<BL_REPS / 16>(a, q);
+}
+
+// Tiles of 32 or 16 replicas: small batches and few replicas.
+template <int RT>
+__global__ __launch_bounds__(512, 4) void k_step_batch_narrow(BatchArgs a, int64_t q) {
+    batch_lds_body<RT>(a, q);
 }
 
 // The same for the FP32 instances of the batch (their own tile table and launch).
@@ -506,6 +528,7 @@ struct BatchPlan {
     BatchInst *dinst = nullptr;
     BatchTile *dtiles[3] = {nullptr, nullptr, nullptr};
     int ntiles[3] = {0, 0, 0};
+    int rt = 4;                         // replica tiles of 16 per BF16 / FP8 workgroup
     std::vector<BatchGraph> graphs;     // most recently used last
     hipStream_t cap = nullptr;          // capture-only stream (no work runs on it)
 };
@@ -581,43 +604,84 @@ static hipError_t build_plan(hqa_md *md, BatchPlan *&out) {
         std::vector<BatchTile> xl[NX];
         int64_t load[NX] = {0};
         int64_t total = 0;
+        // Shape and placement by the number of 64-replica tiles, all of which are resident
+        // at once up to 512 (two per CU).  Few tiles leave a step waiting on its longest one,
+        // whose groups run at the latency of one or two workgroups per CU, so
+        //  * replicas narrower than a tile take a narrower tile, up to 320 tiles are halved
+        //    (32 replicas) and up to 96 quartered: more workgroups, each with less to stage and
+        //    multiply per group (us per step, R = 64, 64 / 32 / 16 replicas a tile: 88 tiles
+        //    30.5 / 18.8 / 16.3; 191 tiles 38.8 / 28.6 / 30.5; 374 tiles 40.2 / 43.8; R = 16, 8
+        //    instances, 64 / 16: 20.5 / 14.5); past that, R = 65 .. 96 takes three 32s rather
+        //    than two 64s (374 x 2 tiles, R = 96: 66.2 / 61.8);
+        //  * up to 1024 tiles go to the XCDs one by one instead of an instance at a time: even
+        //    loads matter more than one L2 per flux operand (374 tiles 55.4 -> 44.0, 640 tiles
+        //    59.3 -> 49.8; 1700 tiles 157 / 158).
+        int64_t count = 0;
+        for (int k : dense)
+            if (member(md->inst[k]))
+                count += (int64_t)((md->inst[k].N + BL_ROWS - 1) / BL_ROWS) * ((md->R + 63) / 64);
+        int reps = 64;
+        if (fam == 1) {
+            bp->rt = md->R <= 16 ? 1 : md->R <= 32 ? 2 : 4;
+            if (bp->rt == 4 && (count <= 320 || (md->R > 64 && md->R <= 96))) bp->rt = 2;
+            if (bp->rt == 2 && count <= 96) bp->rt = 1;
+            reps = 16 * bp->rt;
+        }
+        const bool spread = count <= 1024;
         // work of a tile: the bytes it streams (its couplings and the staged flux
         // block) plus a fixed cost of its first loads and epilogue (about the time of
         // 256 KB)
         auto tile_work = [&](const Instance &I) -> int64_t {
             const int64_t jb = I.jt == JT_F32 ? 512 : I.jt == JT_BF16 ? 256 : I.jbits > 0 ? 16 : 128;
-            return (jb + 128) * (int64_t)I.Np + 262144;
+            return (jb + 2 * reps) * (int64_t)I.Np + 262144;
         };
         for (int k : dense) {
             const Instance &I = md->inst[k];
             if (!member(I)) continue;
-            total += (int64_t)((I.N + BL_ROWS - 1) / BL_ROWS) * ((md->R + 63) / 64) * tile_work(I);
+            total += (int64_t)((I.N + BL_ROWS - 1) / BL_ROWS) * ((md->R + reps - 1) / reps) * tile_work(I);
         }
         for (int k : dense) {
             const Instance &I = md->inst[k];
             if (!member(I)) continue;
             const int nrb = (I.N + BL_ROWS - 1) / BL_ROWS;
             const int64_t tw = tile_work(I);
-            const int64_t work = (int64_t)nrb * ((md->R + 63) / 64) * tw;
+            const int64_t work = (int64_t)nrb * ((md->R + reps - 1) / reps) * tw;
             if (nrb >= NX && NX * work >= total) {
                 for (int x = 0; x < NX; x++) {
                     for (int rb = x * nrb / NX; rb < (x + 1) * nrb / NX; rb++)
-                        for (int r0 = 0; r0 < md->R; r0 += 64) {
+                        for (int r0 = 0; r0 < md->R; r0 += reps) {
                             xl[x].push_back({k, rb * BL_ROWS, r0, 0});
                             load[x] += tw;
                         }
                 }
                 continue;
             }
+            if (spread) {
+                for (int i0 = 0; i0 < I.N; i0 += BL_ROWS)
+                    for (int r0 = 0; r0 < md->R; r0 += reps) {
+                        int x = 0;
+                        for (int y = 1; y < NX; y++)
+                            if (load[y] < load[x]) x = y;
+                        xl[x].push_back({k, i0, r0, 0});
+                        load[x] += tw;
+                    }
+                continue;
+            }
             int x = 0;
             for (int y = 1; y < NX; y++)
                 if (load[y] < load[x]) x = y;
             for (int i0 = 0; i0 < I.N; i0 += BL_ROWS)
-                for (int r0 = 0; r0 < md->R; r0 += 64) {
+                for (int r0 = 0; r0 < md->R; r0 += reps) {
                     xl[x].push_back({k, i0, r0, 0});
                     load[x] += tw;
                 }
         }
+        // an XCD's first 32 tiles get a CU each, the others join them from the first CU on:
+        // longest tiles last among the first, so that they are not joined by long ones
+        // (374 tiles: 44.0 -> 40.3)
+        if (spread)
+            for (int x = 0; x < NX; x++)
+                if (xl[x].size() > 32) std::reverse(xl[x].begin(), xl[x].begin() + 32);
         size_t longest = 0;
         for (int x = 0; x < NX; x++) longest = std::max(longest, xl[x].size());
         std::vector<BatchTile> &dst = ht[fam == 0 ? JT_F32 : JT_BF16];
@@ -659,7 +723,9 @@ static void enqueue_steps(hqa_md *md, const BatchPlan *bp, int64_t q0, int64_t q
             a.tiles = bp->dtiles[t];
             a.ntiles = bp->ntiles[t];
             if (t == JT_F32) k_step_batch_f32<<<a.ntiles, 512, 0, st>>>(a, q);
-            else k_step_batch_lds<<<a.ntiles, 512, 0, st>>>(a, q);   // BF16 and FP8
+            else if (bp->rt == 4) k_step_batch_lds<<<a.ntiles, 512, 0, st>>>(a, q);   // BF16 and FP8
+            else if (bp->rt == 2) k_step_batch_narrow<2><<<a.ntiles, 512, 0, st>>>(a, q);
+            else k_step_batch_narrow<1><<<a.ntiles, 512, 0, st>>>(a, q);
         }
         cur ^= 1;
     }
