@@ -62,11 +62,20 @@ void fault_alloc_arm() {
     g_alloc_count = 0;
 }
 
-hipError_t dev_malloc(void **p, size_t bytes) {
+hipError_t dev_malloc(void **p, size_t bytes, size_t roomy, size_t *got) {
     *p = nullptr;
     const int64_t k = ++g_alloc_count;
     const int64_t f = g_alloc_fail.load();
     if (f > 0 && k == f) return hipErrorOutOfMemory;
+    if (got) *got = bytes;
+    if (roomy > bytes) {
+        if (hipMalloc(p, roomy) == hipSuccess) {
+            if (got) *got = roomy;
+            return hipSuccess;
+        }
+        *p = nullptr;
+        (void)hipGetLastError();
+    }
     return hipMalloc(p, bytes);
 }
 }  // namespace hqa
@@ -117,7 +126,8 @@ static void dfree(void *p) {
 }
 
 static void free_instance(Instance &I) {
-    dfree(I.J64); dfree(I.rp); dfree(I.ci); dfree(I.h64); dfree(I.h32); dfree(I.Js); dfree(I.v32);
+    if (!I.j_borrowed) dfree(I.J64);
+    dfree(I.rp); dfree(I.ci); dfree(I.h64); dfree(I.h32); dfree(I.Js); dfree(I.v32);
     for (int k = 0; k < 2; k++) { dfree(I.phi64[k]); dfree(I.phi32[k]); dfree(I.phib[k]); dfree(I.xt[k]); }
     dfree(I.p64); dfree(I.S64); dfree(I.p32); dfree(I.S32); dfree(I.xch); dfree(I.Jt);
     dfree(I.Jbits);
@@ -155,18 +165,37 @@ static hqa_status check_problem(const hqa_problem &P, int k) {
     return HQA_OK;
 }
 
+// Whether kernels may read this device array where it lies: memory of the current device, its
+// values aligned.
+static bool readable_in_place(const double *p) {
+    hipPointerAttribute_t a;
+    int dev = 0;
+    if ((uintptr_t)p % sizeof(double)) return false;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == dev;
+}
+
 // Upload binary64 couplings and field, validate on the device, gather exponent
-// statistics.  Leaves I.J64 / rp / ci / h64 filled.
+// statistics.  Leaves I.J64 / rp / ci / h64 filled.  With in_place, dense couplings that a
+// kernel can read where they lie are not copied (the caller is done with I before it returns).
 static hqa_status ingest(const hqa_problem &P, int k, hipStream_t st, int32_t *derr,
-                         int32_t *dstats, Instance &I) {
+                         int32_t *dstats, Instance &I, bool in_place = false) {
     I.N = P.n;
     I.layout = P.layout;
     I.has_h = P.h != nullptr;
     const int N = P.n;
     if (P.layout == HQA_DENSE) {
         I.nnz = (int64_t)N * N;
-        HIPCHK(dalloc(&I.J64, (size_t)N * N));
-        HIPCHK(hipMemcpyAsync(I.J64, P.j, sizeof(double) * N * N, kind_in(P.mem), st));
+        if (in_place && P.mem == HQA_DEVICE && readable_in_place(P.j)) {
+            I.J64 = const_cast<double *>(P.j);
+            I.j_borrowed = true;
+        } else {
+            HIPCHK(dalloc(&I.J64, (size_t)N * N));
+            HIPCHK(hipMemcpyAsync(I.J64, P.j, sizeof(double) * N * N, kind_in(P.mem), st));
+        }
     } else {
         // the row pointer is needed on the host to size the arrays
         std::vector<int32_t> rp(N + 1);
@@ -215,20 +244,79 @@ static hqa_status ingest(const hqa_problem &P, int k, hipStream_t st, int32_t *d
 
 static bool exact_ok(const Instance &I) { return I.es.lsb != INT32_MIN; }
 
-// Scoped device buffers for the read-out.
+// Device scratch that a handle keeps between calls (an allocation and its release cost 20 to
+// 50 us each and drain the device, a small read-out made a dozen): at most KEEP bytes, freed
+// with the handle.  A call that finds it taken, by another thread or an enclosing call,
+// allocates for itself.
+struct KeptScratch {
+    static constexpr size_t CHUNK = (size_t)4 << 20, KEEP = (size_t)64 << 20;
+    struct Chunk {
+        uint8_t *p;
+        size_t cap, used;
+    };
+    std::vector<Chunk> chunks;
+    std::atomic_flag busy = ATOMIC_FLAG_INIT;
+    // everything is free again; what exceeds KEEP goes back to the device
+    void release(size_t keep = KEEP) {
+        size_t sum = 0, n = 0;
+        for (Chunk &c : chunks) {
+            c.used = 0;
+            if (sum + c.cap <= keep) {
+                sum += c.cap;
+                chunks[n++] = c;
+            } else {
+                dfree(c.p);
+            }
+        }
+        chunks.resize(n);
+    }
+};
+
+static void free_kept(void *&k) {
+    if (!k) return;
+    ((KeptScratch *)k)->release(0);
+    delete (KeptScratch *)k;
+    k = nullptr;
+}
+
+// Scoped device buffers, from a handle's kept scratch if one is given.  Kept memory is used on
+// the handle's stream only, so a call that left early is ordered before the next one.
 struct DevBufs {
     std::vector<void *> v;
+    KeptScratch *kept = nullptr;
+    explicit DevBufs(void *k = nullptr) {
+        if (k && !((KeptScratch *)k)->busy.test_and_set()) kept = (KeptScratch *)k;
+    }
+    DevBufs(const DevBufs &) = delete;
     template <typename T>
     hipError_t get(T **p, size_t n) {
+        if (kept) {
+            const size_t b = (std::max<size_t>(n, 1) * sizeof(T) + 255) & ~(size_t)255;
+            for (KeptScratch::Chunk &c : kept->chunks)
+                if (c.cap - c.used >= b) {
+                    *p = (T *)(c.p + c.used);
+                    c.used += b;
+                    return hipSuccess;
+                }
+            KeptScratch::Chunk c = {nullptr, 0, b};
+            const hipError_t e = dev_malloc((void **)&c.p, b, KeptScratch::CHUNK, &c.cap);
+            if (e != hipSuccess) return e;
+            kept->chunks.push_back(c);
+            *p = (T *)c.p;
+            return hipSuccess;
+        }
         hipError_t e = dalloc(p, n);
         if (e == hipSuccess) v.push_back(*p);
         return e;
     }
     ~DevBufs() {
         for (void *p : v) dfree(p);
+        if (kept) {
+            kept->release();
+            kept->busy.clear();
+        }
     }
 };
-
 
 // Per-block maxima of |a - b| and |b| over n values (finished on the host).
 __global__ void k_maxdiff(const double *a, const double *b, int64_t n, double *out) {
@@ -304,6 +392,7 @@ void hqa_md_destroy(hqa_md *md) {
     dfree(md->err); dfree(md->scratch_i); dfree(md->bar);
     free_batch_plan(md->batch);
     free_pass(md->pass);
+    free_kept(md->keep);
     delete md;
 }
 
@@ -344,6 +433,7 @@ hqa_status hqa_md_init(const hqa_problem *probs, int32_t count, const hqa_schedu
     }
     hipStream_t st = (hipStream_t)hip_stream;
     hqa_md *md = new hqa_md();
+    md->keep = new KeptScratch();
     md->stream = st;
     md->R = opts->replicas;
     md->prec = opts->precision;
@@ -1111,7 +1201,8 @@ hqa_status hqa_md_state(hqa_md *md, int32_t instance, int32_t what, void *dst, i
     }
     const size_t n = (size_t)I.N * md->R;
     double *buf = (double *)dst;
-    if (dst_mem == HQA_HOST) HIPCHK(dalloc(&buf, n));
+    DevBufs B(md->keep);
+    if (dst_mem == HQA_HOST) HIPCHK(B.get(&buf, n));
     if (import && dst_mem == HQA_HOST)
         HIPCHK(hipMemcpyAsync(buf, dst, n * 8, hipMemcpyHostToDevice, md->stream));
     if (what == HQA_STATE_STATMEAN) {
@@ -1126,7 +1217,6 @@ hqa_status hqa_md_state(hqa_md *md, int32_t instance, int32_t what, void *dst, i
     if (!import && dst_mem == HQA_HOST)
         HIPCHK(hipMemcpyAsync(dst, buf, n * 8, hipMemcpyDeviceToHost, md->stream));
     HIPCHK(hipStreamSynchronize(md->stream));
-    if (dst_mem == HQA_HOST) dfree(buf);
     return HQA_OK;
 }
 
@@ -1205,7 +1295,7 @@ hqa_status hqa_md_hamiltonian(hqa_md *md, int32_t instance, double *H, int32_t d
     if ((size_t)I.N * 8 + 8192 > (size_t)md->max_lds)
         return fail(HQA_EUNSUPPORTED, "binary64 Hamiltonian: N = %d exceeds the LDS capacity", I.N);
     double *buf = H;
-    DevBufs B;
+    DevBufs B(md->keep);
     uint8_t *scr;
     HIPCHK(B.get(&scr, hamiltonian_scratch_bytes(I, md->R)));
     if (dst_mem == HQA_HOST) HIPCHK(B.get(&buf, (size_t)md->R));
@@ -1338,7 +1428,7 @@ static hqa_status classify_impl(hqa_md *md, int32_t instance, int32_t n_amb, int
                                 int32_t prob_mem, int64_t tabu_iters = 0, int32_t tenure = 0) {
     hqa_status s = classify_checks(md, instance, n_amb, solve, out, prob);
     if (s != HQA_OK) return s;
-    DevBufs B;
+    DevBufs B(md->keep);
     CallTimer tm(md->stream);
     s = classify_core(md, instance, n_amb, solve, out, out_mem, prob, prob_mem, tabu_iters,
                       tenure, B);
@@ -1580,13 +1670,13 @@ hqa_status hqa_md_features(hqa_md *md, int32_t instance, float *feat, int32_t ds
     if (K < 1) return fail(HQA_ESTATE, "no step of the statistics window has run");
     const size_t n = (size_t)md->R * I.N * 12;
     float *buf = feat;
-    if (dst_mem == HQA_HOST) HIPCHK(dalloc(&buf, n));
+    DevBufs B(md->keep);
+    if (dst_mem == HQA_HOST) HIPCHK(B.get(&buf, n));
     HIPCHK(launch_features(I, md->R, K, (float)((double)md->q / (double)md->sch.T), I.mean_n1,
                            buf, md->stream));
     if (dst_mem == HQA_HOST)
         HIPCHK(hipMemcpyAsync(feat, buf, n * 4, hipMemcpyDeviceToHost, md->stream));
     HIPCHK(hipStreamSynchronize(md->stream));
-    if (dst_mem == HQA_HOST) dfree(buf);
     return HQA_OK;
 }
 
@@ -1596,6 +1686,7 @@ struct hqa_es {
     float *P = nullptr, *m = nullptr, *v = nullptr, *g = nullptr, *acc = nullptr;
     float *part = nullptr;            // the gradient kernel's partial sums
     size_t part_bytes = 0;
+    void *keep = nullptr;             // copies of host arguments, kept between calls
     int64_t t = 0;
 };
 
@@ -1603,6 +1694,7 @@ void hqa_es_destroy(hqa_es *es) {
     if (!es) return;
     (void)hipStreamSynchronize(es->stream);
     dfree(es->P); dfree(es->m); dfree(es->v); dfree(es->g); dfree(es->acc); dfree(es->part);
+    free_kept(es->keep);
     delete es;
 }
 
@@ -1612,6 +1704,7 @@ hqa_status hqa_es_create(uint64_t seed, void *hip_stream, hqa_es **out) {
     *out = nullptr;
     hqa_es *es = new hqa_es();
     es->stream = (hipStream_t)hip_stream;
+    es->keep = new KeptScratch();
     hipError_t e = dalloc(&es->P, HQA_ES_NPARAM);
     if (e == hipSuccess) e = dalloc(&es->m, HQA_ES_NPARAM);
     if (e == hipSuccess) e = dalloc(&es->v, HQA_ES_NPARAM);
@@ -1685,7 +1778,7 @@ static hqa_status es_part(hqa_es *es, int64_t n) {
 hqa_status hqa_es_grad(hqa_es *es, const float *x, const int32_t *y, int64_t n, const float *cw,
                        float *grad, float *loss, int32_t mem) {
     if (!es || !x || !y || !cw || n < 1) return fail(HQA_EINVAL, "bad arguments");
-    DevBufs B;
+    DevBufs B(es->keep);
     const float *dx, *dcw;
     const int32_t *dy;
     hqa_status s = es_inputs(es, B, x, y, cw, n, mem, &dx, &dy, &dcw);
@@ -1702,7 +1795,7 @@ hqa_status hqa_es_grad(hqa_es *es, const float *x, const int32_t *y, int64_t n, 
 hqa_status hqa_es_train_step(hqa_es *es, const float *x, const int32_t *y, int64_t n,
                              const float *cw, float lr, float *loss, int32_t mem) {
     if (!es || !x || !y || !cw || n < 1 || !(lr > 0.f)) return fail(HQA_EINVAL, "bad arguments");
-    DevBufs B;
+    DevBufs B(es->keep);
     const float *dx, *dcw;
     const int32_t *dy;
     hqa_status s = es_inputs(es, B, x, y, cw, n, mem, &dx, &dy, &dcw);
@@ -1719,7 +1812,7 @@ hqa_status hqa_es_train_step(hqa_es *es, const float *x, const int32_t *y, int64
 hqa_status hqa_es_predict(hqa_es *es, const float *x, int64_t n, float *prob, int32_t bf16_infer,
                           int32_t mem) {
     if (!es || !x || !prob || n < 0) return fail(HQA_EINVAL, "bad arguments");
-    DevBufs B;
+    DevBufs B(es->keep);
     const float *dx, *dcw;
     const int32_t *dy;
     hqa_status s = es_inputs(es, B, x, nullptr, nullptr, n, mem, &dx, &dy, &dcw);
@@ -1737,7 +1830,7 @@ hqa_status hqa_es_confidence(hqa_es *es, const float *prob, int64_t n, int32_t m
                              double *mean_max) {
     if (!es || !prob || !mean_max || n < 1) return fail(HQA_EINVAL, "bad arguments");
     if (mem != HQA_HOST && mem != HQA_DEVICE) return fail(HQA_EINVAL, "bad mem");
-    DevBufs B;
+    DevBufs B(es->keep);
     const float *dp = prob;
     if (mem == HQA_HOST) {
         float *t;
@@ -1773,7 +1866,7 @@ hqa_status hqa_md_run_es(hqa_md *md, int32_t instance, hqa_es *es, int64_t K, in
     if (md->q >= md->sch.T) return fail(HQA_ESTATE, "the run has already reached step T");
     const Instance &I = md->inst[instance];
     const int64_t n = (int64_t)md->R * I.N;
-    DevBufs B;
+    DevBufs B(md->keep);
     float *feat, *pd;
     HIPCHK(B.get(&feat, (size_t)n * HQA_ES_NFEAT));
     HIPCHK(B.get(&pd, (size_t)n * 3));
@@ -1813,7 +1906,7 @@ hqa_status hqa_ising_energy(const hqa_problem *prob, const int8_t *spins, int32_
     HIPCHK(B.get(&derr, 1));
     HIPCHK(B.get(&dstats, 4));
     Instance I;
-    s = ingest(*prob, 0, st, derr, dstats, I);
+    s = ingest(*prob, 0, st, derr, dstats, I, true);
     if (s == HQA_OK && !exact_ok(I))
         s = fail(HQA_EUNSUPPORTED, "coupling exponents span too many binades for exact sums");
     if (s != HQA_OK) { free_instance(I); return s; }

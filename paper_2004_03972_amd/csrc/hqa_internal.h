@@ -54,6 +54,7 @@ struct Instance {
     // binary64 copies of the input (every precision keeps them: reduce, energy,
     // drift check and the reference mode read them)
     double *J64 = nullptr;    // dense N*N or CSR values
+    bool j_borrowed = false;  // J64 is the caller's array
     int32_t *rp = nullptr, *ci = nullptr;
     double *h64 = nullptr;    // N (zeros when no field)
     float *h32 = nullptr;     // N (or Np)
@@ -126,6 +127,7 @@ struct hqa_md {
     int32_t flags = 0;                       // HQA_MD_* run flags
     void *pass = nullptr;                    // read-out scratch, side streams and captured
                                              // graphs of hqa_md_pass
+    void *keep = nullptr;                    // read-out scratch kept between calls
     int64_t stats_k0 = 0, stats_k1 = 0;      // early-stop statistics window [k0, k1)
     int64_t stats_every = 1;                 // ... sampling steps k0, k0 + every, ...
 };
@@ -181,7 +183,8 @@ hipError_t launch_merge(int N, int R, int n, const int32_t *amb, const int64_t *
 // Every device allocation of the library goes through dev_malloc.  With HQA_FAULT_ALLOC=k
 // in the environment, the k-th allocation counted from the start of the latest
 // hqa_md_init (from 1) fails as out of memory (tests of the error paths).
-hipError_t dev_malloc(void **p, size_t bytes);
+// *got takes the bytes allocated: `roomy` of them where that many are free, else `bytes`.
+hipError_t dev_malloc(void **p, size_t bytes, size_t roomy = 0, size_t *got = nullptr);
 void fault_alloc_arm();
 
 // Exact energies and cuts of V spin vectors; `part` holds energy_part_bytes(N, V)
