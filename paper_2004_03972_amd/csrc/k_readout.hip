@@ -4,7 +4,9 @@
 #include <math.h>
 
 #include "exact_acc.h"
+#include <algorithm>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "hqa_internal.h"
@@ -771,27 +773,14 @@ hipError_t launch_merge(int N, int R, int n, const int32_t *amb, const int64_t *
 // ---------------------------------------------------------------------------
 // Exact Ising energy (Eq. 1) and cut (Methods, MAX-CUT with w = J).
 //
-// Dense instances (k_energy_mv): over the upper triangle, with s_i s_j = 1 - 2 [s_i != s_j]
-// and s_i = 1 - 2 [s_i = -1],
-//   C = sum_{i<j, s_i != s_j} J_ij,   S = sum_{i<j} J_ij,
-//   H = sum_i h_i s_i = Ht - 2 Hn,    Ht = sum_i h_i,   Hn = sum_{i: s_i = -1} h_i,
-//   E = sum_{i<j} J_ij s_i s_j + H = S - 2 C + Ht - 2 Hn.
-// The spins of 64 vectors are packed into one 64-bit word per spin (bit v: vector v has
-// s = -1), so one pass over the upper triangle serves every vector of a group: for the
-// pair (i, j) the word m_i ^ m_j marks the vectors the pair cuts.
+// Dense instances (k_energy_mv): with U = sum_{i<j} J_ij s_i s_j, S = sum_{i<j} J_ij and
+// H = sum_i h_i s_i,  E = U + H  and  C = sum_{i<j, s_i != s_j} J_ij = (S - U) / 2.
+// Every J is an integer m 2^b0 with |m| < 2^span; in D balanced base-256 digits d_k in
+// [-128, 127] (span <= 8 D - 2), U's digit sums are products of int8 matrices: exact 32-bit
+// integers y_k = d_k s per row (at most 256 N) and exact 64-bit ones Q_k = s y_k.  The
+// merge adds the digit totals into the fixed-point accumulator and rounds once.
 //
-// Exactness by level sums: every J and h is a multiple of 2^b0 below 2^(msb + 1).  With
-// lg = ceil(log2(N^2 + N)) and w = 51 - lg, the levels sigma_k = b0 + k w (k < L) cover
-// the bits [b0, msb] when L w >= msb + 1 - b0.  A term is cut into parts t_k, multiples of
-// 2^sigma_k below 2^(sigma_(k+1)) (top level: 2^(sigma_L + 1)), by rounding to a multiple
-// of 2^sigma_k from the top level down ((r + K_k) - K_k with K_k = 1.5 2^(sigma_k + 52),
-// exact for |r| <= 2^(sigma_k + 51)) and keeping the exact remainder; the lowest part is
-// the last remainder.  Any sum of at most 2^lg parts of one level is then a multiple of
-// 2^sigma_k below 2^(sigma_k + 53): binary64 adds them exactly, in any order and any
-// grouping (lanes, wavefronts, workgroups, slices).  The merge adds the level totals
-// into the fixed-point accumulator and rounds once.  L = 1 is a plain binary64 sum.
-//
-// CSR instances, and dense ones whose bits need more than four levels (k_energy), keep
+// CSR instances, and dense ones beyond D = 20 or near binary64's range (k_energy), keep
 // one workgroup per (vector, slice): the sum over ordered pairs i != j counts each pair
 // twice, so 2E = sum_{i!=j} J s s + 2 sum h s and 2C = sum_{i!=j, s_i != s_j} J are
 // accumulated exactly (binary64 when the fast condition holds, else the fixed-point
@@ -946,275 +935,423 @@ __global__ __launch_bounds__(64) void k_energy_merge(EnArgs a) {
     if (a.cut) a.cut[v] = acc_round(ac, a.b0 - 1);
 }
 
-// ----- dense: many vectors per pass, level sums -----
+// ----- dense: many vectors per pass, digit sums -----
 struct EnMvArgs {
     int N, V, P, b0;
     int jt;            // type of Js (JT_F32, JT_BF16, JT_FP8), -1 to read J
     int ldj;           // row pitch of Js
     const void *Js;    // the exact storage copy of J (or NULL)
     const double *J;
-    const double *h;   // NULL: no field
+    const double *h;
     const int8_t *spins;
-    uint64_t *masks;   // [ceil(V / 64)][N]
-    double *part;      // see energy_mv_layout
-    double K[4];       // rounding constants of levels 1 .. L - 1
+    int64_t *part;     // [P][V][D] Q = 2 U, then [P][D] S2 = 2 S
+    double scale;      // 2^-b0
     double *E, *cut;
 };
 
-// Offsets (in doubles) of the partial sums of a launch with P slices, V vectors, L
-// levels: C and Hn per (slice, vector, level), then S and Ht per (slice, level).
-struct EnMvLayout {
-    int64_t c, hn, s, ht, total;
-};
-static __host__ __device__ EnMvLayout energy_mv_layout(int P, int V, int L) {
-    EnMvLayout o;
-    o.c = 0;
-    o.hn = (int64_t)P * V * L;
-    o.s = 2 * o.hn;
-    o.ht = o.s + (int64_t)P * L;
-    o.total = o.ht + (int64_t)P * L;
-    return o;
-}
+typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4_r;
 
-// Packed spins: word b of spin j has bit v set when vector 64 b + v has s_j = -1.  A
-// thread per (word, spin): its 64 loads (rows clamped to the last vector, bits past it
-// cleared) are independent, so they are all in flight at once, and consecutive threads
-// read consecutive bytes of a row.
-struct PackArgs {
-    int N, V;
-    const int8_t *spins;
-    uint64_t *masks;
-};
-
-__device__ __forceinline__ void pack_masks_body(int N, int V, const int8_t *spins,
-                                                uint64_t *masks, const int bx_) {
-    const int64_t t = (int64_t)bx_ * blockDim.x + threadIdx.x;
-    const int nw = (V + 63) / 64;
-    if (t >= (int64_t)nw * N) return;
-    const int b = (int)(t / N), j = (int)(t % N);
-    int8_t x[64];
+// Balanced digits of 16 couplings, by digit: A[k] holds the digits k (one MFMA operand of a
+// lane).  m = x 2^-b0 is split into 32-bit words from the top: adding 2^52 rounds to an integer
+// and leaves it in the low word, fma takes it off exactly.  With 0x80808080 added as well the
+// word's bytes are d_k + 128, and bit 32 is the carry into the next word.
+template <int D>
+__device__ __forceinline__ void mv_digits(const double (&x)[16], double scale, i32x4_r (&A)[D]) {
+    constexpr int NWD = (D + 3) / 4;
+    constexpr double LOW = 0x1p52 + 2155905152.0, TOP = 0x1.8p52 + 2155905152.0;
 #pragma unroll
-    for (int v = 0; v < 64; v++) x[v] = spins[(int64_t)min(64 * b + v, V - 1) * N + j];
-    uint64_t m = 0;
+    for (int q = 0; q < 4; q++) {
+        uint32_t wd[4][NWD];
 #pragma unroll
-    for (int v = 0; v < 64; v++) m |= (uint64_t)(x[v] < 0) << v;
-    const int have = V - 64 * b;                     // vectors in this word
-    if (have < 64) m &= (1ull << have) - 1ull;
-    masks[t] = m;
-}
-
-__global__ __launch_bounds__(256) void k_pack_masks(int N, int V, const int8_t *spins,
-                                                    uint64_t *masks) {
-    pack_masks_body(N, V, spins, masks, blockIdx.x);
-}
-
-__global__ __launch_bounds__(256) void k_pack_masks_many(const PackArgs *as, const int *nb) {
-    const int k = blockIdx.y;
-    if ((int)blockIdx.x >= nb[k]) return;
-    const PackArgs a = as[k];
-    pack_masks_body(a.N, a.V, a.spins, a.masks, blockIdx.x);
-}
-
-__device__ __forceinline__ double mv_coupling(const EnMvArgs &a, int i, int j) {
-    if (a.jt < 0) return a.J[(int64_t)i * a.N + j];
-    const int64_t t = (int64_t)i * a.ldj + j;
-    if (a.jt == JT_FP8) {
-        // OCP e4m3: sign, 4 exponent bits (bias 7), 3 mantissa bits; exponent 0 is
-        // subnormal (m 2^-9).  The couplings are finite, so 0x7f / 0xff do not occur.
-        const uint32_t b = ((const uint8_t *)a.Js)[t];
-        const uint32_t e = (b >> 3) & 15u, m = b & 7u;
-        const double mag = e ? (double)(8u + m) * (double)__uint_as_float((e + 117u) << 23)
-                             : (double)m * 0x1p-9;
-        return (b & 0x80u) ? -mag : mag;
-    }
-    if (a.jt == JT_BF16) {
-        const uint32_t b = ((const uint16_t *)a.Js)[t];
-        return (double)__uint_as_float(b << 16);
-    }
-    return (double)((const float *)a.Js)[t];
-}
-
-// The parts of a term on levels 0 .. L - 1 (see above).
-template <int L>
-__device__ __forceinline__ void mv_split(const EnMvArgs &a, double r, double (&t)[L]) {
+        for (int e = 0; e < 4; e++) {
+            const double v = x[4 * q + e];
+            if constexpr (NWD == 1) {
+                wd[e][0] = (uint32_t)__double_as_longlong(__builtin_fma(v, scale, TOP)) ^ 0x80808080u;
+            } else {
+                double rem = v * scale, p32 = 1.0;
 #pragma unroll
-    for (int k = L - 1; k >= 1; k--) {
-        const double hi = (r + a.K[k]) - a.K[k];
-        r -= hi;
-        t[k] = hi;
+                for (int w = 1; w < NWD; w++) p32 *= 0x1p32;
+                uint32_t hi[NWD];
+#pragma unroll
+                for (int w = NWD - 1; w >= 0; w--, p32 *= 0x1p-32) {
+                    const double m = w == NWD - 1 ? TOP : LOW;
+                    const double t = __builtin_fma(rem, 1.0 / p32, m);
+                    if (w) rem = __builtin_fma(t - m, -p32, rem);
+                    const uint64_t b = (uint64_t)__double_as_longlong(t);
+                    wd[e][w] = (uint32_t)b;
+                    hi[w] = (uint32_t)(b >> 32) & 1u;
+                }
+                uint32_t carry = hi[0];
+#pragma unroll
+                for (int w = 1; w < NWD; w++) {
+                    const uint32_t t = wd[e][w] + carry;
+                    if (w + 1 < NWD) carry = hi[w] | (uint32_t)(t < carry);
+                    wd[e][w] = t;
+                }
+#pragma unroll
+                for (int w = 0; w < NWD; w++) wd[e][w] ^= 0x80808080u;
+            }
+        }
+#pragma unroll
+        for (int w = 0; w < NWD; w++) {                  // 4 x 4 byte transposes
+            const uint32_t a01 = __builtin_amdgcn_perm(wd[1][w], wd[0][w], 0x05010400u);
+            const uint32_t a23 = __builtin_amdgcn_perm(wd[3][w], wd[2][w], 0x05010400u);
+            if (4 * w < D) A[4 * w][q] = (int)__builtin_amdgcn_perm(a23, a01, 0x05040100u);
+            if (4 * w + 1 < D) A[4 * w + 1][q] = (int)__builtin_amdgcn_perm(a23, a01, 0x07060302u);
+            const uint32_t b01 = __builtin_amdgcn_perm(wd[1][w], wd[0][w], 0x07030602u);
+            const uint32_t b23 = __builtin_amdgcn_perm(wd[3][w], wd[2][w], 0x07030602u);
+            if (4 * w + 2 < D) A[4 * w + 2][q] = (int)__builtin_amdgcn_perm(b23, b01, 0x05040100u);
+            if (4 * w + 3 < D) A[4 * w + 3][q] = (int)__builtin_amdgcn_perm(b23, b01, 0x07060302u);
+        }
     }
-    t[0] = r;
 }
 
-// Workgroup (p, g): vectors g G .. g G + G - 1 (G divides 64, so one mask word), rows
-// 4 p + w, 4 p + w + 4 P, ... (wavefront w), lanes along the columns j > i.  Lane x holds
-// the column sums of C for every vector of the group and, for vector g G + x, the sum
-// Hn; group 0 also sums S and Ht.
-template <int G, int L>
+// Couplings of a row in a block of 64 columns from 64 c, zeros past the last column.  A storage
+// copy gives lane group kg the columns 16 kg .. + 15; binary64 couplings go out in pieces of
+// two, columns 8 j + 2 kg, + 1 (j = 0 .. 7), so that a load of the four groups is 64
+// consecutive bytes instead of pieces 128 bytes apart.
+__device__ __forceinline__ void mv_load(const EnMvArgs &a, int row, int c, int kg, double (&x)[16]) {
+    typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+    if (a.jt >= 0) {                                     // padded with zeros, pieces aligned
+        const int64_t t = (int64_t)row * a.ldj + min(64 * c + 16 * kg, (a.N - 1) & ~15);
+        if (a.jt == JT_FP8) {
+            const i32x4_r w = *(const i32x4_r *)((const uint8_t *)a.Js + t);
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                x[4 * q] = __builtin_amdgcn_cvt_f32_fp8(w[q], 0);
+                x[4 * q + 1] = __builtin_amdgcn_cvt_f32_fp8(w[q], 1);
+                x[4 * q + 2] = __builtin_amdgcn_cvt_f32_fp8(w[q], 2);
+                x[4 * q + 3] = __builtin_amdgcn_cvt_f32_fp8(w[q], 3);
+            }
+        } else if (a.jt == JT_BF16) {
+#pragma unroll
+            for (int q = 0; q < 2; q++) {
+                const i32x4_r w = *(const i32x4_r *)((const uint16_t *)a.Js + t + 8 * q);
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    x[8 * q + 2 * e] = __uint_as_float((uint32_t)w[e] << 16);
+                    x[8 * q + 2 * e + 1] = __uint_as_float((uint32_t)w[e] & 0xffff0000u);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const float4 f = *(const float4 *)((const float *)a.Js + t + 4 * q);
+                x[4 * q] = f.x; x[4 * q + 1] = f.y; x[4 * q + 2] = f.z; x[4 * q + 3] = f.w;
+            }
+        }
+        return;
+    }
+    const int k = 64 * c + 2 * kg;
+    const double *Jr = a.J + (int64_t)row * a.N + k;
+    if (64 * c + 64 <= a.N) {
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            const d2 d = *(const d2 *)(Jr + 8 * j);
+            x[2 * j] = d[0];
+            x[2 * j + 1] = d[1];
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            const int o = 8 * (e >> 1) + (e & 1);
+            x[e] = k + o < a.N ? Jr[o] : 0.0;
+        }
+    }
+}
+
+// 16 consecutive spins of a vector from column k < N, a multiple of 16 (columns past the end:
+// any value).
+__device__ __forceinline__ i32x4_r mv_spins(const EnMvArgs &a, int v, int k) {
+    typedef i32x4_r i4u __attribute__((aligned(1)));
+    const int8_t *s = a.spins + (int64_t)v * a.N + k;
+    i32x4_r x = {0, 0, 0, 0};
+    if (k + 16 <= a.N) {
+        x = *(const i4u *)s;
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            uint32_t w = 0;
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+                w |= k + 4 * q + e < a.N ? (uint32_t)(uint8_t)s[4 * q + e] << (8 * e) : 0u;
+            x[q] = (int)w;
+        }
+    }
+    return x;
+}
+
+// Bytes +-1 by the sign bits.
+__device__ __forceinline__ i32x4_r mv_signs(i32x4_r x) {
+#pragma unroll
+    for (int q = 0; q < 4; q++)
+        x[q] = (int)((((uint32_t)x[q] >> 7) & 0x01010101u) * 0xfeu ^ 0x01010101u);
+    return x;
+}
+
+// Spins of columns 16 kg .. + 15 by lane group to the order of the binary64 couplings: word q
+// of group kg becomes columns 16 q + 2 kg, + 1, + 8 + 2 kg, + 9 + 2 kg.  The words for each
+// group within a lane, then a 4 x 4 transpose over the lane groups.
+__device__ __forceinline__ i32x4_r mv_order(i32x4_r x) {
+    uint32_t w0 = __builtin_amdgcn_perm(x[2], x[0], 0x05040100u);
+    uint32_t w1 = __builtin_amdgcn_perm(x[2], x[0], 0x07060302u);
+    uint32_t w2 = __builtin_amdgcn_perm(x[3], x[1], 0x05040100u);
+    uint32_t w3 = __builtin_amdgcn_perm(x[3], x[1], 0x07060302u);
+    const auto a = __builtin_amdgcn_permlane32_swap(w0, w2, false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(w1, w3, false, false);
+    const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+    const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+    return (i32x4_r){(int)c[0], (int)c[1], (int)d[0], (int)d[1]};
+}
+
+// A wavefront takes VEC vectors and a contiguous range of the blocks of 16 rows x 64 columns
+// that reach the diagonal or lie above it, in row order, the next block's couplings in flight.
+// A 16-column tile has weight 0 below the diagonal, 1 on it and 2 above: with it Q = sum over
+// ordered pairs = 2 U.  The weight goes to the spins, D 16x16x64 int8 MFMAs per 16 vectors do
+// the rest, and at the end of a block row y is folded into Q.  Bound by vector instructions:
+// the digits (about 14 a coupling), the spins' order and the folds, which is why a wavefront
+// takes as many vectors as its accumulators allow.  Measured at N = 5000, V = 256 real
+// couplings (D = 7): 1040 us as masked binary64 multiply-adds on exact parts of J, 440 us as
+// binary64 MFMAs on those, 170 us this way (211 us with 32 vectors a wavefront; 233 us with
+// digits shifted out of the significand and 16 consecutive couplings a lane); 8 instances of
+// N = 2000, V = 64, FP8 couplings (D = 1): 639 us, now 103 us.
+template <int VEC, int D>
 __device__ __forceinline__ void energy_mv_body(const EnMvArgs &a, const int bx_, const int by_) {
-    __shared__ double red[4][G + 2][L];
-    const int p = bx_, g = by_, tid = threadIdx.x;
-    const int lane = tid & 63, w = tid >> 6;
-    const int v0 = g * G, word = v0 >> 6, sh = v0 & 63;
-    const bool first = g == 0;
-    const uint64_t *M = a.masks + (int64_t)word * a.N;
-    double c[G][L], hn[L], s[L], ht[L];
+    constexpr int NT = VEC / 16;
+    __shared__ int64_t red[4][VEC][D], reds[4][D];
+    const int tid = threadIdx.x, lane = tid & 63, kg = lane >> 4, l16 = lane & 15;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int p = bx_, v0 = by_ * VEC;
+    const bool first = by_ == 0;
+    const int klast = (a.N - 1) & ~15;
+    const int nt = (a.N + 15) / 16, nc = (a.N + 63) / 64;
+    // blocks of row I: columns I / 4 .. nc - 1; rows 4 B .. 4 B + 3 start at B (4 nc - 2 (B - 1))
+    auto start = [&](int r) {
+        const int64_t B = r >> 2;
+        return B * (4ll * nc - 2 * (B - 1)) + (int64_t)(r & 3) * (nc - B);
+    };
+    // this wavefront's share: a row's fold counts as a block, so short rows are not the slowest
+    const int64_t nw = 4ll * a.P, g = 4 * p + w;
+    auto locate = [&](int64_t x, int &row) {             // first block at or after cost x
+        int lo = 0, hi = nt - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (start(mid) + mid <= x) lo = mid;
+            else hi = mid - 1;
+        }
+        row = lo;
+        const int64_t off = x - start(lo) - lo - 1;
+        return start(lo) + (off > 0 ? off : 0);
+    };
+    const int64_t cost = start(nt) + nt;
+    int I, Ie;
+    const int64_t u1 = locate(cost * (g + 1) / nw, Ie);
+    int64_t u = locate(cost * g / nw, I);
+    int c = (I >> 2) + (int)(u - start(I));
+    const int vl = v0 + l16;
+
+    int64_t q[NT][D], s2[D];
+    i32x4_r y[NT][D];
+    int s2i[D];
 #pragma unroll
-    for (int k = 0; k < L; k++) {
-        hn[k] = 0.0; s[k] = 0.0; ht[k] = 0.0;
+    for (int k = 0; k < D; k++) {
+        s2[k] = 0;
+        s2i[k] = 0;
 #pragma unroll
-        for (int v = 0; v < G; v++) c[v][k] = 0.0;
+        for (int t = 0; t < NT; t++) {
+            q[t][k] = 0;
+            y[t][k] = (i32x4_r){0, 0, 0, 0};
+        }
     }
-    for (int i = 4 * p + w; i < a.N; i += 4 * a.P) {
-        const uint64_t mi = M[i];
-        if (a.h) {
-            double t[L];
-            mv_split<L>(a, a.h[i], t);
-            // lanes x < G read bit sh + x <= 63 of the word; the others are not used
-            const double bit = (double)(uint32_t)((mi >> ((sh + lane) & 63)) & 1ull);
-            if (lane < G) {
+    const bool nat = a.jt >= 0;                          // couplings in column order
+    double x[16];
+    i32x4_r raw[NT];
+    if (u < u1) {
+        mv_load(a, min(16 * I + l16, a.N - 1), c, kg, x);
 #pragma unroll
-                for (int k = 0; k < L; k++) hn[k] = fma(t[k], bit, hn[k]);
-            }
-            if (first && lane == 0) {
-#pragma unroll
-                for (int k = 0; k < L; k++) ht[k] += t[k];
-            }
-        }
-        for (int j = i + 1 + lane; j < a.N; j += 64) {
-            double t[L];
-            mv_split<L>(a, mv_coupling(a, i, j), t);
-            if (first) {
-#pragma unroll
-                for (int k = 0; k < L; k++) s[k] += t[k];
-            }
-            const uint64_t d = (mi ^ M[j]) >> sh;
-#pragma unroll
-            for (int v = 0; v < G; v++) {
-                const double bit = (double)(uint32_t)((d >> v) & 1ull);
-#pragma unroll
-                for (int k = 0; k < L; k++) c[v][k] = fma(t[k], bit, c[v][k]);
-            }
-        }
+        for (int n = 0; n < NT; n++)
+            raw[n] = mv_spins(a, min(vl + 16 * n, a.V - 1), min(64 * c + 16 * kg, klast));
     }
-    // column sums over the lanes, then over the wavefronts
+    for (; u < u1; u++) {
+        i32x4_r A[D];
+        mv_digits<D>(x, a.scale, A);
+        const int In = c + 1 < nc ? I : I + 1, cn = c + 1 < nc ? c + 1 : (I + 1) >> 2;
+        if (u + 1 < u1) mv_load(a, min(16 * In + l16, a.N - 1), cn, kg, x);
+        // weights 0, 1, 2 of this lane's words: the shift and the mask of their spins
+        int wgt[4];
+        uint32_t keep[4];
 #pragma unroll
-    for (int v = 0; v < G; v++)
+        for (int q = 0; q < 4; q++) {
+            const int ct = 4 * c + (nat ? kg : q);       // the word's 16-column tile
+            wgt[q] = ct < I || 16 * ct >= a.N ? 0 : ct == I ? 1 : 2;
+            keep[q] = wgt[q] == 0 ? 0u : wgt[q] == 1 ? 0xffffffffu : 0xfefefefeu;
+        }
+        if (first) {
+            const bool in = 16 * I + l16 < a.N;
 #pragma unroll
-        for (int k = 0; k < L; k++) {
-            double x = c[v][k];
-            for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-            if (lane == 0) red[w][v][k] = x;
+            for (int k = 0; k < D; k++)
+#pragma unroll
+                for (int q = 0; q < 4; q++)
+                    s2i[k] += in ? wgt[q] * __builtin_amdgcn_sdot4(A[k][q], 0x01010101, 0, false) : 0;
         }
 #pragma unroll
-    for (int k = 0; k < L; k++) {
-        double x = s[k];
-        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-        if (lane == 0) {
-            red[w][G][k] = x;
-            red[w][G + 1][k] = ht[k];
+        for (int n = 0; n < NT; n++) {
+            i32x4_r sp = mv_signs(raw[n]);
+            if (!nat) sp = mv_order(sp);
+            if (u + 1 < u1)
+                raw[n] = mv_spins(a, min(vl + 16 * n, a.V - 1), min(64 * cn + 16 * kg, klast));
+#pragma unroll
+            for (int q = 0; q < 4; q++)                  // doubled: 0x01 -> 0x02, 0xff -> 0xfe
+                sp[q] = (int)(((uint32_t)sp[q] << (wgt[q] >> 1)) & keep[q]);
+#pragma unroll
+            for (int k = 0; k < D; k++)
+                y[n][k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[k], sp, y[n][k], 0, 0, 0);
         }
+        if (In != I || u + 1 == u1) {
+            // Q += s_i y_i: accumulator v of a lane is row 16 I + 4 kg + v, vector l16; the four
+            // rows stay below 1024 N <= 2^30
+            const int i0 = 16 * I + 4 * kg;
+            const bool full = 16 * I + 16 <= a.N;
+#pragma unroll
+            for (int n = 0; n < NT; n++) {
+                const int8_t *sr = a.spins + (int64_t)min(vl + 16 * n, a.V - 1) * a.N;
+                int m[4], ms = 0;                        // -1 where the spin is -1
+#pragma unroll
+                for (int v = 0; v < 4; v++) {
+                    m[v] = (int)sr[min(i0 + v, a.N - 1)] >> 31;
+                    ms -= m[v];
+                }
+                if (!full) {
+                    ms = 0;
+#pragma unroll
+                    for (int v = 0; v < 4; v++) {
+                        ms -= i0 + v < a.N ? m[v] : 0;
+#pragma unroll
+                        for (int k = 0; k < D; k++) y[n][k][v] = i0 + v < a.N ? y[n][k][v] : 0;
+                        m[v] = i0 + v < a.N ? m[v] : 0;
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < D; k++) {
+                    const int t = (y[n][k][0] ^ m[0]) + ((y[n][k][1] ^ m[1]) + ((y[n][k][2] ^ m[2]) +
+                                  ((y[n][k][3] ^ m[3]) + ms)));
+                    q[n][k] += (int64_t)t;
+                    y[n][k] = (i32x4_r){0, 0, 0, 0};
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < D; k++) {
+                s2[k] += s2i[k];
+                s2i[k] = 0;
+            }
+        }
+        I = In;
+        c = cn;
+    }
+#pragma unroll
+    for (int n = 0; n < NT; n++)
+#pragma unroll
+        for (int k = 0; k < D; k++) {
+            int64_t t = q[n][k];
+            t += (int64_t)__shfl_xor((long long)t, 16);
+            t += (int64_t)__shfl_xor((long long)t, 32);
+            if (kg == 0) red[w][16 * n + l16][k] = t;
+        }
+#pragma unroll
+    for (int k = 0; k < D; k++) {
+        int64_t t = s2[k];
+        for (int o = 32; o > 0; o >>= 1) t += (int64_t)__shfl_xor((long long)t, o);
+        if (lane == 0) reds[w][k] = t;
     }
     __syncthreads();
-    const EnMvLayout lay = energy_mv_layout(a.P, a.V, L);
-    for (int e = tid; e < G * L; e += 256) {
-        const int v = e / L, k = e % L;
+    for (int e = tid; e < VEC * D; e += 256) {
+        const int v = e / D, k = e % D;
         if (v0 + v < a.V)
-            a.part[lay.c + ((int64_t)p * a.V + v0 + v) * L + k] =
+            a.part[((int64_t)p * a.V + v0 + v) * D + k] =
                 red[0][v][k] + red[1][v][k] + red[2][v][k] + red[3][v][k];
     }
-    __syncthreads();
-    // Hn: lane x of each wavefront holds vector v0 + x
-    if (lane < G) {
-#pragma unroll
-        for (int k = 0; k < L; k++) red[w][lane][k] = hn[k];
-    }
-    __syncthreads();
-    for (int e = tid; e < G * L; e += 256) {
-        const int v = e / L, k = e % L;
-        if (v0 + v < a.V)
-            a.part[lay.hn + ((int64_t)p * a.V + v0 + v) * L + k] =
-                red[0][v][k] + red[1][v][k] + red[2][v][k] + red[3][v][k];
-    }
-    if (first && tid < L) {
-        a.part[lay.s + (int64_t)p * L + tid] =
-            red[0][G][tid] + red[1][G][tid] + red[2][G][tid] + red[3][G][tid];
-        a.part[lay.ht + (int64_t)p * L + tid] =
-            red[0][G + 1][tid] + red[1][G + 1][tid] + red[2][G + 1][tid] + red[3][G + 1][tid];
-    }
+    if (first && tid < D)
+        a.part[(int64_t)a.P * a.V * D + (int64_t)p * D + tid] =
+            reds[0][tid] + reds[1][tid] + reds[2][tid] + reds[3][tid];
 }
 
-template <int G, int L>
+template <int VEC, int D>
 __global__ __launch_bounds__(256) void k_energy_mv(EnMvArgs a) {
-    energy_mv_body<G, L>(a, blockIdx.x, blockIdx.y);
+    energy_mv_body<VEC, D>(a, blockIdx.x, blockIdx.y);
 }
 
 // Many instances: instance blockIdx.z, its own slice count nb[z] (= its a.P).
-template <int G, int L>
+template <int VEC, int D>
 __global__ __launch_bounds__(256) void k_energy_mv_many(const EnMvArgs *as, const int *nb) {
     const int k = blockIdx.z;
     if ((int)blockIdx.x >= nb[k]) return;
     const EnMvArgs a = as[k];
-    energy_mv_body<G, L>(a, blockIdx.x, blockIdx.y);
+    energy_mv_body<VEC, D>(a, blockIdx.x, blockIdx.y);
 }
 
-// Per vector (one wavefront, lanes over the slices): level totals over the slices (exact
-// binary64 in any grouping), then E = S - 2 C + Ht - 2 Hn and C in the fixed-point
-// accumulator, each rounded once.
-template <int L>
+// Per vector (one wavefront): digit totals over the slices and of H = sum h_i s_i (h shares J's
+// digits), then E = (Q + 2 H) / 2 and C = (S2 - Q) / 4, each rounded once.
+template <int D>
 __device__ __forceinline__ void energy_mv_merge_body(const EnMvArgs &a, const int bx_) {
     const int v = bx_ * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (v >= a.V) return;
-    const EnMvLayout lay = energy_mv_layout(a.P, a.V, L);
-    double C[L], Hn[L], S[L], Ht[L];
-#pragma unroll
-    for (int k = 0; k < L; k++) {
-        C[k] = 0.0; Hn[k] = 0.0; S[k] = 0.0; Ht[k] = 0.0;
-    }
-    for (int p = lane; p < a.P; p += 64) {
-#pragma unroll
-        for (int k = 0; k < L; k++) {
-            C[k] += a.part[lay.c + ((int64_t)p * a.V + v) * L + k];
-            Hn[k] += a.part[lay.hn + ((int64_t)p * a.V + v) * L + k];
-            S[k] += a.part[lay.s + (int64_t)p * L + k];
-            Ht[k] += a.part[lay.ht + (int64_t)p * L + k];
+    constexpr int G = 64 / D;
+    const int k = lane % D, p0 = lane / D;               // slices p0, p0 + G, ...
+    int64_t Q = 0, S = 0;
+    if (p0 < G)
+#pragma unroll 4
+        for (int p = p0; p < a.P; p += G) {
+            Q += a.part[((int64_t)p * a.V + v) * D + k];
+            S += a.part[(int64_t)a.P * a.V * D + (int64_t)p * D + k];
         }
-    }
+    int hs[D];
 #pragma unroll
-    for (int k = 0; k < L; k++)
-        for (int o = 32; o > 0; o >>= 1) {
-            C[k] += __shfl_xor(C[k], o);
-            Hn[k] += __shfl_xor(Hn[k], o);
-            S[k] += __shfl_xor(S[k], o);
-            Ht[k] += __shfl_xor(Ht[k], o);
-        }
-    if (lane) return;
+    for (int d = 0; d < D; d++) hs[d] = 0;
+    for (int i = 16 * lane; i < a.N; i += 1024) {
+        double x[16];
+#pragma unroll
+        for (int e = 0; e < 16; e++) x[e] = i + e < a.N ? a.h[i + e] : 0.0;
+        i32x4_r A[D];
+        mv_digits<D>(x, a.scale, A);
+        const i32x4_r sp = mv_signs(mv_spins(a, v, i));
+#pragma unroll
+        for (int d = 0; d < D; d++)
+#pragma unroll
+            for (int q = 0; q < 4; q++) hs[d] = __builtin_amdgcn_sdot4(A[d][q], sp[q], hs[d], false);
+    }
+    int64_t T = Q;                                       // Q + 2 H by digit
+#pragma unroll
+    for (int d = 0; d < D; d++) {
+        int t = hs[d];
+        for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
+        if (lane == d) T += 2 * (int64_t)t;
+    }
     Acc256 ae, ac;
     acc_zero(ae);
     acc_zero(ac);
-#pragma unroll
-    for (int k = 0; k < L; k++) {
-        acc_add(ac, C[k], a.b0);
-        acc_add(ae, S[k], a.b0);
-        acc_add(ae, Ht[k], a.b0);
-        acc_add(ae, -2.0 * C[k], a.b0);
-        acc_add(ae, -2.0 * Hn[k], a.b0);
+    if (p0 < G) {
+        // |Q_k|, |S_k| <= 128 N^2, together below 2^53
+        acc_add(ae, ldexp((double)T, a.b0 + 8 * k), a.b0);
+        acc_add(ac, ldexp((double)(S - Q), a.b0 + 8 * k), a.b0);
     }
-    if (a.E) a.E[v] = acc_round(ae, a.b0);
-    if (a.cut) a.cut[v] = acc_round(ac, a.b0);
+    acc_wave_allreduce(ae);
+    acc_wave_allreduce(ac);
+    if (lane) return;
+    if (a.E) a.E[v] = acc_round(ae, a.b0 - 1);
+    if (a.cut) a.cut[v] = acc_round(ac, a.b0 - 2);
 }
 
-template <int L>
+template <int D>
 __global__ __launch_bounds__(256) void k_energy_mv_merge(EnMvArgs a) {
-    energy_mv_merge_body<L>(a, blockIdx.x);
+    energy_mv_merge_body<D>(a, blockIdx.x);
 }
 
-template <int L>
+template <int D>
 __global__ __launch_bounds__(256) void k_energy_mv_merge_many(const EnMvArgs *as, const int *nb) {
     const int k = blockIdx.y;
     if ((int)blockIdx.x >= nb[k]) return;
     const EnMvArgs a = as[k];
-    energy_mv_merge_body<L>(a, blockIdx.x);
+    energy_mv_merge_body<D>(a, blockIdx.x);
 }
 
 int energy_slices(int N, int V) {
@@ -1224,77 +1361,89 @@ int energy_slices(int N, int V) {
     return std::max(1, std::min(want, most));
 }
 
-// Slices of the many-vector kernel: about 1024 workgroups over the vector groups, each
-// slice at least 16 rows.
-static int energy_mv_slices(int N, int groups) {
-    const int want = (1024 + groups - 1) / groups;
-    const int most = (N + 15) / 16;
-    return std::max(1, std::min(want, most));
+// Digit counts the many-vector kernel is built for.
+static const int MV_DIGITS[] = {1, 2, 4, 7, 8, 10, 12, 16, 20};
+constexpr int MV_NDIGITS = 9;
+
+// Vectors of a wavefront: up to 64 while the 4 D accumulators per 16 of them fit the registers.
+static int energy_mv_vec(int V, int D) { return V <= 16 || D > 12 ? 16 : D > 8 ? 32 : 64; }
+
+// Doubles' worth of partial sums: part of the fixed-scratch read-out's limit, so it does not
+// follow the launch; energy_mv_slices keeps within it.
+static size_t energy_mv_room(int N, int V) {
+    size_t m = 0;
+    for (int L = 1; L <= 4; L++) {
+        const int G = L == 1 ? 64 : L == 2 ? 32 : 16, groups = (V + G - 1) / G;
+        const size_t P = std::max(1, std::min((1024 + groups - 1) / groups, (N + 15) / 16));
+        m = std::max(m, 2 * P * L * (V + 1));
+    }
+    return m;
 }
 
-static int energy_mv_group(int L) { return L == 1 ? 64 : L == 2 ? 32 : 16; }
+// Slices: one or two workgroups per CU over the vector blocks (64-vector blocks fill the
+// registers of one), each slice at least a block row, within the room for partial sums.
+static int energy_mv_slices(int N, int V, int D) {
+    const int vec = energy_mv_vec(V, D), blocks = (V + vec - 1) / vec;
+    const int want = ((D > 2 ? 256 : 512) + blocks - 1) / blocks;
+    const int most = std::min((N + 15) / 16, (int)(energy_mv_room(N, V) / ((size_t)D * (V + 1))));
+    return std::max(1, std::min(want, most));
+}
 
 size_t energy_part_bytes(int N, int V) {
     V = std::max(V, 1);
     const size_t old = (size_t)V * energy_slices(N, V) * 2 * sizeof(Acc256);
-    size_t mv = 0;
-    for (int L = 1; L <= 4; L++) {
-        const int G = energy_mv_group(L);
-        const int P = energy_mv_slices(N, (V + G - 1) / G);
-        const size_t b = (size_t)((V + 63) / 64) * N * 8 +
-                         (size_t)energy_mv_layout(P, V, L).total * 8 + 256;
-        mv = std::max(mv, b);
-    }
+    const size_t mv = (size_t)((V + 63) / 64) * N * 8 + energy_mv_room(N, V) * 8 + 256;
     return std::max(old, mv);
 }
 
-// Levels of the many-vector kernel for instance I (0: it does not apply).
-static int energy_levels(const Instance &I, double *K) {
-    for (int k = 0; k < 4; k++) K[k] = 0.0;
+// Digits of the many-vector kernel for instance I (0: it does not apply): the smallest count
+// it is built for with 8 D - 2 >= span.  The partial sums have to fit their room even in one
+// slice, and every digit total has to stay a normal binary64 number.
+static int energy_digits(const Instance &I, int V) {
     if (I.layout != HQA_DENSE || I.es.lsb == INT32_MIN) return 0;
-    const double terms = (double)I.N * I.N + I.N;
-    int lg = 0;
-    while (lg < 64 && std::ldexp(1.0, lg) < terms) lg++;
-    const int w = 51 - lg;
-    if (w < 8) return 0;
     const int span = I.es.msb + 1 - I.es.lsb;
-    const int L = std::max(1, (span + w - 1) / w);
-    // the rounding constants stay normal binary64 numbers
-    if (L > 4 || I.es.lsb + 52 < -1022 || I.es.lsb + (L - 1) * w + 52 > 1000) return 0;
-    for (int k = 1; k < L; k++) K[k] = std::ldexp(1.5, I.es.lsb + k * w + 52);
-    return L;
+    if (I.es.msb > 900 || I.es.lsb < -900 || I.N > (1 << 20)) return 0;
+    for (int k = 0; k < MV_NDIGITS; k++)
+        if (8 * MV_DIGITS[k] - 2 >= span)
+            return (size_t)MV_DIGITS[k] * (V + 1) <= energy_mv_room(I.N, V) ? MV_DIGITS[k] : 0;
+    return 0;
 }
 
-template <int L>
-static void launch_mv(EnMvArgs &a, hipStream_t st) {
-    constexpr int G = L == 1 ? 64 : L == 2 ? 32 : 16;
-    const int groups = (a.V + G - 1) / G;
-    a.P = energy_mv_slices(a.N, groups);
-    k_energy_mv<G, L><<<dim3(a.P, groups), 256, 0, st>>>(a);
-    k_energy_mv_merge<L><<<(a.V + 3) / 4, 256, 0, st>>>(a);
+static EnMvArgs energy_mv_args(const Instance &I, int V, int D, const int8_t *spins, double *E,
+                               double *cut, void *part) {
+    EnMvArgs m;
+    m.N = I.N; m.V = V; m.b0 = I.es.lsb; m.P = energy_mv_slices(I.N, V, D);
+    m.J = I.J64; m.h = I.h64; m.spins = spins; m.E = E; m.cut = cut;
+    // the compact storage copy when it holds every coupling exactly
+    m.jt = -1; m.ldj = 0; m.Js = nullptr;
+    if (I.js_exact && I.Js) {
+        m.jt = (int)I.jt; m.ldj = I.Np; m.Js = I.Js;
+    }
+    m.part = (int64_t *)part;
+    m.scale = std::ldexp(1.0, -I.es.lsb);
+    return m;
+}
+
+// k_energy_mv or its batched form for (vec, D): f(integral constants) over the built pairs.
+template <class F>
+static void energy_mv_dispatch(int vec, int D, F f) {
+#define HQA_MV(VV, DD) if (vec == VV && D == DD) f(std::integral_constant<int, VV>(), std::integral_constant<int, DD>());
+    HQA_MV(16, 1) HQA_MV(16, 2) HQA_MV(16, 4) HQA_MV(16, 7) HQA_MV(16, 8) HQA_MV(16, 10)
+    HQA_MV(16, 12) HQA_MV(16, 16) HQA_MV(16, 20) HQA_MV(32, 10) HQA_MV(32, 12)
+    HQA_MV(64, 1) HQA_MV(64, 2) HQA_MV(64, 4) HQA_MV(64, 7) HQA_MV(64, 8)
+#undef HQA_MV
 }
 
 hipError_t launch_energy(const Instance &I, int V, const int8_t *spins, double *E, double *cut,
                          void *part, hipStream_t st) {
     if (V == 0) return hipSuccess;
-    EnMvArgs m;
-    const int L = energy_levels(I, m.K);
-    if (L) {
-        m.N = I.N; m.V = V; m.b0 = I.es.lsb;
-        m.J = I.J64; m.h = I.h64; m.spins = spins; m.E = E; m.cut = cut;
-        // the compact storage copy when it holds every coupling exactly
-        m.jt = -1; m.ldj = 0; m.Js = nullptr;
-        if (I.js_exact && I.Js) {
-            m.jt = (int)I.jt; m.ldj = I.Np; m.Js = I.Js;
-        }
-        m.masks = (uint64_t *)part;
-        const size_t mw = (size_t)((V + 63) / 64) * I.N;
-        m.part = (double *)((uint8_t *)part + ((mw * 8 + 255) & ~(size_t)255));
-        k_pack_masks<<<(unsigned)((mw + 255) / 256), 256, 0, st>>>(I.N, V, spins, m.masks);
-        if (L == 1) launch_mv<1>(m, st);
-        else if (L == 2) launch_mv<2>(m, st);
-        else if (L == 3) launch_mv<3>(m, st);
-        else launch_mv<4>(m, st);
+    if (const int D = energy_digits(I, V)) {
+        const EnMvArgs m = energy_mv_args(I, V, D, spins, E, cut, part);
+        const int vec = energy_mv_vec(V, D);
+        energy_mv_dispatch(vec, D, [&](auto vv, auto dd) {
+            k_energy_mv<vv.value, dd.value><<<dim3(m.P, (V + vec - 1) / vec), 256, 0, st>>>(m);
+            k_energy_mv_merge<dd.value><<<(V + 3) / 4, 256, 0, st>>>(m);
+        });
         return hipGetLastError();
     }
     EnArgs a;
@@ -1339,7 +1488,7 @@ size_t put_vec(Blob &b, const std::vector<T> &v) { return b.put(v.data(), v.size
 size_t readout_batch_arg_bytes(int count) {
     // the argument arrays and their block counts, each rounded to 256 bytes
     const size_t per = sizeof(EnMvArgs) + sizeof(EnumRealArgs) + sizeof(EnumArgs) + sizeof(SelArgs) +
-                       sizeof(RedArgs) + sizeof(MergeArgs) + sizeof(PackArgs) + 24 * sizeof(int);
+                       sizeof(RedArgs) + sizeof(MergeArgs) + 24 * sizeof(int);
     return (size_t)count * per + 40 * 256;
 }
 
@@ -1405,46 +1554,27 @@ hipError_t launch_readout_batch(const std::vector<ReadoutJob> &jobs, int R, int 
     const size_t o_er = put_vec(b, er), o_ner = put_vec(b, ner), o_nmid = put_vec(b, nmid);
     const size_t o_ei = put_vec(b, ei), o_nei = put_vec(b, nei);
     const size_t o_mg = put_vec(b, mg), o_nmg = put_vec(b, nmg);
-    // energy: the many-vector kernel by level count; others one instance at a time
-    std::vector<PackArgs> pk;
-    std::vector<int> npk;
-    std::vector<EnMvArgs> mv[5];
-    std::vector<int> nmv[5], nmm[5];   // slices of the sums, blocks of the merge
+    // energy: the many-vector kernel by digit count; others one instance at a time
+    std::vector<EnMvArgs> mv[MV_NDIGITS];
+    std::vector<int> nmv[MV_NDIGITS], nmm[MV_NDIGITS];   // slices of the sums, blocks of the merge
     std::vector<int> fallback;
     for (int c = 0; c < count; c++) {
         const ReadoutJob &j = jobs[c];
-        const Instance &I = *j.I;
-        EnMvArgs m;
-        const int L = energy_levels(I, m.K);
-        if (!L) {
+        const int D = energy_digits(*j.I, R);
+        if (!D) {
             fallback.push_back(c);
             continue;
         }
-        m.N = I.N; m.V = R; m.b0 = I.es.lsb;
-        m.J = I.J64; m.h = I.h64; m.spins = j.spins; m.E = j.E; m.cut = j.C;
-        m.jt = -1; m.ldj = 0; m.Js = nullptr;
-        if (I.js_exact && I.Js) {
-            m.jt = (int)I.jt; m.ldj = I.Np; m.Js = I.Js;
-        }
-        m.masks = (uint64_t *)j.part;
-        const size_t mw = (size_t)((R + 63) / 64) * I.N;
-        m.part = (double *)((uint8_t *)j.part + ((mw * 8 + 255) & ~(size_t)255));
-        const int G = energy_mv_group(L);
-        m.P = energy_mv_slices(I.N, (R + G - 1) / G);
-        PackArgs q;
-        q.N = I.N; q.V = R; q.spins = j.spins; q.masks = m.masks;
-        pk.push_back(q);
-        npk.push_back((int)((mw + 255) / 256));
-        mv[L].push_back(m);
-        nmv[L].push_back(m.P);
-        nmm[L].push_back((R + 3) / 4);
+        const int x = (int)(std::find(MV_DIGITS, MV_DIGITS + MV_NDIGITS, D) - MV_DIGITS);
+        mv[x].push_back(energy_mv_args(*j.I, R, D, j.spins, j.E, j.C, j.part));
+        nmv[x].push_back(mv[x].back().P);
+        nmm[x].push_back((R + 3) / 4);
     }
-    const size_t o_pk = put_vec(b, pk), o_npk = put_vec(b, npk);
-    size_t o_mv[5] = {}, o_nmv[5] = {}, o_nmm[5] = {};
-    for (int L = 1; L <= 4; L++) {
-        o_mv[L] = put_vec(b, mv[L]);
-        o_nmv[L] = put_vec(b, nmv[L]);
-        o_nmm[L] = put_vec(b, nmm[L]);
+    size_t o_mv[MV_NDIGITS] = {}, o_nmv[MV_NDIGITS] = {}, o_nmm[MV_NDIGITS] = {};
+    for (int x = 0; x < MV_NDIGITS; x++) {
+        o_mv[x] = put_vec(b, mv[x]);
+        o_nmv[x] = put_vec(b, nmv[x]);
+        o_nmm[x] = put_vec(b, nmm[x]);
     }
     if (b.h.size() > argcap) return hipErrorInvalidValue;
     // the host copy of the arguments lives only in this call: wait for the upload
@@ -1490,19 +1620,16 @@ hipError_t launch_readout_batch(const std::vector<ReadoutJob> &jobs, int R, int 
         k_merge_many<<<dim3(mx(nmg), count), 256, 0, st>>>((const MergeArgs *)(d + o_mg),
                                                           (const int *)(d + o_nmg));
     }
-    if (!pk.empty())
-        k_pack_masks_many<<<dim3(mx(npk), (int)pk.size()), 256, 0, st>>>(
-            (const PackArgs *)(d + o_pk), (const int *)(d + o_npk));
-    for (int L = 1; L <= 4; L++) {
-        if (mv[L].empty()) continue;
-        const int G = energy_mv_group(L), groups = (R + G - 1) / G, cl = (int)mv[L].size();
-        const EnMvArgs *as = (const EnMvArgs *)(d + o_mv[L]);
-        const int *np = (const int *)(d + o_nmv[L]), *nq = (const int *)(d + o_nmm[L]);
-        const dim3 g1(mx(nmv[L]), groups, cl), g2((R + 3) / 4, cl);
-        if (L == 1) { k_energy_mv_many<64, 1><<<g1, 256, 0, st>>>(as, np); k_energy_mv_merge_many<1><<<g2, 256, 0, st>>>(as, nq); }
-        if (L == 2) { k_energy_mv_many<32, 2><<<g1, 256, 0, st>>>(as, np); k_energy_mv_merge_many<2><<<g2, 256, 0, st>>>(as, nq); }
-        if (L == 3) { k_energy_mv_many<16, 3><<<g1, 256, 0, st>>>(as, np); k_energy_mv_merge_many<3><<<g2, 256, 0, st>>>(as, nq); }
-        if (L == 4) { k_energy_mv_many<16, 4><<<g1, 256, 0, st>>>(as, np); k_energy_mv_merge_many<4><<<g2, 256, 0, st>>>(as, nq); }
+    for (int x = 0; x < MV_NDIGITS; x++) {
+        if (mv[x].empty()) continue;
+        const int D = MV_DIGITS[x], vec = energy_mv_vec(R, D), cl = (int)mv[x].size();
+        const EnMvArgs *as = (const EnMvArgs *)(d + o_mv[x]);
+        const int *np = (const int *)(d + o_nmv[x]), *nq = (const int *)(d + o_nmm[x]);
+        energy_mv_dispatch(vec, D, [&](auto vv, auto dd) {
+            k_energy_mv_many<vv.value, dd.value>
+                <<<dim3(mx(nmv[x]), (R + vec - 1) / vec, cl), 256, 0, st>>>(as, np);
+            k_energy_mv_merge_many<dd.value><<<dim3((R + 3) / 4, cl), 256, 0, st>>>(as, nq);
+        });
     }
     for (int c : fallback) {
         const ReadoutJob &j = jobs[c];
