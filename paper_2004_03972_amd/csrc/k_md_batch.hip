@@ -2,8 +2,8 @@
 //
 // A batch of uneven instances (sizes N_k, one shared schedule and replica count)
 // advances step by step; each step is one launch over a tile table of (instance, 128
-// rows, 64 replicas) tiles (32 or 16 replicas in small batches), whatever the storage type (FP32, BF16, FP8), so with 64
-// replicas each J row block is read once per step.  An FP8 instance whose couplings are
+// rows, 64 replicas) tiles (32 or 16 replicas in small batches), whatever the storage type
+// (FP32, BF16, FP8), so with 64 replicas each J row block is read once per step.  An FP8 instance whose couplings are
 // all 0 or 1 (unit-weight MAX-CUT) is streamed from a copy with one bit per coupling,
 // expanded in registers to the same BF16 operands.  In large batches the tiles of an
 // instance share one XCD; tiles are placed longest-first (LPT by padded size), so the
@@ -57,19 +57,16 @@ struct BatchArgs {
     int32_t *err;
 };
 
-// BF16 / FP8 storage: tiles of 128 rows x 64 replicas, eight wavefronts, wavefront w
-// owning row tile i0 + 16 w and all four replica tiles.  Per 128-column group the
-// flux operand block (64 replicas x 128 columns, BF16) is staged once into LDS by
-// the whole workgroup with full-line loads and shared by the eight row tiles, so it
-// is read from L2 once per 128 rows instead of once per 32; the J fragments come
+// BF16 / FP8 storage, eight wavefronts, 64, 32 or 16 replicas: wavefront w owning row tile
+// i0 + 16 w and all replica tiles.  Per 128-column group the flux operand block
+// (16 RT replicas x 128 columns, BF16) is staged once into LDS by the whole workgroup
+// with full-line loads and shared by the eight row tiles; the J fragments come
 // from the MFMA-tiled copy, one group ahead in registers; the LDS block is double-
 // buffered with one barrier per group.  Chains, operands and epilogue are those of
 // the other dense kernels (bit-identical results).  Wavefronts whose rows are all
 // padding compute on a real row tile, store nothing, and take part in the staging and
 // the barriers.  The kernel is held to 128 VGPRs so that two workgroups share a
-// compute unit: each covers the other's memory waits, tile prologue and epilogue.  On
-// the 512-instance batch that beat one workgroup per CU with a three-deep register
-// prefetch and the epilogue's loads issued early (220 VGPRs) by 4%.
+// compute unit: each covers the other's memory waits, tile prologue and epilogue.
 //
 // Every global access goes through global-address-space pointers.  The buffers come
 // from a table in memory, so plain pointers would be generic (flat) ones, and a flat
@@ -321,6 +318,219 @@ __device__ __forceinline__ void batch_lds_tile(const BatchArgs &a, int64_t q, co
     }
 }
 
+// State accesses of the epilogue, past the last-level cache if STREAM (see build_plan).
+template <bool STREAM, typename T>
+__device__ __forceinline__ T ld_state(const __attribute__((address_space(1))) T *p) {
+    if constexpr (STREAM) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+template <bool STREAM, typename T>
+__device__ __forceinline__ void st_state(__attribute__((address_space(1))) T *p, T v) {
+    if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
+// BF16 / FP8 storage, 64 replicas: four wavefronts, wavefront w owning rows i0 + 32 w .. + 31 and
+// all 64 replicas as two 32 x 32 tiles (four chains each: 128 accumulators, 240 VGPRs, two
+// workgroups a CU).  A pair of 32x32x16 MFMAs over the halves of a 32-column chunk gives the
+// bits of one 16x16x32 MFMA, and reads half the flux operands from LDS per product: eight
+// wavefronts of 16 x 16 tiles were bound by those reads (1024 LDS cycles a group and workgroup
+// against 512 of MFMA).  Bound now by two phases that all resident workgroups pass together:
+// the groups (0.8 us per group and two workgroups) and the state of the epilogue (25 us at
+// N R = 4.2 million).  Measured per step: N = 8192, R = 512, FP8 92 -> 80 us, BF16 111 -> 102;
+// N = 5400, R = 512, FP8 64 -> 56; 24 instances, R = 256 133 -> 119.  No better: fluxes by
+// asynchronous copies into four LDS blocks three groups ahead, couplings three groups ahead,
+// fluxes read from LDS a chunk ahead (80 to 82 us at N = 8192); eight wavefronts of 32 x 32
+// (84); a higher priority for one of a CU's two workgroups (80).
+template <int JT, bool STREAM>
+__device__ __forceinline__ void batch_lds_tile32(const BatchArgs &a, int64_t q, const BatchTile &tl,
+                                                 const BatchInst &I,
+                                                 bf16 (&Bs)[2][BL_REPS][BL_LDB]) {
+    typedef float f32x16 __attribute__((ext_vector_type(16)));
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i0 = tl.i0 + 32 * w;
+    const int r0 = tl.r0;
+    const bool odd = a.cur != 0;
+    const float *phi_in = odd ? I.phi[1] : I.phi[0];
+    const bf16 *xb_in = odd ? I.xb[1] : I.xb[0];
+    float *phi_out = odd ? I.phi[0] : I.phi[1];
+    bf16 *xb_out = odd ? I.xb[0] : I.xb[1];
+    const int ngroups = I.Np / 128;
+    using JW = typename std::conditional<JT == JT_BIT, uint32_t, u32x4_b>::type;
+    constexpr int NA = JT == JT_BF16 ? 4 : JT == JT_FP8 ? 2 : 1;
+    // lane (row l32, half hf) takes the words of its row's 16-row tile, K groups hf and 2 + hf
+    // of each chunk; rows past the last real tile read that tile
+    const int t0 = min(i0, I.N - 1) / 16, t1 = min(i0 + 16 * ((lane >> 4) & 1), I.N - 1) / 16;
+    const auto *Jt = gld<JW>((const uint8_t *)I.Jt + (int64_t)t0 * I.nrounds * 64 * (int)sizeof(JW) * NA);
+    const int jl = ((t1 - t0) * I.nrounds * 64 + 16 * hf + (lane & 15)) * NA;
+    // staging: 16 threads a replica row (16 bytes each), rows tid / 16 + 16 v
+    const auto *Bsrc = gld<u32x4_b>(xb_in + (int64_t)r0 * I.ld);
+    const int srow = tid >> 4, sseg = tid & 15;
+    int sl[4];
+#pragma unroll
+    for (int v = 0; v < 4; v++) sl[v] = (min(r0 + srow + 16 * v, a.R - 1) - r0) * (I.ld / 8) + sseg;
+
+    f32x16 acc[2][4];
+#pragma unroll
+    for (int rt = 0; rt < 2; rt++)
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) acc[rt][j][e] = 0.f;
+
+    JW A0[2][NA], A1[2][NA];
+    u32x4_b S0[4];
+#define HQA_LOAD_J(g, A)                                                              \
+    do {                                                                              \
+        _Pragma("unroll") for (int s = 0; s < 2; s++)                                \
+            _Pragma("unroll") for (int j = 0; j < NA; j++)                           \
+                A[s][j] = Jt[(g) * 64 * NA + jl + 32 * NA * s + j];                   \
+    } while (0)
+#define HQA_LOAD_S(g, S)                                                              \
+    do {                                                                              \
+        _Pragma("unroll") for (int v = 0; v < 4; v++) S[v] = Bsrc[sl[v] + 16 * (g)]; \
+    } while (0)
+#define HQA_PUT_S(buf, S)                                                             \
+    do {                                                                              \
+        _Pragma("unroll") for (int v = 0; v < 4; v++)                                \
+            *(u32x4_b *)&Bs[buf][srow + 16 * v][8 * sseg] = S[v];                     \
+    } while (0)
+#define HQA_MFMA_GROUP(buf, A)                                                        \
+    do {                                                                              \
+        _Pragma("unroll") for (int j = 0; j < 4; j++)                                \
+            _Pragma("unroll") for (int s = 0; s < 2; s++) {                          \
+                const bf16x8 av = a_chunk<JT>(A[s], j);                               \
+                _Pragma("unroll") for (int rt = 0; rt < 2; rt++) {                   \
+                    const bf16x8 bv = *(const bf16x8 *)&Bs[buf][32 * rt + l32][32 * j + 16 * s + 8 * hf]; \
+                    acc[rt][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[rt][j], 0, 0, 0); \
+                }                                                                     \
+            }                                                                         \
+    } while (0)
+    const int gl = ngroups - 1;
+    if constexpr (JT != JT_BF16) {
+        // couplings of few registers: the fluxes of group g + 2 are requested when g begins
+        u32x4_b S1[4];
+        HQA_LOAD_S(0, S0);
+        HQA_LOAD_J(0, A0);
+        HQA_PUT_S(0, S0);
+        __syncthreads();
+        HQA_LOAD_S(min(1, gl), S0);
+        for (int gi = 0; gi < ngroups; gi += 2) {
+            HQA_LOAD_J(min(gi + 1, gl), A1);
+            HQA_LOAD_S(min(gi + 2, gl), S1);
+            __builtin_amdgcn_sched_barrier(0);
+            HQA_MFMA_GROUP(0, A0);
+            HQA_PUT_S(1, S0);
+            __syncthreads();
+            if (gi + 1 >= ngroups) break;
+            HQA_LOAD_J(min(gi + 2, gl), A0);
+            HQA_LOAD_S(min(gi + 3, gl), S0);
+            __builtin_amdgcn_sched_barrier(0);
+            HQA_MFMA_GROUP(1, A1);
+            HQA_PUT_S(0, S1);
+            __syncthreads();
+        }
+    } else {
+        HQA_LOAD_S(0, S0);
+        HQA_LOAD_J(0, A0);
+        HQA_PUT_S(0, S0);
+        __syncthreads();
+        for (int gi = 0; gi < ngroups; gi += 2) {
+            HQA_LOAD_S(min(gi + 1, gl), S0);
+            HQA_LOAD_J(min(gi + 1, gl), A1);
+            __builtin_amdgcn_sched_barrier(0);
+            HQA_MFMA_GROUP(0, A0);
+            HQA_PUT_S(1, S0);
+            __syncthreads();
+            if (gi + 1 >= ngroups) break;
+            HQA_LOAD_S(min(gi + 2, gl), S0);
+            HQA_LOAD_J(min(gi + 2, gl), A0);
+            __builtin_amdgcn_sched_barrier(0);
+            HQA_MFMA_GROUP(1, A1);
+            HQA_PUT_S(0, S0);
+            __syncthreads();
+        }
+    }
+#undef HQA_LOAD_J
+#undef HQA_LOAD_S
+#undef HQA_PUT_S
+#undef HQA_MFMA_GROUP
+
+    // Epilogue with full-line accesses, as in batch_lds_tile: thread (replica tid / 8 + 32 b,
+    // j = tid % 8) updates rows 32 v + 4 j .. + 3.
+    float *U = (float *)&Bs[0][0][0];                      // [64 replicas][136]
+    constexpr int UL = 136;
+#pragma unroll
+    for (int rt = 0; rt < 2; rt++)
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+            f32x4 parts[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) parts[j][e] = acc[rt][j][4 * v + e];
+            *(f32x4 *)&U[(32 * rt + l32) * UL + 32 * w + 8 * v + 4 * hf] = combine4(parts);
+        }
+    const int j8 = tid & 7;
+    f32x4 xv[2][4], pv[2][4];
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+        const int col = r0 + (tid >> 3) + 32 * b;
+        if (col >= a.R) continue;
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+            const int ib = tl.i0 + 32 * v + 4 * j8;
+            if (ib >= I.N) continue;
+            const int64_t base = (int64_t)col * I.ld + ib;
+            xv[b][v] = ld_state<STREAM>(gld<f32x4>(phi_in + base));
+            pv[b][v] = ld_state<STREAM>(gld<f32x4>(I.p + base));
+        }
+    }
+    __syncthreads();
+    const StepCoef cf = step_coef(a.a32, a.b32, q, a.rg, a.M);
+    const bool win = q + 1 >= a.T - a.W + 1;
+    bool bad = false;
+    const auto *hg = gld<float>(I.h);
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+        const int rep = (tid >> 3) + 32 * b, col = r0 + rep;
+        if (col >= a.R) continue;
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+            const int loc = 32 * v + 4 * j8, ib = tl.i0 + loc;
+            if (ib >= I.N) continue;
+            const f32x4 u = *(const f32x4 *)&U[rep * UL + loc];
+            const int64_t base = (int64_t)col * I.ld + ib;
+            f32x4 xn, ps = pv[b][v];
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                float pe = ps[e], xe = 0.0f;
+                if (ib + e < I.N) {
+                    leapfrog(cf, xv[b][v][e], u[e], hg[ib + e], pe, xe);
+                    bad |= !isfinite(xe) || !isfinite(pe);
+                } else {
+                    pe = 0.0f;
+                }
+                ps[e] = pe;
+                xn[e] = xe;
+            }
+            st_state<STREAM>(gst<f32x4>(phi_out + base), xn);
+            st_state<STREAM>(gst<f32x4>(I.p + base), ps);
+            typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
+            const bf16x4 xb = {(bf16)xn[0], (bf16)xn[1], (bf16)xn[2], (bf16)xn[3]};
+            st_state<STREAM>(gst<bf16x4>(xb_out + base), xb);
+            if (win) {
+                f32x4 sv = ld_state<STREAM>(gld<f32x4>(I.S + base));
+#pragma unroll
+                for (int e = 0; e < 4; e++) sv[e] = sv[e] + xn[e];
+                st_state<STREAM>(gst<f32x4>(I.S + base), sv);
+            }
+        }
+    }
+    if (bad) atomicOr(a.err, ERR_NONFINITE);
+}
+
 // FP32 storage: the same tiles, staging, prefetch and epilogue as batch_lds_tile, with
 // FP32 couplings read row-major (four 16-byte words per lane per group of 64 columns),
 // the FP32 flux block staged in LDS (64 replicas x 64 columns), and 16x16x4 FP32 MFMAs:
@@ -494,11 +704,27 @@ __device__ __forceinline__ void batch_lds_body(const BatchArgs &a, int64_t q) {
     else batch_lds_tile<JT_BF16, RT>(a, q, tl, I, Bs);
 }
 
-__global__ __launch_bounds__(512, 4) void k_step_batch_lds(BatchArgs a, int64_t q) {
-    batch_lds_body<BL_REPS / 16>(a, q);
+template <bool STREAM>
+__device__ __forceinline__ void batch_wide_body(const BatchArgs &a, int64_t q) {
+    __shared__ __align__(16) bf16 Bs[2][BL_REPS][BL_LDB];
+    const BatchTile tl = a.tiles[blockIdx.x];
+    if (tl.inst < 0) return;
+    const BatchInst I = a.inst[tl.inst];
+    if (I.jt == JT_FP8) batch_lds_tile32<JT_FP8, STREAM>(a, q, tl, I, Bs);
+    else if (I.jt == JT_BIT) batch_lds_tile32<JT_BIT, STREAM>(a, q, tl, I, Bs);
+    else batch_lds_tile32<JT_BF16, STREAM>(a, q, tl, I, Bs);
 }
 
-// Tiles of 32 or 16 replicas: small batches and few replicas.
+// Tiles of 64 replicas of a batch larger than the last-level cache, and of one that fits it.
+__global__ __launch_bounds__(256, 2) void k_step_batch_lds(BatchArgs a, int64_t q) {
+    batch_wide_body<true>(a, q);
+}
+
+__global__ __launch_bounds__(256, 2) void k_step_batch_cached(BatchArgs a, int64_t q) {
+    batch_wide_body<false>(a, q);
+}
+
+// Eight wavefronts of 16-row tiles: small batches and few replicas.
 template <int RT>
 __global__ __launch_bounds__(512, 4) void k_step_batch_narrow(BatchArgs a, int64_t q) {
     batch_lds_body<RT>(a, q);
@@ -528,6 +754,8 @@ struct BatchPlan {
     BatchInst *dinst = nullptr;
     BatchTile *dtiles[3] = {nullptr, nullptr, nullptr};
     int ntiles[3] = {0, 0, 0};
+    bool stream = false;                // the state passes the last-level cache by
+    bool wide = false;                  // four wavefronts of 32-row tiles
     int rt = 4;                         // replica tiles of 16 per BF16 / FP8 workgroup
     std::vector<BatchGraph> graphs;     // most recently used last
     hipStream_t cap = nullptr;          // capture-only stream (no work runs on it)
@@ -626,6 +854,20 @@ static hipError_t build_plan(hqa_md *md, BatchPlan *&out) {
             if (bp->rt == 4 && (count <= 320 || (md->R > 64 && md->R <= 96))) bp->rt = 2;
             if (bp->rt == 2 && count <= 96) bp->rt = 1;
             reps = 16 * bp->rt;
+            // Four wavefronts of 32-row tiles multiply faster, eight of 16-row tiles have the
+            // shorter way through a group when a CU holds one workgroup: they take batches whose
+            // tiles are all resident at once but uneven (24 instances, 374 tiles: 23.07 ms a
+            // pass, 23.34 with four; 40 instances 51.3 / 49.6 us a step) and BF16 couplings of
+            // few groups (N = 2048, R = 2048, 16 groups: 43 / 47 us; N = 4096, R = 1024 64 / 65;
+            // N = 8192, R = 512 111 / 102).
+            int members = 0;
+            bool few = false;
+            for (int k : dense)
+                if (member(md->inst[k])) {
+                    members++;
+                    few |= md->inst[k].jt == JT_BF16 && md->inst[k].Np < 4096;
+                }
+            bp->wide = count > 512 || (members == 1 && !few);
         }
         const bool spread = count <= 1024;
         // work of a tile: the bytes it streams (its couplings and the staged flux
@@ -689,6 +931,21 @@ static hipError_t build_plan(hqa_md *md, BatchPlan *&out) {
             for (int x = 0; x < NX; x++)
                 dst.push_back(j < xl[x].size() ? xl[x][j] : BatchTile{-1, 0, 0, 0});
     }
+    // What a step reads and writes: the couplings, and per spin two copies of phi and of its
+    // BF16 operand, p and S.  Up to the 256 MB of last-level cache it stays there from step to
+    // step; beyond, the state passes that cache by, which leaves it to the couplings and
+    // operands (us per step, kept / passed by: 24 instances R = 64, 102 MB 40.6 / 42.2; 40
+    // instances, 162 MB 49.6 / 54.0; N = 8192, R = 768, 190 MB 128 / 150; 24 instances R = 256,
+    // 271 MB 125 / 120; 60 instances, 294 MB 104 / 93; 100 instances, 464 MB 152 / 138; couplings
+    // passed by as well: 60 instances 141).
+    int64_t bytes = 0;
+    for (int k : dense) {
+        const Instance &I = md->inst[k];
+        const int64_t cells = (int64_t)I.Np * I.Np;
+        bytes += (I.jt == JT_F32 ? 4 * cells : I.jt == JT_BF16 ? 2 * cells : I.jbits > 0 ? cells / 8 : cells) +
+                 20ll * I.N * md->R;
+    }
+    bp->stream = bytes > ((int64_t)256 << 20);
     hipError_t e = dev_malloc((void **)&bp->dinst, sizeof(BatchInst) * hi.size());
     if (e == hipSuccess)
         e = hipMemcpy(bp->dinst, hi.data(), sizeof(BatchInst) * hi.size(), hipMemcpyHostToDevice);
@@ -723,7 +980,9 @@ static void enqueue_steps(hqa_md *md, const BatchPlan *bp, int64_t q0, int64_t q
             a.tiles = bp->dtiles[t];
             a.ntiles = bp->ntiles[t];
             if (t == JT_F32) k_step_batch_f32<<<a.ntiles, 512, 0, st>>>(a, q);
-            else if (bp->rt == 4) k_step_batch_lds<<<a.ntiles, 512, 0, st>>>(a, q);   // BF16 and FP8
+            else if (bp->rt == 4 && bp->stream) k_step_batch_lds<<<a.ntiles, 256, 0, st>>>(a, q);
+            else if (bp->rt == 4 && bp->wide) k_step_batch_cached<<<a.ntiles, 256, 0, st>>>(a, q);
+            else if (bp->rt == 4) k_step_batch_narrow<4><<<a.ntiles, 512, 0, st>>>(a, q);
             else if (bp->rt == 2) k_step_batch_narrow<2><<<a.ntiles, 512, 0, st>>>(a, q);
             else k_step_batch_narrow<1><<<a.ntiles, 512, 0, st>>>(a, q);
         }
