@@ -229,14 +229,13 @@ hipError_t launch_reduce(const Instance &I, int R, int n, const int32_t *amb,
 // ---------------------------------------------------------------------------
 // Exact minimum of the reduced energy E'(c) = sum_{a<b} J_ab x_a x_b + sum_a h_a x_a
 // over all codes c (bit a set: x_a = -1), ties to the smallest code.  Thread t
-// fixes the top bits of the code to t and walks the low bits in Gray-code order
-// (one workgroup per replica for integer couplings, several for real ones; see
-// k_enumerate_int and k_enum_real), updating E' and the local fields
-// f_a = h_a + sum_{b != a} J_ab x_b by one flip per code (dE = -2 x_a f_a).
-// Integer instances run in int64 (exact).  Otherwise pass 1 walks in binary64
-// and pass 2 re-walks, rescoring exactly (fixed-point accumulator, rounded once)
-// every code whose binary64 energy lies within a rigorous error bound of the
-// pass-1 minimum.
+// fixes the top bits of the code to t and walks the low bits (one workgroup per replica
+// for integer couplings, several for real ones; see k_enumerate_int and k_enum_real),
+// updating E' and the local fields f_a = h_a + sum_{b != a} J_ab x_b by flips
+// (dE = -2 x_a f_a).  Integer instances run in int32 or int64 (exact).  Otherwise pass 1
+// walks in binary64 and pass 2 re-walks, rescoring exactly (fixed-point accumulator,
+// rounded once) every code whose binary64 energy lies within a rigorous error bound of
+// the pass-1 minimum.
 // ---------------------------------------------------------------------------
 #define ENUM_MAXN 24
 #define ENERGY_MAXN_LDS 16384
@@ -320,21 +319,23 @@ __device__ __forceinline__ void gray_walk(const T *J, const T *h, int n, int nl,
 
 // Real couplings, many codes: the code space of each replica is split over P
 // workgroups of 256 threads; thread t of workgroup p fixes the top pt = n - NL bits of
-// the code to p * 256 + t and walks the NL low bits in Gray-code order.  Every code
-// sees the operations of gray_walk above in the same order (E and the local fields
-// from scratch at the start, then E - 2 x_a f_a and f_b - 2 J_ab x_a per flip, each
-// product exact, one rounding per update; the products are formed inside fma, which
-// rounds once like the two-step form), so the pass-1 minimum obeys the same error
-// bound with K = 2^NL codes per walk.  The local fields sit in registers: within a
-// block of 16 codes the flipped bit is a compile-time ruler index (with 2 J_ab of
-// those bits in registers), and the flip between blocks picks its field by selects.
-//   k_enum_real<NL>(pass 1): each workgroup's binary64 minimum (E, code) -> part;
+// the code to p * 256 + t and walks the NL low bits by blocks as k_enumerate_int does: E and
+// the fields from scratch at the start (m and 2 n roundings), one rounding of E and of each
+// field per flip between blocks, and within a block at most nine for a code's change of E (a
+// sum of up to four fields, each within 2 n + K / 8 roundings by then, and of up to six
+// couplings).  All are of numbers within 4 S, and K / 16 flips leave the errors below the
+// bound u S (m + K (2 n + 1) + K^2) of a walk that flips K = 2^NL times.
+//   k_enum_real<NL, 1>: each workgroup's binary64 minimum -> part;
 //   k_enum_real_mid: per replica, the minimum over the workgroups and the rescoring
 //     threshold E_min + 2 delta + 4 u S (the bound of k_enumerate);
-//   k_enum_real<NL>(pass 2): every code at or below the threshold is rescored exactly
-//     (fixed-point accumulator, rounded once); each workgroup's exact minimum -> part;
-//   k_enum_real_fin: per replica, the exact minimum over the workgroups, ties to the
+//   k_enum_real<NL, 2>: workgroups whose minimum is at or below the threshold walk again and
+//     rescore every such code exactly (fixed-point accumulator, rounded once); each
+//     workgroup's exact minimum -> part;
+//   k_enum_real_mid: per replica, the exact minimum over the workgroups, ties to the
 //     smallest code.
+// Bound by binary64 additions in pass 1 (three a code), the exact sums in pass 2.  n = 20,
+// 64 replicas of 12 instances: 836 us a pass with the code kept beside each minimum and both
+// walks in full; now 270 us for pass 1 (456 with every field updated per code), 255 for pass 2.
 // ---------------------------------------------------------------------------
 #define ENUM_PT_REAL 12
 
@@ -348,109 +349,158 @@ struct EnumRealArgs {
     double *e_red;
 };
 
-template <int NL>
-__device__ __forceinline__ void enum_real_body(const EnumRealArgs &a, int pass, const int bx_) {
-    __shared__ double Jd[ENUM_MAXN * ENUM_MAXN], J2[ENUM_MAXN * ENUM_MAXN], hd[ENUM_MAXN];
+template <int NL, int PASS>
+__device__ __forceinline__ void enum_real_body(const EnumRealArgs &a, const int bx_) {
+    __shared__ double Jd[ENUM_MAXN * ENUM_MAXN], J4[ENUM_MAXN * ENUM_MAXN], hd[ENUM_MAXN];
     __shared__ double sE[256];
-    __shared__ int64_t sC[256];
+    __shared__ int64_t sC[PASS == 2 ? 256 : 1];
     const int r = bx_ / a.P, p = bx_ % a.P, tid = threadIdx.x, n = a.n;
+    const double thr = PASS == 2 ? a.thresh[r] : 0.0;
+    // pass 2 walks the same binary64 energies: without one at or below the threshold in pass 1
+    // this workgroup has no code to rescore
+    if (PASS == 2 && !(a.partE[(int64_t)r * a.P + p] <= thr)) {
+        __syncthreads();
+        if (tid == 0) {
+            a.partE[(int64_t)r * a.P + p] = INFINITY;
+            a.partC[(int64_t)r * a.P + p] = INT64_MAX;
+        }
+        return;
+    }
     for (int k = tid; k < n * n; k += 256) {
         const double v = a.J_eff[(int64_t)r * n * n + k];
         Jd[k] = v;
-        J2[k] = 2.0 * v;
+        J4[k / n * ENUM_MAXN + k % n] = 4.0 * v;
     }
     for (int k = tid; k < n; k += 256) hd[k] = a.h_eff[(int64_t)r * n + k];
     __syncthreads();
     const uint32_t top = (uint32_t)(p * 256 + tid);
     const bool active = top < (1u << (n - NL));
-    const double thr = pass == 2 ? a.thresh[r] : 0.0;
     double bestE = INFINITY;
     int64_t bestC = INT64_MAX;
-    auto visit = [&](double E, uint32_t c) {
-        if (pass == 1) {
-            if (better_d(E, c, bestE, bestC)) { bestE = E; bestC = c; }
-        } else if (E <= thr) {
-            const double ex = energy_exact(Jd, hd, n, c, a.b0);
-            if (better_d(ex, c, bestE, bestC)) { bestE = ex; bestC = c; }
-        }
-    };
     if (active) {
-        uint32_t code = top << NL;
+        const uint32_t code = top << NL;
         double E = energy_from_scratch<double>(Jd, hd, n, code);
-        visit(E, code);
-        if constexpr (NL > 0) {
-            double f[NL];
+        constexpr int NA = NL < 4 ? NL : 4, NC = 1 << NA, NBLK = 1 << (NL - NA), NU = NBLK < 4 ? NBLK : 4;
+        // G_b = -2 f_b with the block's bits 0: flipping b from there adds G_b x_b
+        double G[NL ? NL : 1], Q[NC];
 #pragma unroll
-            for (int aa = 0; aa < NL; aa++) {
-                double acc = hd[aa];
-                for (int b = 0; b < n; b++)
-                    if (b != aa) acc = acc + Jd[aa * n + b] * (((code >> b) & 1) ? -1.0 : 1.0);
-                f[aa] = acc;
+        for (int aa = 0; aa < NL; aa++) {
+            double acc = hd[aa];
+            for (int b = 0; b < n; b++)
+                if (b != aa) acc = acc + Jd[aa * n + b] * (((code >> b) & 1) ? -1.0 : 1.0);
+            G[aa] = -2.0 * acc;
+        }
+        // pairs flipped together, by code of the block
+#pragma unroll
+        for (int c = 0; c < NC; c++) {
+            Q[c] = 0.0;
+#pragma unroll
+            for (int x = 0; x < NA; x++)
+#pragma unroll
+                for (int y = x + 1; y < NA; y++)
+                    if ((c >> x & 1) && (c >> y & 1)) Q[c] = Q[c] + J4[x * ENUM_MAXN + y];
+        }
+        uint32_t up = 0;                               // the low bits above the block's, uniform
+        auto block = [&]() {
+            double u[NC], mn = 0.0;
+            u[0] = 0.0;
+#pragma unroll
+            for (int c = 1; c < NC; c++) {
+                const int t = 31 - __builtin_clz(c), c0 = c ^ (1 << t);
+                u[c] = c0 ? u[c0] + G[t] : G[t];       // sum of G over the flipped bits
             }
-            constexpr int NA = NL < 4 ? NL : 4;        // bits flipped inside a block of 16
-            double D[NA][NL];
 #pragma unroll
-            for (int aa = 0; aa < NA; aa++)
+            for (int c = 1; c < NC; c++) {
+                if (c & (c - 1)) u[c] = u[c] + Q[c];
+                mn = __builtin_fmin(mn, u[c]);
+            }
+            // rounding is monotone: E + mn is the least of the block's E + u
+            if constexpr (PASS == 1) {
+                bestE = __builtin_fmin(bestE, E + mn);
+            } else if (E + mn <= thr) {
+#pragma unroll 1
+                for (int c = 0; c < NC; c++) {
+                    double uc = u[0];
 #pragma unroll
-                for (int b = 0; b < NL; b++) D[aa][b] = J2[aa * n + b];
-            constexpr int NBLK = NL >= 4 ? 1 << (NL - 4) : 1;
-            for (int m = 0; m < NBLK; m++) {
-#pragma unroll
-                for (int j = 1; j < 16; j++) {
-                    if (j >= (1 << NL)) break;
-                    const int aa = __builtin_ctz(j);
-                    const double xa = ((code >> aa) & 1u) ? -1.0 : 1.0;
-                    E = __builtin_fma(-2.0 * xa, f[aa], E);
-#pragma unroll
-                    for (int b = 0; b < NL; b++)
-                        if (b != aa) f[b] = __builtin_fma(-xa, D[aa][b], f[b]);
-                    code ^= 1u << aa;
-                    visit(E, code);
-                }
-                if (m + 1 < NBLK) {                       // flip of bit 4 + ctz(m + 1)
-                    const int aa = 4 + __builtin_ctz(m + 1);
-                    const double xa = ((code >> aa) & 1u) ? -1.0 : 1.0;
-                    double fa = f[0];
-#pragma unroll
-                    for (int b = 1; b < NL; b++) fa = b == aa ? f[b] : fa;
-                    E = __builtin_fma(-2.0 * xa, fa, E);
-#pragma unroll
-                    for (int b = 0; b < NL; b++)
-                        if (b != aa) f[b] = __builtin_fma(-xa, J2[aa * n + b], f[b]);
-                    code ^= 1u << aa;
-                    visit(E, code);
+                    for (int k = 1; k < NC; k++) uc = k == c ? u[k] : uc;
+                    if (E + uc <= thr) {
+                        const uint32_t full = code | up | (uint32_t)c;
+                        const double ex = energy_exact(Jd, hd, n, full, a.b0);
+                        if (better_d(ex, full, bestE, bestC)) { bestE = ex; bestC = full; }
+                    }
                 }
             }
+        };
+        // flip of bit aa (uniform), x_a +1 where its bit is 0
+        auto flip = [&](int aa, double ga, const double (&row)[NL ? NL : 1]) {
+            const double xa = ((up >> aa) & 1u) ? -1.0 : 1.0;
+            E = __builtin_fma(xa, ga, E);
+#pragma unroll
+            for (int b = 0; b < NL; b++) G[b] = __builtin_fma(xa, row[b], G[b]);   // J_aa = 0
+            up ^= 1u << aa;
+        };
+        if constexpr (NL > 4) {
+            double R4[NL], R5[NL];
+#pragma unroll
+            for (int b = 0; b < NL; b++) {
+                R4[b] = J4[4 * ENUM_MAXN + b];
+                R5[b] = NL > 5 ? J4[5 * ENUM_MAXN + b] : 0.0;
+            }
+            for (int m = 0; m < NBLK; m += NU) {
+                block();
+                flip(4, G[4], R4);
+                block();
+                if constexpr (NL > 5) {
+                    flip(5, G[5], R5);
+                    block();
+                    flip(4, G[4], R4);
+                    block();
+                    if (m + NU < NBLK) {
+                        const int aa = 4 + __builtin_ctz(m + NU);
+                        double ga = G[0], row[NL];
+#pragma unroll
+                        for (int b = 6; b < NL; b++) ga = b == aa ? G[b] : ga;
+#pragma unroll
+                        for (int b = 0; b < NL; b++) row[b] = J4[aa * ENUM_MAXN + b];
+                        flip(aa, ga, row);
+                    }
+                }
+            }
+        } else {
+            block();
         }
     }
     sE[tid] = bestE;
-    sC[tid] = bestC;
+    if (PASS == 2) sC[tid] = bestC;
     __syncthreads();
     for (int s2 = 128; s2 > 0; s2 >>= 1) {
-        if (tid < s2 && better_d(sE[tid + s2], sC[tid + s2], sE[tid], sC[tid])) {
-            sE[tid] = sE[tid + s2];
-            sC[tid] = sC[tid + s2];
+        if (tid < s2) {
+            if constexpr (PASS == 1) {
+                if (sE[tid + s2] < sE[tid]) sE[tid] = sE[tid + s2];
+            } else if (better_d(sE[tid + s2], sC[tid + s2], sE[tid], sC[tid])) {
+                sE[tid] = sE[tid + s2];
+                sC[tid] = sC[tid + s2];
+            }
         }
         __syncthreads();
     }
     if (tid == 0) {
         a.partE[(int64_t)r * a.P + p] = sE[0];
-        a.partC[(int64_t)r * a.P + p] = sC[0];
+        a.partC[(int64_t)r * a.P + p] = PASS == 2 ? sC[0] : 0;
     }
 }
 
-template <int NL>
-__global__ __launch_bounds__(256) void k_enum_real(EnumRealArgs a, int pass) {
-    enum_real_body<NL>(a, pass, blockIdx.x);
+template <int NL, int PASS>
+__global__ __launch_bounds__(256) void k_enum_real(EnumRealArgs a) {
+    enum_real_body<NL, PASS>(a, blockIdx.x);
 }
 
-template <int NL>
-__global__ __launch_bounds__(256) void k_enum_real_many(const EnumRealArgs *as, const int *nb,
-                                                        int pass) {
+template <int NL, int PASS>
+__global__ __launch_bounds__(256) void k_enum_real_many(const EnumRealArgs *as, const int *nb) {
     const int k = blockIdx.y;
     if ((int)blockIdx.x >= nb[k]) return;
     const EnumRealArgs a = as[k];
-    enum_real_body<NL>(a, pass, blockIdx.x);
+    enum_real_body<NL, PASS>(a, blockIdx.x);
 }
 
 // One wavefront per replica: minimum over the P workgroup results; after pass 1 the
@@ -511,9 +561,9 @@ __global__ __launch_bounds__(64) void k_enum_real_mid_many(const EnumRealArgs *a
 
 template <int NL>
 static void launch_enum_real(const EnumRealArgs &a, hipStream_t st) {
-    k_enum_real<NL><<<a.R * a.P, 256, 0, st>>>(a, 1);
+    k_enum_real<NL, 1><<<a.R * a.P, 256, 0, st>>>(a);
     k_enum_real_mid<<<a.R, 64, 0, st>>>(a, 1);
-    k_enum_real<NL><<<a.R * a.P, 256, 0, st>>>(a, 2);
+    k_enum_real<NL, 2><<<a.R * a.P, 256, 0, st>>>(a);
     k_enum_real_mid<<<a.R, 64, 0, st>>>(a, 2);
 }
 
@@ -524,16 +574,18 @@ size_t enum_scratch_bytes(int n, int R) {
 }
 
 // Integer instances with small sums: 1024 threads per replica, thread t fixes the
-// top pt = n - NL <= 10 bits of the code to t and walks the NL low bits in Gray-code
-// order in int32.  The low bits of every thread follow the same sequence, so the
-// flipped bit a and the sign x_a before the flip are the same for all lanes: 15 of
-// every 16 flips have a compile-time a (the ruler sequence of the block), the local
-// fields sit in registers and each update f_b += (-x_a) 2 J_ab is one 24-bit
-// multiply-add with a wavefront-uniform factor.  The walk keeps the minimum of the
-// key (E' + S) << NL | low code, so equal energies resolve to the smallest code.
+// top pt = n - NL <= 10 bits of the code to t and walks the NL low bits in int32: blocks of
+// the 16 codes of the lowest four bits, one flip of a higher bit (Gray order) between them.
+// From the block's first code, all four x = +1, flipping the set F changes E' by
+// -2 sum_F f_a + 4 sum_{a<b in F} J_ab; the second sum is the replica's, so a code costs an
+// addition, a 24-bit multiply-add and a minimum, and only the flips between blocks update the
+// NL fields.  The low bits of every thread follow the same sequence, so the flipped bit and
+// its sign are wavefront-uniform.  The walk keeps the minimum of the key
+// (E' + S) << NL | low code, so equal energies resolve to the smallest code.
 // Requires every |J_ab|, |h_a| integral with S = sum_{a<b} |J_ab| + sum_a |h_a| below
-// 2^22 and 2 S < 2^(31 - NL) (all terms then fit the 24-bit products and the key);
-// other integer replicas take the int64 walk.
+// 2^22 and 2 S < 2^(31 - NL) (sums of f over F stay within 2 S, changes of E' within 2 S: all
+// terms then fit the 24-bit products and the key); other integer replicas take the int64 walk.
+// Measured at n = 20, R = 1024: 440 us with every field updated per code, 233 this way.
 #define ENUM_PT 10
 
 __device__ __forceinline__ int32_t mad24(int32_t x, int32_t y, int32_t z) {
@@ -554,51 +606,73 @@ __device__ __forceinline__ void walk_i32(const int32_t *Jv, const int32_t *J2, c
         for (int bb = aa + 1; bb < n; bb++) acc += Jv[aa * n + bb] * xof(bb);
         E += xof(aa) * acc;
     }
-    uint32_t key = (uint32_t)E << NL;
-    if constexpr (NL > 0) {
-        int32_t f[NL];
+    constexpr int NA = NL < 4 ? NL : 4, NC = 1 << NA, NBLK = 1 << (NL - NA), NU = NBLK < 4 ? NBLK : 4;
+    int32_t f[NL ? NL : 1], Q[NC];
+#pragma unroll
+    for (int b = 0; b < NL; b++) {
+        int32_t acc = hv[b];
+        for (int c = 0; c < n; c++) acc += Jv[b * n + c] * xof(c);   // J_bb = 0
+        f[b] = acc;
+    }
+    // pairs flipped together, by code of the block, with that code below them
+#pragma unroll
+    for (int c = 0; c < NC; c++) {
+        int32_t t = 0;
+#pragma unroll
+        for (int x = 0; x < NA; x++)
+#pragma unroll
+            for (int y = x + 1; y < NA; y++)
+                if ((c >> x & 1) && (c >> y & 1)) t += 2 * J2[x * ENUM_MAXN + y];
+        Q[c] = (int32_t)((uint32_t)t << NL) + c;
+    }
+    uint32_t g = 0, key = 0xffffffffu;                 // g: the low bits above the block's, uniform
+    auto block = [&]() {
+        int32_t u[NC], mn = 0;
+#pragma unroll
+        for (int c = 1; c < NC; c++) {
+            const int t = 31 - __builtin_clz(c), c0 = c ^ (1 << t);
+            u[c] = c0 ? u[c0] + f[t] : f[t];           // sum of f over the flipped bits
+        }
+#pragma unroll
+        for (int c = 1; c < NC; c++) mn = min(mn, mad24(u[c], -(2 << NL), Q[c]));
+        key = min(key, ((uint32_t)E << NL) + g + (uint32_t)mn);
+    };
+    auto flip = [&](int aa, int32_t fa, const int32_t (&row)[NL ? NL : 1]) {
+        const int32_t sgn = ((g >> aa) & 1u) ? 1 : -1;   // -x_a before the flip
+        E = mad24(fa, 2 * sgn, E);
+#pragma unroll
+        for (int b = 0; b < NL; b++) f[b] = mad24(row[b], sgn, f[b]);   // J_aa = 0
+        g ^= 1u << aa;
+    };
+    if constexpr (NL > 4) {
+        int32_t R4[NL], R5[NL];
 #pragma unroll
         for (int b = 0; b < NL; b++) {
-            int32_t acc = hv[b];
-            for (int c = 0; c < n; c++) acc += Jv[b * n + c] * xof(c);   // J_bb = 0
-            f[b] = acc;
+            R4[b] = J2[4 * ENUM_MAXN + b];
+            R5[b] = NL > 5 ? J2[5 * ENUM_MAXN + b] : 0;
         }
-        constexpr int NA = NL < 4 ? NL : 4;           // bits flipped inside a block of 16
-        int32_t D[NA][NL];
+        for (int m = 0; m < NBLK; m += NU) {
+            block();
+            flip(4, f[4], R4);
+            block();
+            if constexpr (NL > 5) {
+                flip(5, f[5], R5);
+                block();
+                flip(4, f[4], R4);
+                block();
+                if (m + NU < NBLK) {
+                    const int aa = 4 + __builtin_ctz(m + NU);
+                    int32_t fa = f[0], row[NL];
 #pragma unroll
-        for (int aa = 0; aa < NA; aa++)
+                    for (int b = 6; b < NL; b++) fa = b == aa ? f[b] : fa;
 #pragma unroll
-            for (int b = 0; b < NL; b++) D[aa][b] = J2[aa * n + b];
-        uint32_t g = 0;                                // low code (uniform)
-        constexpr int NBLK = NL >= 4 ? 1 << (NL - 4) : 1;
-        for (int m = 0; m < NBLK; m++) {
-#pragma unroll
-            for (int j = 1; j < 16; j++) {
-                if (j >= (1 << NL)) break;
-                constexpr int dummy = 0;
-                (void)dummy;
-                const int aa = __builtin_ctz(j);
-                const int32_t sgn = ((g >> aa) & 1u) ? 1 : -1;   // -x_a before the flip
-                E = mad24(f[aa], 2 * sgn, E);
-#pragma unroll
-                for (int b = 0; b < NL; b++)
-                    if (b != aa) f[b] = mad24(D[aa][b], sgn, f[b]);
-                g ^= 1u << aa;
-                key = min(key, ((uint32_t)E << NL) | g);
-            }
-            if (m + 1 < NBLK) {                        // flip of bit 4 + ctz(m + 1)
-                const int aa = 4 + __builtin_ctz(m + 1);
-                const int32_t sgn = ((g >> aa) & 1u) ? 1 : -1;
-                int32_t fa = f[0];
-#pragma unroll
-                for (int b = 1; b < NL; b++) fa = b == aa ? f[b] : fa;
-                E = mad24(fa, 2 * sgn, E);
-#pragma unroll
-                for (int b = 0; b < NL; b++) f[b] = mad24(J2[aa * n + b], sgn, f[b]);   // J_aa = 0
-                g ^= 1u << aa;
-                key = min(key, ((uint32_t)E << NL) | g);
+                    for (int b = 0; b < NL; b++) row[b] = J2[aa * ENUM_MAXN + b];
+                    flip(aa, fa, row);
+                }
             }
         }
+    } else {
+        block();
     }
     bestE = (int64_t)(key >> NL) - S;
     bestC = ((int64_t)top << NL) | (key & ((1u << NL) - 1u));
@@ -629,7 +703,7 @@ __device__ __forceinline__ void enumerate_int_body(const EnumArgs &a, const int 
     if (fast) {
         for (int k = tid; k < n * n; k += 1024) {
             Jv[k] = (int32_t)Jl[k];
-            J2[k] = 2 * (int32_t)Jl[k];
+            J2[k / n * ENUM_MAXN + k % n] = 2 * (int32_t)Jl[k];
         }
         for (int k = tid; k < n; k += 1024) hv[k] = (int32_t)hl[k];
         __syncthreads();
@@ -1596,10 +1670,11 @@ hipError_t launch_readout_batch(const std::vector<ReadoutJob> &jobs, int R, int 
             const int ce = (int)er.size();
             for (int pass = 1; pass <= 2; pass++) {
                 switch (n - pt) {
-#define HQA_ER(NL) case NL: k_enum_real_many<NL><<<dim3(R * Pe, ce), 256, 0, st>>>(as, nr, pass); break;
+#define HQA_ER(NL) case NL: if (pass == 1) k_enum_real_many<NL, 1><<<dim3(R * Pe, ce), 256, 0, st>>>(as, nr); \
+                    else k_enum_real_many<NL, 2><<<dim3(R * Pe, ce), 256, 0, st>>>(as, nr); break;
                     HQA_ER(0) HQA_ER(1) HQA_ER(2) HQA_ER(3) HQA_ER(4) HQA_ER(5) HQA_ER(6)
                     HQA_ER(7) HQA_ER(8) HQA_ER(9) HQA_ER(10) HQA_ER(11)
-                    default: k_enum_real_many<12><<<dim3(R * Pe, ce), 256, 0, st>>>(as, nr, pass); break;
+                    HQA_ER(12)
 #undef HQA_ER
                 }
                 k_enum_real_mid_many<<<dim3(R, ce), 64, 0, st>>>(as, nm, pass);
