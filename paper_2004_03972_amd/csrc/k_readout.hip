@@ -48,18 +48,39 @@ __device__ __forceinline__ uint64_t sel_key(const SelArgs &a, int r, int i, int8
     return (uint64_t)__float_as_uint(fabsf(pb));
 }
 
+// Keys are formed once and kept in LDS where they fit (N <= 8192, or 4096 in binary64); a
+// replica-minor state costs a line per value, and workgroups of the 32 replicas of a line run
+// on one XCD so that its L2 serves the other 31.  The digit's bin is found by one wavefront, four
+// bins a lane.  Measured at N = 4096, R = 1024, replica-minor: 222 us with every pass reading the
+// state and one thread walking the bins, 54 us now.
+constexpr int SEL_KEYS = 8192;
+
 __device__ __forceinline__ void select_body(const SelArgs &a, const int bx_) {
     __shared__ uint32_t hist[256];
     __shared__ uint64_t s_prefix;
     __shared__ int s_k;
     __shared__ int wsum[2][4];
-    const int r = bx_, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    __shared__ uint64_t s_keys[SEL_KEYS / 2];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    // workgroup b runs on XCD b mod 8 as a rule: whole groups of 256 replicas are dealt by lines
+    const int r = a.smaj && bx_ < (a.R & ~255)
+                      ? (bx_ & ~255) + 32 * (bx_ & 7) + ((bx_ >> 3) & 31) : bx_;
+    const bool kept = a.N <= (a.f64 ? SEL_KEYS / 2 : SEL_KEYS);
+    uint32_t *const k32 = (uint32_t *)s_keys;
+    auto key = [&](int i) -> uint64_t {
+        if (!kept) return sel_key(a, r, i, nullptr);
+        return a.f64 ? s_keys[i] : (uint64_t)k32[i];
+    };
     // spins
-    for (int i = tid; i < a.N && !a.keys; i += 256) {
-        int8_t s;
-        sel_key(a, r, i, &s);
-        a.spins[(int64_t)r * a.N + i] = s;
-    }
+    if (kept || !a.keys)
+#pragma unroll 4
+        for (int i = tid; i < a.N; i += 256) {
+            int8_t s;
+            const uint64_t k = sel_key(a, r, i, &s);
+            if (!a.keys) a.spins[(int64_t)r * a.N + i] = s;
+            if (kept && a.f64) s_keys[i] = k;
+            else if (kept) k32[i] = (uint32_t)k;
+        }
     if (a.n == 0) return;
     uint64_t prefix = 0, pmask = 0;
     if (tid == 0) s_k = a.n;
@@ -68,16 +89,30 @@ __device__ __forceinline__ void select_body(const SelArgs &a, const int bx_) {
         hist[tid] = 0;
         __syncthreads();
         for (int i = tid; i < a.N; i += 256) {
-            uint64_t k = sel_key(a, r, i, nullptr);
+            uint64_t k = key(i);
             if ((k & pmask) == prefix) atomicAdd(&hist[(k >> (8 * ps)) & 255], 1u);
         }
         __syncthreads();
-        if (tid == 0) {
-            int k = s_k;
-            int b = 0;
-            while (b < 255 && (int)hist[b] < k) { k -= hist[b]; b++; }
-            s_k = k;
-            s_prefix = prefix | ((uint64_t)b << (8 * ps));
+        if (w == 0) {
+            // the bin that holds the k-th key of the prefix (at least k keys have it)
+            int c[4], sum = 0;
+#pragma unroll
+            for (int b = 0; b < 4; b++) {
+                c[b] = (int)hist[4 * lane + b];
+                sum += c[b];
+            }
+            int upto = sum;
+            for (int off = 1; off < 64; off <<= 1) {
+                const int t = __shfl_up(upto, off);
+                if (lane >= off) upto += t;
+            }
+            int k = s_k - (upto - sum);
+            if (k >= 1 && k <= sum) {
+                int b = 0;
+                while (b < 3 && c[b] < k) { k -= c[b]; b++; }
+                s_prefix = prefix | ((uint64_t)(4 * lane + b) << (8 * ps));
+                s_k = k;
+            }
         }
         __syncthreads();
         prefix = s_prefix;
@@ -88,7 +123,7 @@ __device__ __forceinline__ void select_body(const SelArgs &a, const int bx_) {
     int eq_run = 0, out_run = 0;
     for (int c0 = 0; c0 < a.N; c0 += 256) {
         int i = c0 + tid;
-        uint64_t k = i < a.N ? sel_key(a, r, i, nullptr) : ~0ull;
+        uint64_t k = i < a.N ? key(i) : ~0ull;
         bool eq = i < a.N && k == kstar;
         bool lt = i < a.N && k < kstar;
         uint64_t beq = __ballot(eq);
@@ -147,6 +182,8 @@ hipError_t launch_select_keys(int N, int R, const float *keys, int n, int32_t *a
 // ---------------------------------------------------------------------------
 struct RedArgs {
     int N, R, n, csr, b0;
+    int words;            // 32-bit words of the dense sums (see reduce_words), 0: one accumulator
+    double scale;         // 2^-b0
     const double *J;
     const int32_t *rp, *ci;
     const double *h;
@@ -176,6 +213,48 @@ __device__ __forceinline__ double jlookup(const RedArgs &a, int i, int j) {
     return (lo < a.rp[i + 1] && a.ci[lo] == j) ? a.J[lo] : 0.0;
 }
 
+// x 2^-b0 s added to W sums: the integer in W words from the top, adding 1.5 2^52 rounds to an
+// integer and fma takes it off exactly, so that every sum of them is exact in binary64.
+template <int W>
+__device__ __forceinline__ void words_add(double x, double s, double scale, double (&sum)[W]) {
+    constexpr double RND = 0x1.8p52;
+    double m = x * scale;
+    if constexpr (W > 2) {
+        const double h = __builtin_fma(m, 0x1p-64, RND) - RND;
+        m = __builtin_fma(h, -0x1p64, m);
+        sum[2] = __builtin_fma(h, s, sum[2]);
+    }
+    if constexpr (W > 1) {
+        const double h = __builtin_fma(m, 0x1p-32, RND) - RND;
+        m = __builtin_fma(h, -0x1p32, m);
+        sum[1] = __builtin_fma(h, s, sum[1]);
+    }
+    sum[0] = __builtin_fma(m, s, sum[0]);
+}
+
+// acc += sum over k not in A of J_k s_k, on lane 0: every k, then the ambivalent ones taken off
+// (both exact).
+template <int W>
+__device__ __forceinline__ void reduce_row(const RedArgs &a, const double *Jr, const int8_t *s,
+                                           const int32_t *A, int lane, Acc256 &acc) {
+    double sum[W];
+#pragma unroll
+    for (int w = 0; w < W; w++) sum[w] = 0.0;
+#pragma unroll 8
+    for (int k = lane; k < a.N; k += 64) words_add<W>(Jr[k], (double)s[k], a.scale, sum);
+    for (int b = lane; b < a.n; b += 64) {
+        const int k = A[b];
+        if (k >= 0 && k < a.N) words_add<W>(Jr[k], -(double)s[k], a.scale, sum);
+    }
+#pragma unroll
+    for (int w = 0; w < W; w++) {
+        for (int o = 32; o > 0; o >>= 1) sum[w] += __shfl_xor(sum[w], o);
+        if (lane == 0) acc_add(acc, ldexp(sum[w], a.b0 + 32 * w), a.b0);
+    }
+}
+
+// Bound by the reads of J's rows.  n = 20, R = 64, 24 instances of 500 to 5000 spins: 509 us with
+// a fixed-point accumulator a lane and a search of A for every k, 140 us with sums of words.
 __device__ __forceinline__ void reduce_body(const RedArgs &a, const int bx_) {
     const int lane = threadIdx.x & 63;
     const int64_t wid = ((int64_t)bx_ * blockDim.x + threadIdx.x) >> 6;
@@ -188,8 +267,14 @@ __device__ __forceinline__ void reduce_body(const RedArgs &a, const int bx_) {
     Acc256 acc;
     acc_zero(acc);
     if (lane == 0) acc_add(acc, a.h[row], a.b0);
-    if (!a.csr) {
-        const double *Jr = a.J + (int64_t)row * a.N;
+    const double *Jr = a.J + (int64_t)row * a.N;
+    if (a.words == 1) {
+        reduce_row<1>(a, Jr, s, A, lane, acc);
+    } else if (a.words == 2) {
+        reduce_row<2>(a, Jr, s, A, lane, acc);
+    } else if (a.words == 3) {
+        reduce_row<3>(a, Jr, s, A, lane, acc);
+    } else if (!a.csr) {
         for (int k = lane; k < a.N; k += 64)
             if (!in_sorted(A, a.n, k)) acc_add(acc, Jr[k] * (double)s[k], a.b0);
     } else {
@@ -214,10 +299,26 @@ __global__ __launch_bounds__(256) void k_reduce_many(const RedArgs *as, const in
     reduce_body(a, blockIdx.x);
 }
 
+// Words of the dense sums: the N + n terms below 2^span leave every sum of the top words
+// below 2^53, and those of 32-bit words (rounded, up to 2^31) too.  0 for CSR rows, wider spans
+// and scales near binary64's range.
+static int reduce_words(const Instance &I, int n) {
+    if (I.layout == HQA_CSR || I.es.lsb == INT32_MIN) return 0;
+    if (I.es.msb > 900 || I.es.lsb < -900 || I.N > (1 << 20)) return 0;
+    const int span = I.es.msb + 1 - I.es.lsb;
+    int lg = 1;
+    while (((int64_t)1 << lg) < (int64_t)I.N + n) lg++;
+    for (int w = 1; w <= 3; w++)
+        if (span - 32 * (w - 1) + lg <= 53) return w;
+    return 0;
+}
+
 hipError_t launch_reduce(const Instance &I, int R, int n, const int32_t *amb,
                          const int8_t *spins, double *h_eff, double *J_eff, hipStream_t st) {
     RedArgs a;
     a.N = I.N; a.R = R; a.n = n; a.csr = I.layout == HQA_CSR; a.b0 = I.es.lsb;
+    a.words = reduce_words(I, n);
+    a.scale = a.words ? std::ldexp(1.0, -I.es.lsb) : 0.0;
     a.J = I.J64; a.rp = I.rp; a.ci = I.ci; a.h = I.h64;
     a.amb = amb; a.spins = spins; a.h_eff = h_eff; a.J_eff = J_eff;
     int64_t waves = (int64_t)R * n;
@@ -1597,6 +1698,8 @@ hipError_t launch_readout_batch(const std::vector<ReadoutJob> &jobs, int R, int 
             const Instance &I = *j.I;
             RedArgs a;
             a.N = I.N; a.R = R; a.n = n; a.csr = I.layout == HQA_CSR; a.b0 = I.es.lsb;
+            a.words = reduce_words(I, n);
+            a.scale = a.words ? std::ldexp(1.0, -I.es.lsb) : 0.0;
             a.J = I.J64; a.rp = I.rp; a.ci = I.ci; a.h = I.h64;
             a.amb = j.amb; a.spins = j.spins; a.h_eff = j.h_eff; a.J_eff = j.J_eff;
             red.push_back(a);
