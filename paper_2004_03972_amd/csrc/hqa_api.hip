@@ -1641,7 +1641,7 @@ hqa_status hqa_md_stats_window(hqa_md *md, int64_t k0, int64_t k1, int64_t every
     for (auto &I : md->inst) {
         const size_t n = I.smaj ? (size_t)I.N * I.ld : (size_t)I.Rp * I.ld;
         if (!I.st) {
-            HIPCHK(dalloc(&I.st, 9 * n));
+            HIPCHK(dalloc(&I.st, 9 * n + 2 * (size_t)md->R));   // statistics, feature scales
             HIPCHK(dalloc(&I.n1, (size_t)I.N));
             HIPCHK(dalloc(&I.inv_n2, (size_t)I.N));
             HIPCHK(launch_row_norms(I, I.n1, I.inv_n2, md->stream));

@@ -54,11 +54,31 @@ struct FeatArgs {
     int64_t sst;
     float K, tau, mean_n1;
     const float *phi, *st, *n1;
+    float *scale;         // [R][2], behind the statistics
     float *feat;
 };
 
 __device__ __forceinline__ int64_t fidx(const FeatArgs &a, int r, int i) {
     return a.smaj ? (int64_t)i * a.ld + r : (int64_t)r * a.ld + i;
+}
+
+// The features of one spin and replica (position k of the state).
+__device__ __forceinline__ void feature_row(const FeatArgs &a, int64_t k, int i, float sig, float pmean,
+                                            float *f) {
+    const float *S = a.st + k;
+    const float m0 = S[0] / a.K, m5 = S[5 * a.sst] / a.K;
+    f[0] = m0 / sig;
+    f[1] = sqrtf(fmaxf(S[1 * a.sst] / a.K - m0 * m0, 0.f)) / sig;
+    f[2] = (S[2 * a.sst] / a.K) / sig;
+    f[3] = a.phi[k] / sig;
+    f[4] = fabsf(2.f * S[3 * a.sst] / a.K - 1.f);
+    f[5] = S[4 * a.sst] / a.K;
+    f[6] = m5 / sig;
+    f[7] = sqrtf(fmaxf(S[6 * a.sst] / a.K - m5 * m5, 0.f)) / sig;
+    f[8] = (S[7 * a.sst] / a.K) / sig;
+    f[9] = (S[8 * a.sst] / a.K) / pmean;
+    f[10] = a.mean_n1 > 0.f ? a.n1[i] / a.mean_n1 : 0.f;
+    f[11] = a.tau;
 }
 
 __global__ __launch_bounds__(256) void k_features(FeatArgs a) {
@@ -87,21 +107,58 @@ __global__ __launch_bounds__(256) void k_features(FeatArgs a) {
     if (pmean == 0.f) pmean = 1.f;
     for (int i = tid; i < a.N; i += 256) {
         const int64_t k = fidx(a, r, i);
-        const float *S = a.st + k;
-        const float m0 = S[0] / a.K, m5 = S[5 * a.sst] / a.K;
-        float *f = a.feat + ((int64_t)r * a.N + i) * NF;
-        f[0] = m0 / sig;
-        f[1] = sqrtf(fmaxf(S[1 * a.sst] / a.K - m0 * m0, 0.f)) / sig;
-        f[2] = (S[2 * a.sst] / a.K) / sig;
-        f[3] = a.phi[k] / sig;
-        f[4] = fabsf(2.f * S[3 * a.sst] / a.K - 1.f);
-        f[5] = S[4 * a.sst] / a.K;
-        f[6] = m5 / sig;
-        f[7] = sqrtf(fmaxf(S[6 * a.sst] / a.K - m5 * m5, 0.f)) / sig;
-        f[8] = (S[7 * a.sst] / a.K) / sig;
-        f[9] = (S[8 * a.sst] / a.K) / pmean;
-        f[10] = a.mean_n1 > 0.f ? a.n1[i] / a.mean_n1 : 0.f;
-        f[11] = a.tau;
+        feature_row(a, k, i, sig, pmean, a.feat + ((int64_t)r * a.N + i) * NF);
+    }
+}
+
+// Replica-minor state: four replicas a workgroup, lane group t / 4 = 0 .. 255 taking the spins of
+// thread t / 4 of k_features, so that every sum has the same terms in the same order; the two
+// scales go to a.scale[2 r], [2 r + 1].
+__global__ __launch_bounds__(1024) void k_feature_scales(FeatArgs a) {
+    __shared__ float red[2][256][5];
+    const int q = threadIdx.x & 3, j = threadIdx.x >> 2, r = blockIdx.x * 4 + q;
+    float s2 = 0.f, pm = 0.f;
+    if (r < a.R)
+#pragma unroll 4
+        for (int i = j; i < a.N; i += 256) {
+            const int64_t k = (int64_t)i * a.ld + r;
+            const float x = a.phi[k];
+            s2 += x * x;
+            pm += a.st[8 * a.sst + k] / a.K;
+        }
+    red[0][j][q] = s2;
+    red[1][j][q] = pm;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if (j < s) {
+            red[0][j][q] += red[0][j + s][q];
+            red[1][j][q] += red[1][j + s][q];
+        }
+        __syncthreads();
+    }
+    if (j == 0 && r < a.R) {
+        float sig = sqrtf(red[0][0][q] / (float)a.N), pmean = red[1][0][q] / (float)a.N;
+        a.scale[2 * r] = sig == 0.f ? 1.f : sig;
+        a.scale[2 * r + 1] = pmean == 0.f ? 1.f : pmean;
+    }
+}
+
+// ... and the features of 16 spins x 32 replicas a workgroup, read along the replicas and turned
+// in LDS to rows of 16 spins.  Bound by the ten arrays read and the twelve written; N = 10^4,
+// R = 128: 236 us as one workgroup a replica reading across the lines, 53 both kernels.
+__global__ __launch_bounds__(512) void k_features_turn(FeatArgs a) {
+    __shared__ float t[32][16 * NF + 1];
+    const int tid = threadIdx.x, x = tid & 31, y = tid >> 5;
+    const int i0 = blockIdx.x * 16, r0 = blockIdx.y * 32, i = i0 + y, r = r0 + x;
+    if (i < a.N && r < a.R) {
+        const int64_t k = (int64_t)i * a.ld + r;
+        feature_row(a, k, i, a.scale[2 * r], a.scale[2 * r + 1], &t[x][y * NF]);
+    }
+    __syncthreads();
+    const int cols = min(16, a.N - i0) * NF;
+    for (int e = tid; e < 32 * 16 * NF; e += 512) {
+        const int rr = e / (16 * NF), c = e % (16 * NF);
+        if (c < cols && r0 + rr < a.R) a.feat[((int64_t)(r0 + rr) * a.N + i0) * NF + c] = t[rr][c];
     }
 }
 
@@ -112,6 +169,12 @@ hipError_t launch_features(const Instance &I, int R, int64_t K, float tau, float
     a.sst = I.smaj ? (int64_t)I.N * I.ld : (int64_t)I.Rp * I.ld;
     a.K = (float)K; a.tau = tau; a.mean_n1 = mean_n1;
     a.phi = I.phi32[I.cur]; a.st = I.st; a.n1 = I.n1; a.feat = feat;
+    a.scale = I.st + 9 * a.sst;
+    if (I.smaj && (R + 31) / 32 <= 65535) {
+        k_feature_scales<<<(R + 3) / 4, 1024, 0, st>>>(a);
+        k_features_turn<<<dim3((I.N + 15) / 16, (R + 31) / 32), 512, 0, st>>>(a);
+        return hipGetLastError();
+    }
     k_features<<<R, 256, 0, st>>>(a);
     return hipGetLastError();
 }

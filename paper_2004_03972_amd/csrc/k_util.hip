@@ -336,6 +336,13 @@ __global__ void k_init_state(InitArgs a) {
     int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (int64_t)a.N * a.R) return;
     int r = (int)(t / a.N), i = (int)(t % a.N);
+    // a replica-minor state without given values is written along its lines (N = 4096, R = 1024:
+    // 62 us across them, 16 along)
+    if (a.smaj && !a.f64 && !a.p0 && !a.phi0) {
+        i = (int)(t / a.R);
+        r = (int)(t % a.R);
+        t = (int64_t)r * a.N + i;
+    }
     double p = a.p0 ? a.p0[t] : ((splitmix64_at(a.seed, (uint64_t)t) >> 63) ? -1.0 : 1.0);
     double x = a.phi0 ? a.phi0[t] : 0.0;
     if (a.f64) {
@@ -395,6 +402,25 @@ __global__ void k_export(XArgs a) {
     }
 }
 
+// Export of a replica-minor state: tiles of 32 spins x 32 replicas turned in LDS, so that reads and
+// writes are both whole lines (N = 4096, R = 1024: 19 us read across the lines, 12 now).
+__global__ __launch_bounds__(256) void k_export_turn(XArgs a) {
+    __shared__ float t[32][33];
+    const int i0 = blockIdx.x * 32, x = threadIdx.x & 31, y0 = threadIdx.x >> 5;
+    for (int r0 = blockIdx.y * 32; r0 < a.R; r0 += gridDim.y * 32) {
+        __syncthreads();
+        for (int y = y0; y < 32; y += 8)
+            if (i0 + y < a.N && r0 + x < a.R) t[y][x] = a.x32[(int64_t)(i0 + y) * a.ld + r0 + x];
+        __syncthreads();
+        for (int y = y0; y < 32; y += 8)
+            if (i0 + x < a.N && r0 + y < a.R) {
+                const float v = t[x][y];
+                a.dst[(int64_t)(r0 + y) * a.N + i0 + x] =
+                    a.what == HQA_STATE_PHIBAR ? (double)(v / (float)a.W) : (double)v;
+            }
+    }
+}
+
 hipError_t launch_export(const Instance &I, int R, int prec, int what, double *dst, int import,
                          int W, hipStream_t st) {
     XArgs a;
@@ -409,6 +435,10 @@ hipError_t launch_export(const Instance &I, int R, int prec, int what, double *d
         a.x64 = I.S64; a.x32 = I.S32;
     }
     int64_t n = (int64_t)I.N * R;
+    if (a.smaj && !a.f64 && !import && R > 1) {
+        k_export_turn<<<dim3((I.N + 31) / 32, std::min((R + 31) / 32, 65535)), 256, 0, st>>>(a);
+        return hipGetLastError();
+    }
     k_export<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(a);
     return hipGetLastError();
 }
