@@ -259,8 +259,8 @@ def bench_ea3d(args, hqa, torch):
                            "frac": flop / (ms / 1e3) / 78.6e12,
                            "frac_of_vendor_157": flop / (ms / 1e3) / 157.3e12,
                            "traffic": measured_traffic("k_csr_resident_ea3d_pmc.txt",
-                                                       "csr_resident", "k_csr_resident<4, 6>"),
-                           "kernel": "k_csr_resident<4, 6>", "flop_per_update": flop / upd,
+                                                       "csr_resident", "k_csr_resident<4, 6, 6>"),
+                           "kernel": "k_csr_resident<4, 6, 6>", "flop_per_update": flop / upd,
                            "hbm_equivalent_GBps": bytes_alg / (ms / 1e3) / 1e9}
     else:
         out["roofline"] = {"bound": "hbm", "achieved": bytes_alg / (ms / 1e3) / 1e9,

@@ -5,7 +5,7 @@
 // of a sparse instance needs nothing from any other workgroup.  For a bounded-
 // degree graph (every row at most DMAX couplings; lattices have six) the whole
 // per-step working set stays on chip for the entire anneal:
-//   * the fluxes of the four replicas, double-buffered, in LDS ([N] x float4 each);
+//   * the fluxes of the four replicas, double-buffered, in LDS ([N][2] x float4);
 //   * the field h in LDS;
 //   * each thread's spins' couplings (column, value) in registers, loaded once;
 //   * each thread's momenta and window sums in registers.
@@ -15,6 +15,8 @@
 // arithmetic is the streamed CSR kernel's (field accumulated with fmaf in ascending column order
 // from +0, the shared binary32 leapfrog, the window sum), so both give
 // bit-identical trajectories.
+#include <type_traits>
+
 #include "hqa_internal.h"
 #include "md_epilogue.h"
 
@@ -53,21 +55,29 @@ __device__ __forceinline__ StepCoef csr_res_coef(const CsrResArgs &a, int64_t q)
 }
 
 // SPT spins per thread: spin i = tid + CSR_RES_THREADS k, k < SPT.  MP: the potential
-// exponent when it is 6 (the paper's), else 0 for any even M.
-template <int SPT, int MP>
+// exponent when it is 6 (the paper's), else 0 for any even M.  D: the number of couplings of
+// every row when that is 4 or 6 (periodic square and cubic lattices), else 0.
+//
+// Bound by vector instructions, four wavefronts a SIMD: 24 multiply-adds and 56 operations of the
+// leapfrog a spin and four replicas at D = 6.  So the two flux buffers are interleaved (a
+// buffer is an offset in the instruction, steps go in pairs), couplings keep LDS addresses, the
+// initial half kick is a step of its own, and rows of one length need no masks and no spilled
+// registers.  N = 4096, R = 1024: 3.35 us a step without these, 2.95 with.
+template <int SPT, int MP, int D>
 __global__ __launch_bounds__(CSR_RES_THREADS) void k_csr_resident(CsrResArgs a) {
+    constexpr int DM = D ? D : CSR_RES_DMAX;
     extern __shared__ __align__(16) float lds_c[];
-    float4 *ph0 = (float4 *)lds_c, *ph1 = ph0 + a.N;
-    float *hl = (float *)(ph1 + a.N);
+    float4 *ph = (float4 *)lds_c;                      // [N][2]
+    float *hl = (float *)(ph + 2 * a.N);
     const int tid = threadIdx.x;
     const int g0 = blockIdx.x * CSR_RES_RG;
 
     for (int i = tid; i < a.N; i += CSR_RES_THREADS) {
-        ph0[i] = *(const float4 *)(a.phi_in + (int64_t)i * a.ld + g0);
+        ph[2 * i] = *(const float4 *)(a.phi_in + (int64_t)i * a.ld + g0);
         hl[i] = a.h[i];
     }
-    int deg[SPT], col[SPT][CSR_RES_DMAX];
-    float val[SPT][CSR_RES_DMAX];
+    int deg[SPT], col[SPT][DM];                        // col: byte address of the spin's pair
+    float val[SPT][DM];
     float4 p[SPT], S[SPT];
 #pragma unroll
     for (int k = 0; k < SPT; k++) {
@@ -75,7 +85,7 @@ __global__ __launch_bounds__(CSR_RES_THREADS) void k_csr_resident(CsrResArgs a) 
         deg[k] = 0;
         p[k] = S[k] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int d = 0; d < CSR_RES_DMAX; d++) {
+        for (int d = 0; d < DM; d++) {
             col[k][d] = 0;
             val[k][d] = 0.0f;
         }
@@ -83,9 +93,9 @@ __global__ __launch_bounds__(CSR_RES_THREADS) void k_csr_resident(CsrResArgs a) 
             const int e0 = a.rp[i];
             deg[k] = a.rp[i + 1] - e0;   // the host checked deg <= CSR_RES_DMAX
 #pragma unroll
-            for (int d = 0; d < CSR_RES_DMAX; d++) {
+            for (int d = 0; d < DM; d++) {
                 if (d < deg[k]) {
-                    col[k][d] = a.ci[e0 + d];
+                    col[k][d] = a.ci[e0 + d] * 32;
                     val[k][d] = a.v[e0 + d];
                 }
             }
@@ -96,22 +106,21 @@ __global__ __launch_bounds__(CSR_RES_THREADS) void k_csr_resident(CsrResArgs a) 
     }
     __syncthreads();
 
-    int cur = 0;
-    for (int64_t q = a.q0; q < a.q1; q++) {
-        const StepCoef c = csr_res_coef(a, q);
+    auto step = [&](int64_t q, auto parity, auto first) {
+        constexpr int par = decltype(parity)::value;
+        StepCoef c = csr_res_coef(a, q);
+        if constexpr (!decltype(first)::value) c.kick = 1.0f;
         const bool win = q + 1 >= a.T - a.W + 1;
-        const float4 *X = cur ? ph1 : ph0;
-        float4 *Y = cur ? ph0 : ph1;
 #pragma unroll
         for (int k = 0; k < SPT; k++) {
             const int i = tid + CSR_RES_THREADS * k;
             if (i < a.N) {
                 float4 u = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-                for (int d = 0; d < CSR_RES_DMAX; d++) {
-                    if (d < deg[k]) {
+                for (int d = 0; d < DM; d++) {
+                    if (D || d < deg[k]) {
                         const float w = val[k][d];
-                        const float4 xj = X[col[k][d]];
+                        const float4 xj = *(const float4 *)((const char *)lds_c + col[k][d] + 16 * par);
                         u.x = fmaf(w, xj.x, u.x);
                         u.y = fmaf(w, xj.y, u.y);
                         u.z = fmaf(w, xj.z, u.z);
@@ -119,7 +128,7 @@ __global__ __launch_bounds__(CSR_RES_THREADS) void k_csr_resident(CsrResArgs a) 
                     }
                 }
                 const float hi = hl[i];
-                const float4 x = X[i];
+                const float4 x = ph[2 * i + par];
                 float4 xn;
                 if constexpr (MP == 6) {
                     leapfrog_m<6>(c, x.x, u.x, hi, p[k].x, xn.x);
@@ -132,7 +141,7 @@ __global__ __launch_bounds__(CSR_RES_THREADS) void k_csr_resident(CsrResArgs a) 
                     leapfrog(c, x.z, u.z, hi, p[k].z, xn.z);
                     leapfrog(c, x.w, u.w, hi, p[k].w, xn.w);
                 }
-                Y[i] = xn;
+                ph[2 * i + (par ^ 1)] = xn;
                 if (win) {
                     S[k].x = S[k].x + xn.x; S[k].y = S[k].y + xn.y;
                     S[k].z = S[k].z + xn.z; S[k].w = S[k].w + xn.w;
@@ -140,20 +149,37 @@ __global__ __launch_bounds__(CSR_RES_THREADS) void k_csr_resident(CsrResArgs a) 
             }
         }
         __syncthreads();
-        cur ^= 1;
+    };
+    typedef std::integral_constant<int, 0> P0;
+    typedef std::integral_constant<int, 1> P1;
+    // steps go in pairs from buffer 0; an odd first step (the half kick included) is copied back
+    int64_t q = a.q0;
+    if (q < a.q1 && (q == 0 || ((a.q1 - q) & 1))) {
+        step(q, P0(), std::true_type());
+        for (int i = tid; i < a.N; i += CSR_RES_THREADS) ph[2 * i] = ph[2 * i + 1];
+        __syncthreads();
+        q++;
+    }
+    for (; q + 2 <= a.q1; q += 2) {
+        step(q, P0(), std::false_type());
+        step(q + 1, P1(), std::false_type());
+    }
+    int cur = 0;
+    if (q < a.q1) {
+        step(q, P0(), std::false_type());
+        cur = 1;
     }
 
     // A non-finite flux or momentum never becomes finite again under the leapfrog (and
     // spreads to the neighbours through the field), so checking the final state raises
     // the same flag as checking every step.
-    const float4 *X = cur ? ph1 : ph0;
     bool bad = false;
 #pragma unroll
     for (int k = 0; k < SPT; k++) {
         const int i = tid + CSR_RES_THREADS * k;
         if (i < a.N) {
             const int64_t base = (int64_t)i * a.ld + g0;
-            const float4 xf = X[i];
+            const float4 xf = ph[2 * i + cur];
             bad |= !isfinite(xf.x) || !isfinite(xf.y) || !isfinite(xf.z) || !isfinite(xf.w) ||
                    !isfinite(p[k].x) || !isfinite(p[k].y) || !isfinite(p[k].z) ||
                    !isfinite(p[k].w);
@@ -172,18 +198,21 @@ bool csr_resident_fits(hqa_md *md, Instance &I) {
     return I.max_deg >= 0 && I.max_deg <= CSR_RES_DMAX;   // max_deg: set at ingest
 }
 
-template <int SPT, int MP>
+template <int SPT, int MP, int D>
 static hipError_t launch_crm(const CsrResArgs &a, int grid, size_t lds, hipStream_t st) {
-    hipError_t e = hipFuncSetAttribute((const void *)k_csr_resident<SPT, MP>,
+    hipError_t e = hipFuncSetAttribute((const void *)k_csr_resident<SPT, MP, D>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    k_csr_resident<SPT, MP><<<grid, CSR_RES_THREADS, lds, st>>>(a);
+    k_csr_resident<SPT, MP, D><<<grid, CSR_RES_THREADS, lds, st>>>(a);
     return hipGetLastError();
 }
 
+// deg: the length of every row, or 0.
 template <int SPT>
-static hipError_t launch_cr(const CsrResArgs &a, int grid, size_t lds, hipStream_t st) {
-    return a.M == 6 ? launch_crm<SPT, 6>(a, grid, lds, st) : launch_crm<SPT, 0>(a, grid, lds, st);
+static hipError_t launch_cr(const CsrResArgs &a, int deg, int grid, size_t lds, hipStream_t st) {
+    if (a.M == 6 && deg == 4) return launch_crm<SPT, 6, 4>(a, grid, lds, st);
+    if (a.M == 6 && deg == 6) return launch_crm<SPT, 6, 6>(a, grid, lds, st);
+    return a.M == 6 ? launch_crm<SPT, 6, 0>(a, grid, lds, st) : launch_crm<SPT, 0, 0>(a, grid, lds, st);
 }
 
 hipError_t launch_md_csr_resident(hqa_md *md, Instance &I, int64_t q0, int64_t q1) {
@@ -196,10 +225,12 @@ hipError_t launch_md_csr_resident(hqa_md *md, Instance &I, int64_t q0, int64_t q
     const size_t lds = csr_resident_lds_bytes(I.N);
     const int grid = I.Rp / CSR_RES_RG;
     const int spt = (I.N + CSR_RES_THREADS - 1) / CSR_RES_THREADS;
+    // nnz = N max_deg: every row has max_deg couplings
+    const int deg = I.nnz == (int64_t)I.N * I.max_deg ? I.max_deg : 0;
     hipError_t e;
-    if (spt <= 1) e = launch_cr<1>(a, grid, lds, md->stream);
-    else if (spt <= 2) e = launch_cr<2>(a, grid, lds, md->stream);
-    else e = launch_cr<4>(a, grid, lds, md->stream);
+    if (spt <= 1) e = launch_cr<1>(a, deg, grid, lds, md->stream);
+    else if (spt <= 2) e = launch_cr<2>(a, deg, grid, lds, md->stream);
+    else e = launch_cr<4>(a, deg, grid, lds, md->stream);
     if (e == hipSuccess) I.cur ^= 1;
     return e;
 }
