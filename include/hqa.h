@@ -180,7 +180,7 @@ typedef struct hqa_md_opts {
  *                      their whole state in LDS and streams J from L2 (BF16/FP8 J,
  *                      N up to 800 on a device with 160 KB of LDS per workgroup).
  *   HQA_PLAN_BATCH     one launch per MD step over tiles of 128 rows x 64 replicas
- *                      with the flux operand staged in LDS: AUTO's plan for several
+ *                      (32 or 16 in small batches) with the flux operand staged in LDS: AUTO's plan for several
  *                      dense instances; selectable for a handle whose only dense
  *                      instance has BF16 or FP8 storage (row blocks of a large
  *                      instance spread over all XCDs).
