@@ -1867,6 +1867,11 @@ hqa_status hqa_md_run_es(hqa_md *md, int32_t instance, hqa_es *es, int64_t K, in
     const Instance &I = md->inst[instance];
     const int64_t n = (int64_t)md->R * I.N;
     DevBufs B(md->keep);
+    // the classifier's stream uses B too: drained before B goes, whichever way the call ends
+    struct Drain {
+        hipStream_t st;
+        ~Drain() { (void)hipStreamSynchronize(st); }
+    } drain{es->stream};
     float *feat, *pd;
     HIPCHK(B.get(&feat, (size_t)n * HQA_ES_NFEAT));
     HIPCHK(B.get(&pd, (size_t)n * 3));
