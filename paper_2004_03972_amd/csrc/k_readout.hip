@@ -430,15 +430,17 @@ __device__ __forceinline__ void gray_walk(const T *J, const T *h, int n, int nl,
 //   k_enum_real_mid: per replica, the minimum over the workgroups and the rescoring
 //     threshold E_min + 2 delta + 4 u S (the bound of k_enumerate);
 //   k_enum_real<NL, 2>: workgroups whose minimum is at or below the threshold walk again and
-//     rescore every such code exactly (fixed-point accumulator, rounded once); each
-//     workgroup's exact minimum -> part;
+//     collect every such code, which a wavefront each then rescores exactly (fixed-point
+//     accumulator, rounded once); each workgroup's exact minimum -> part;
 //   k_enum_real_mid: per replica, the exact minimum over the workgroups, ties to the
 //     smallest code.
 // Bound by binary64 additions in pass 1 (three a code), the exact sums in pass 2.  n = 20,
 // 64 replicas of 12 instances: 836 us a pass with the code kept beside each minimum and both
-// walks in full; now 270 us for pass 1 (456 with every field updated per code), 255 for pass 2.
+// walks in full; now 270 us for pass 1 (456 with every field updated per code), 65 for pass 2
+// (255 with each candidate's terms added by the thread that found it).
 // ---------------------------------------------------------------------------
 #define ENUM_PT_REAL 12
+#define ENUM_CAND 256    // candidates a workgroup rescores together; further ones by their thread
 
 struct EnumRealArgs {
     int n, R, P, b0;
@@ -455,6 +457,8 @@ __device__ __forceinline__ void enum_real_body(const EnumRealArgs &a, const int 
     __shared__ double Jd[ENUM_MAXN * ENUM_MAXN], J4[ENUM_MAXN * ENUM_MAXN], hd[ENUM_MAXN];
     __shared__ double sE[256];
     __shared__ int64_t sC[PASS == 2 ? 256 : 1];
+    __shared__ uint32_t cand[PASS == 2 ? ENUM_CAND : 1];   // codes to rescore
+    __shared__ int ncand;
     const int r = bx_ / a.P, p = bx_ % a.P, tid = threadIdx.x, n = a.n;
     const double thr = PASS == 2 ? a.thresh[r] : 0.0;
     // pass 2 walks the same binary64 energies: without one at or below the threshold in pass 1
@@ -473,6 +477,7 @@ __device__ __forceinline__ void enum_real_body(const EnumRealArgs &a, const int 
         J4[k / n * ENUM_MAXN + k % n] = 4.0 * v;
     }
     for (int k = tid; k < n; k += 256) hd[k] = a.h_eff[(int64_t)r * n + k];
+    if (PASS == 2 && tid == 0) ncand = 0;
     __syncthreads();
     const uint32_t top = (uint32_t)(p * 256 + tid);
     const bool active = top < (1u << (n - NL));
@@ -526,6 +531,11 @@ __device__ __forceinline__ void enum_real_body(const EnumRealArgs &a, const int 
                     for (int k = 1; k < NC; k++) uc = k == c ? u[k] : uc;
                     if (E + uc <= thr) {
                         const uint32_t full = code | up | (uint32_t)c;
+                        const int slot = atomicAdd(&ncand, 1);
+                        if (slot < ENUM_CAND) {
+                            cand[slot] = full;
+                            continue;
+                        }
                         const double ex = energy_exact(Jd, hd, n, full, a.b0);
                         if (better_d(ex, full, bestE, bestC)) { bestE = ex; bestC = full; }
                     }
@@ -569,6 +579,24 @@ __device__ __forceinline__ void enum_real_body(const EnumRealArgs &a, const int 
             }
         } else {
             block();
+        }
+    }
+    if constexpr (PASS == 2) {
+        // a wavefront a candidate, its terms over the lanes (exact sums have no order)
+        __syncthreads();
+        const int lane = tid & 63, total = min(ncand, ENUM_CAND);
+        for (int k = tid >> 6; k < total; k += 4) {
+            const uint32_t c = cand[k];
+            Acc256 acc;
+            acc_zero(acc);
+            for (int t = lane; t < n * n; t += 64) {
+                const int x = t / n, y = t % n;
+                const double sx = ((c >> x) & 1) ? -1.0 : 1.0, sy = ((c >> y) & 1) ? -1.0 : 1.0;
+                if (y >= x) acc_add(acc, y > x ? Jd[t] * (sx * sy) : hd[x] * sx, a.b0);
+            }
+            acc_wave_allreduce(acc);
+            const double ex = acc_round(acc, a.b0);
+            if (lane == 0 && better_d(ex, c, bestE, bestC)) { bestE = ex; bestC = c; }
         }
     }
     sE[tid] = bestE;

@@ -42,3 +42,15 @@ def test_scales(H, n, e):
     else:
         J, h = J * 2.0 ** e, h * 2.0 ** e
     _solve_real(H, J, n, 2, seed=n, h=h)
+
+
+@pytest.mark.parametrize("n", [8, 13, 16])
+def test_many_candidates(H, n):
+    """Couplings so small that nearly every code is within the rescoring bound of the others:
+    more candidates than a workgroup rescores together."""
+    J = np.zeros((30, 30))
+    h = np.zeros(30)
+    h[0] = 0.5                                           # a fraction keeps the instance real
+    J[0, 1] = J[1, 0] = 2.0 ** -60
+    J[2, 3] = J[3, 2] = -(2.0 ** -61)
+    _solve_real(H, J, n, 3, seed=n, h=h)
