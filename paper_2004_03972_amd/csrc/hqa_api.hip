@@ -1890,9 +1890,12 @@ hqa_status hqa_md_run_es(hqa_md *md, int32_t instance, hqa_es *es, int64_t K, in
         if ((s = hqa_es_confidence(es, pd, n, HQA_DEVICE, &conf)) != HQA_OK) return s;
         if (conf >= threshold || q >= T) break;
     }
-    if (prob)
-        HIPCHK(hipMemcpy(prob, pd, sizeof(float) * n * 3,
-                         prob_mem == HQA_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice));
+    if (prob) {
+        // on the classifier's stream, which wrote pd, and waited for: a copy within the device on
+        // the null stream may still be running when it returns, and pd's memory is used again
+        HIPCHK(hipMemcpyAsync(prob, pd, sizeof(float) * n * 3, kind_out(prob_mem), es->stream));
+        HIPCHK(hipStreamSynchronize(es->stream));
+    }
     if (stop_step) *stop_step = q;
     if (confidence) *confidence = conf;
     return HQA_OK;
