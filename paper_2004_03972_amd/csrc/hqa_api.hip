@@ -48,9 +48,11 @@ static hqa_status fail(hqa_status st, const char *fmt, ...) {
 #define HIPCHK(expr)                                                                   \
     do {                                                                               \
         hipError_t e_ = (expr);                                                        \
-        if (e_ != hipSuccess)                                                          \
+        if (e_ != hipSuccess) {                                                        \
+            (void)hipGetLastError(); /* reported here, not by the next launch's check */ \
             return fail(e_ == hipErrorOutOfMemory ? HQA_ENOMEM : HQA_EDEVICE, "%s: %s", \
                         #expr, hipGetErrorString(e_));                                 \
+        }                                                                              \
     } while (0)
 
 namespace hqa {
@@ -165,17 +167,23 @@ static hqa_status check_problem(const hqa_problem &P, int k) {
     return HQA_OK;
 }
 
-// Whether kernels may read this device array where it lies: memory of the current device, its
-// values aligned.
-static bool readable_in_place(const double *p) {
+// Whether kernels may read these bytes of device memory where they lie: memory of the current
+// device, its values aligned, all of it in the allocation that p points into (a shorter one goes
+// to the copy, which refuses it).
+static bool readable_in_place(const double *p, size_t bytes) {
     hipPointerAttribute_t a;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
     int dev = 0;
     if ((uintptr_t)p % sizeof(double)) return false;
-    if (hipPointerGetAttributes(&a, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+    if (hipPointerGetAttributes(&a, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
+        a.type != hipMemoryTypeDevice || a.device != dev ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return a.type == hipMemoryTypeDevice && a.device == dev;
+    const size_t at = (size_t)((const uint8_t *)p - (const uint8_t *)base);
+    return at <= size && bytes <= size - at;
 }
 
 // Upload binary64 couplings and field, validate on the device, gather exponent
@@ -189,7 +197,7 @@ static hqa_status ingest(const hqa_problem &P, int k, hipStream_t st, int32_t *d
     const int N = P.n;
     if (P.layout == HQA_DENSE) {
         I.nnz = (int64_t)N * N;
-        if (in_place && P.mem == HQA_DEVICE && readable_in_place(P.j)) {
+        if (in_place && P.mem == HQA_DEVICE && readable_in_place(P.j, sizeof(double) * N * N)) {
             I.J64 = const_cast<double *>(P.j);
             I.j_borrowed = true;
         } else {
