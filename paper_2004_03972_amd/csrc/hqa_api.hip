@@ -1692,8 +1692,8 @@ hqa_status hqa_md_features(hqa_md *md, int32_t instance, float *feat, int32_t ds
 struct hqa_es {
     hipStream_t stream = nullptr;
     float *P = nullptr, *m = nullptr, *v = nullptr, *g = nullptr, *acc = nullptr;
-    float *part = nullptr;            // the gradient kernel's partial sums
-    size_t part_bytes = 0;
+    float *part = nullptr;            // the gradient kernel's partial sums, for any batch: a training
+                                      // step allocates nothing, and a captured one names this buffer
     void *keep = nullptr;             // copies of host arguments, kept between calls
     int64_t t = 0;
 };
@@ -1718,6 +1718,7 @@ hqa_status hqa_es_create(uint64_t seed, void *hip_stream, hqa_es **out) {
     if (e == hipSuccess) e = dalloc(&es->v, HQA_ES_NPARAM);
     if (e == hipSuccess) e = dalloc(&es->g, HQA_ES_NPARAM);
     if (e == hipSuccess) e = dalloc(&es->acc, 4);
+    if (e == hipSuccess) e = dev_malloc((void **)&es->part, mlp_grad_scratch_bytes());
     if (e == hipSuccess) e = hipMemsetAsync(es->m, 0, sizeof(float) * HQA_ES_NPARAM, es->stream);
     if (e == hipSuccess) e = hipMemsetAsync(es->v, 0, sizeof(float) * HQA_ES_NPARAM, es->stream);
     if (e == hipSuccess) e = launch_mlp_init(es->P, seed, es->stream);
@@ -1770,19 +1771,6 @@ static hqa_status es_inputs(hqa_es *es, DevBufs &B, const float *x, const int32_
     return HQA_OK;
 }
 
-// The gradient scratch for n samples, kept with the classifier.
-static hqa_status es_part(hqa_es *es, int64_t n) {
-    const size_t need = mlp_grad_scratch_bytes(n);
-    if (need <= es->part_bytes) return HQA_OK;
-    HIPCHK(hipStreamSynchronize(es->stream));
-    dfree(es->part);
-    es->part = nullptr;
-    es->part_bytes = 0;
-    HIPCHK(dev_malloc((void **)&es->part, need));
-    es->part_bytes = need;
-    return HQA_OK;
-}
-
 hqa_status hqa_es_grad(hqa_es *es, const float *x, const int32_t *y, int64_t n, const float *cw,
                        float *grad, float *loss, int32_t mem) {
     if (!es || !x || !y || !cw || n < 1) return fail(HQA_EINVAL, "bad arguments");
@@ -1791,7 +1779,6 @@ hqa_status hqa_es_grad(hqa_es *es, const float *x, const int32_t *y, int64_t n, 
     const int32_t *dy;
     hqa_status s = es_inputs(es, B, x, y, cw, n, mem, &dx, &dy, &dcw);
     if (s != HQA_OK) return s;
-    if ((s = es_part(es, n)) != HQA_OK) return s;
     HIPCHK(launch_mlp_grad(es->P, n, dx, dy, dcw, es->g, es->acc, es->part, es->m, es->v, 0, 0.f,
                            es->stream));
     if (grad) HIPCHK(hipMemcpyAsync(grad, es->g, sizeof(float) * HQA_ES_NPARAM, kind_out(mem), es->stream));
@@ -1808,7 +1795,6 @@ hqa_status hqa_es_train_step(hqa_es *es, const float *x, const int32_t *y, int64
     const int32_t *dy;
     hqa_status s = es_inputs(es, B, x, y, cw, n, mem, &dx, &dy, &dcw);
     if (s != HQA_OK) return s;
-    if ((s = es_part(es, n)) != HQA_OK) return s;
     HIPCHK(launch_mlp_grad(es->P, n, dx, dy, dcw, es->g, es->acc, es->part, es->m, es->v, es->t + 1, lr,
                            es->stream));
     es->t += 1;

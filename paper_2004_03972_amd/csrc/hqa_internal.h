@@ -223,7 +223,7 @@ hipError_t launch_features(const Instance &I, int R, int64_t K, float tau, float
 hipError_t launch_mlp_init(float *P, uint64_t seed, hipStream_t st);
 hipError_t launch_mlp_predict(const float *P, int64_t B, const float *x, float *prob, int bf,
                               hipStream_t st);
-size_t mlp_grad_scratch_bytes(int64_t B);
+size_t mlp_grad_scratch_bytes();
 hipError_t launch_mlp_grad(float *P, int64_t B, const float *x, const int32_t *y, const float *cw,
                            float *grad, float *acc, float *part, float *m, float *v, int64_t t,
                            float lr, hipStream_t st);

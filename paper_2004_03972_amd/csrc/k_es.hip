@@ -648,12 +648,15 @@ __global__ __launch_bounds__(256) void k_grad_reduce(const float *part, int nb, 
     }
 }
 
+constexpr int GRAD_BLOCKS = 512;   // two workgroups per CU
+
 static int grad_blocks(int64_t B) {
     const int64_t tiles = (B + MLP_TILE - 1) / MLP_TILE;
-    return (int)std::min<int64_t>((tiles + 3) / 4, 512);   // two workgroups per CU
+    return (int)std::min<int64_t>((tiles + 3) / 4, GRAD_BLOCKS);
 }
 
-size_t mlp_grad_scratch_bytes(int64_t B) { return (size_t)grad_blocks(B) * GP * sizeof(float); }
+// Bytes of `part`, enough for any batch (13.6 MB).
+size_t mlp_grad_scratch_bytes() { return (size_t)GRAD_BLOCKS * GP * sizeof(float); }
 
 // Gradient and loss of B >= 1 samples into grad and acc[2]; with lr > 0, Adam step t.
 hipError_t launch_mlp_grad(float *P, int64_t B, const float *x, const int32_t *y, const float *cw,
