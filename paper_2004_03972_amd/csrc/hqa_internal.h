@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/hqa.h"
+#include "energy_plan.h"
 
 namespace hqa {
 
@@ -187,10 +188,6 @@ hipError_t launch_merge(int N, int R, int n, const int32_t *amb, const int64_t *
 hipError_t dev_malloc(void **p, size_t bytes, size_t roomy = 0, size_t *got = nullptr);
 void fault_alloc_arm();
 
-// Exact energies and cuts of V spin vectors; `part` holds energy_part_bytes(N, V)
-// bytes of device scratch for the per-slice partial sums.
-int energy_slices(int N, int V);
-size_t energy_part_bytes(int N, int V);
 // One instance's part of a batched read-out: its buffers in device scratch.
 struct ReadoutJob {
     const Instance *I;

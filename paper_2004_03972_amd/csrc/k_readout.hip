@@ -13,6 +13,8 @@
 
 namespace hqa {
 
+static_assert(sizeof(Acc256) == ACC_BYTES, "the scratch of the energies is sized by it");
+
 // Position of spin i of replica r in the state arrays.
 __device__ __forceinline__ int64_t sidx(int smaj, int ld, int r, int i) {
     return smaj ? (int64_t)i * ld + r : (int64_t)r * ld + i;
@@ -1557,65 +1559,21 @@ __global__ __launch_bounds__(256) void k_energy_mv_merge_many(const EnMvArgs *as
     energy_mv_merge_body<D>(a, blockIdx.x);
 }
 
-int energy_slices(int N, int V) {
-    if (V <= 0) return 1;
-    const int want = (512 + V - 1) / V;          // at least 512 workgroups in all
-    const int most = (N + 63) / 64;              // at least 64 rows per slice
-    return std::max(1, std::min(want, most));
-}
-
-// Digit counts the many-vector kernel is built for.
-static const int MV_DIGITS[] = {1, 2, 4, 7, 8, 10, 12, 16, 20};
-constexpr int MV_NDIGITS = 9;
-
-// Vectors of a wavefront: up to 64 while the 4 D accumulators per 16 of them fit the registers.
-static int energy_mv_vec(int V, int D) { return V <= 16 || D > 12 ? 16 : D > 8 ? 32 : 64; }
-
-// Doubles' worth of partial sums: part of the fixed-scratch read-out's limit, so it does not
-// follow the launch; energy_mv_slices keeps within it.
-static size_t energy_mv_room(int N, int V) {
-    size_t m = 0;
-    for (int L = 1; L <= 4; L++) {
-        const int G = L == 1 ? 64 : L == 2 ? 32 : 16, groups = (V + G - 1) / G;
-        const size_t P = std::max(1, std::min((1024 + groups - 1) / groups, (N + 15) / 16));
-        m = std::max(m, 2 * P * L * (V + 1));
-    }
-    return m;
-}
-
-// Slices: one or two workgroups per CU over the vector blocks (64-vector blocks fill the
-// registers of one), each slice at least a block row, within the room for partial sums.
-static int energy_mv_slices(int N, int V, int D) {
-    const int vec = energy_mv_vec(V, D), blocks = (V + vec - 1) / vec;
-    const int want = ((D > 2 ? 256 : 512) + blocks - 1) / blocks;
-    const int most = std::min((N + 15) / 16, (int)(energy_mv_room(N, V) / ((size_t)D * (V + 1))));
-    return std::max(1, std::min(want, most));
-}
-
-size_t energy_part_bytes(int N, int V) {
-    V = std::max(V, 1);
-    const size_t old = (size_t)V * energy_slices(N, V) * 2 * sizeof(Acc256);
-    const size_t mv = (size_t)((V + 63) / 64) * N * 8 + energy_mv_room(N, V) * 8 + 256;
-    return std::max(old, mv);
-}
-
-// Digits of the many-vector kernel for instance I (0: it does not apply): the smallest count
-// it is built for with 8 D - 2 >= span.  The partial sums have to fit their room even in one
-// slice, and every digit total has to stay a normal binary64 number.
-static int energy_digits(const Instance &I, int V) {
+// Digits of the many-vector kernel for instance I (0: it does not apply): the smallest count it
+// is built for with 8 D - 2 >= span; every digit total has to stay a normal binary64 number.
+static int energy_digits(const Instance &I) {
     if (I.layout != HQA_DENSE || I.es.lsb == INT32_MIN) return 0;
     const int span = I.es.msb + 1 - I.es.lsb;
     if (I.es.msb > 900 || I.es.lsb < -900 || I.N > (1 << 20)) return 0;
     for (int k = 0; k < MV_NDIGITS; k++)
-        if (8 * MV_DIGITS[k] - 2 >= span)
-            return (size_t)MV_DIGITS[k] * (V + 1) <= energy_mv_room(I.N, V) ? MV_DIGITS[k] : 0;
+        if (8 * MV_DIGITS[k] - 2 >= span) return MV_DIGITS[k];
     return 0;
 }
 
-static EnMvArgs energy_mv_args(const Instance &I, int V, int D, const int8_t *spins, double *E,
+static EnMvArgs energy_mv_args(const Instance &I, int V, int P, const int8_t *spins, double *E,
                                double *cut, void *part) {
     EnMvArgs m;
-    m.N = I.N; m.V = V; m.b0 = I.es.lsb; m.P = energy_mv_slices(I.N, V, D);
+    m.N = I.N; m.V = V; m.b0 = I.es.lsb; m.P = P;
     m.J = I.J64; m.h = I.h64; m.spins = spins; m.E = E; m.cut = cut;
     // the compact storage copy when it holds every coupling exactly
     m.jt = -1; m.ldj = 0; m.Js = nullptr;
@@ -1640,13 +1598,17 @@ static void energy_mv_dispatch(int vec, int D, F f) {
 hipError_t launch_energy(const Instance &I, int V, const int8_t *spins, double *E, double *cut,
                          void *part, hipStream_t st) {
     if (V == 0) return hipSuccess;
-    if (const int D = energy_digits(I, V)) {
-        const EnMvArgs m = energy_mv_args(I, V, D, spins, E, cut, part);
-        const int vec = energy_mv_vec(V, D);
-        energy_mv_dispatch(vec, D, [&](auto vv, auto dd) {
-            k_energy_mv<vv.value, dd.value><<<dim3(m.P, (V + vec - 1) / vec), 256, 0, st>>>(m);
-            k_energy_mv_merge<dd.value><<<(V + 3) / 4, 256, 0, st>>>(m);
-        });
+    if (const int D = energy_digits(I)) {
+        const EnergyPlan pl = energy_plan(I.N, V, D);
+        for (int v0 = 0; v0 < V; v0 += pl.piece) {
+            const int n = std::min(pl.piece, V - v0);
+            const EnMvArgs m = energy_mv_args(I, n, pl.P, spins + (int64_t)v0 * I.N, E ? E + v0 : nullptr,
+                                              cut ? cut + v0 : nullptr, part);
+            energy_mv_dispatch(pl.vec, D, [&](auto vv, auto dd) {
+                k_energy_mv<vv.value, dd.value><<<dim3(m.P, (n + pl.vec - 1) / pl.vec), 256, 0, st>>>(m);
+                k_energy_mv_merge<dd.value><<<(n + 3) / 4, 256, 0, st>>>(m);
+            });
+        }
         return hipGetLastError();
     }
     EnArgs a;
@@ -1765,13 +1727,14 @@ hipError_t launch_readout_batch(const std::vector<ReadoutJob> &jobs, int R, int 
     std::vector<int> fallback;
     for (int c = 0; c < count; c++) {
         const ReadoutJob &j = jobs[c];
-        const int D = energy_digits(*j.I, R);
-        if (!D) {
+        const int D = energy_digits(*j.I);
+        const EnergyPlan pl = D ? energy_plan(j.I->N, R, D) : EnergyPlan{0, 0, 0};
+        if (!D || pl.piece < R) {
             fallback.push_back(c);
             continue;
         }
         const int x = (int)(std::find(MV_DIGITS, MV_DIGITS + MV_NDIGITS, D) - MV_DIGITS);
-        mv[x].push_back(energy_mv_args(*j.I, R, D, j.spins, j.E, j.C, j.part));
+        mv[x].push_back(energy_mv_args(*j.I, R, pl.P, j.spins, j.E, j.C, j.part));
         nmv[x].push_back(mv[x].back().P);
         nmm[x].push_back((R + 3) / 4);
     }
