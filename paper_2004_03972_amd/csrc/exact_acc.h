@@ -77,10 +77,12 @@ __device__ __forceinline__ void acc_merge(Acc256 &a, const Acc256 &b) {
     add256(a.n, b.n);
 }
 
-// Wavefront-wide merge by butterfly shuffles; every lane ends with the total.
+// Merge over groups of LANES consecutive lanes (a power of two) by butterfly shuffles; every lane
+// ends with its group's total.
+template <int LANES = 64>
 __device__ __forceinline__ void acc_wave_allreduce(Acc256 &a) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
+    for (int off = LANES / 2; off >= 1; off >>= 1) {
         Acc256 b;
 #pragma unroll
         for (int k = 0; k < 4; k++) {
