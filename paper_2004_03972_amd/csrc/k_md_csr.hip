@@ -90,10 +90,10 @@ __global__ __launch_bounds__(256) void k_step_csr(CsrArgs a, int64_t q, uint32_t
         x = *(const fv *)(a.phi_in + base);
         p = *(const fv *)(a.p + base);
     }
-    const int e1 = rp[i + 1];
+    const int e1 = rp[i + 1];   // up to 2^31 - 1: e is compared by its distance from it
     int e = rp[i];
     if constexpr (VEC <= 2) {   // four a lane: eight gathers are already 8 KB in flight
-        for (; e + 16 <= e1; e += 16) {
+        for (; e1 - e >= 16; e += 16) {
             const i32x8 ja = *(cint8 *)(ci + e), jb = *(cint8 *)(ci + e + 8);
             const f32x8 wa = *(cfloat8 *)(wv + e), wb = *(cfloat8 *)(wv + e + 8);
             fv g[16];
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256) void k_step_csr(CsrArgs a, int64_t q, uint32_t
                 for (int v = 0; v < VEC; v++) u[v] = fmaf(k < 8 ? wa[k & 7] : wb[k & 7], g[k][v], u[v]);
         }
     }
-    for (; e + 8 <= e1; e += 8) {
+    for (; e1 - e >= 8; e += 8) {
         const i32x8 j = *(cint8 *)(ci + e);
         const f32x8 w = *(cfloat8 *)(wv + e);
         fv g[8];
@@ -118,13 +118,14 @@ __global__ __launch_bounds__(256) void k_step_csr(CsrArgs a, int64_t q, uint32_t
 #pragma unroll
             for (int v = 0; v < VEC; v++) u[v] = fmaf(w[k], g[k][v], u[v]);
     }
-    if (e < e1) {
+    const int left = e1 - e;
+    if (left > 0) {
         fv g[8];
 #pragma unroll
-        for (int k = 0; k < 8; k++) g[k] = *(const fv *)(X + ((O)ci[min(e + k, e1 - 1)] * pitch + off));
+        for (int k = 0; k < 8; k++) g[k] = *(const fv *)(X + ((O)ci[e + min(k, left - 1)] * pitch + off));
 #pragma unroll
         for (int k = 0; k < 8; k++)
-            if (e + k < e1) {
+            if (k < left) {
 #pragma unroll
                 for (int v = 0; v < VEC; v++) u[v] = fmaf(wv[e + k], g[k][v], u[v]);
             }
