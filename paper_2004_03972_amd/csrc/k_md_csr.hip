@@ -5,6 +5,7 @@
 // of 4): row i holds spin i of every replica, so a neighbour's fluxes are one
 // contiguous run.  Per spin update the kernel moves 16 bytes of state (read phi,
 // read and write p, write phi') and gathers 4 bytes per coupling.
+#include "csr_plan.h"
 #include "hqa_internal.h"
 #include "md_epilogue.h"
 
@@ -28,6 +29,47 @@ struct CsrArgs {
     const float *inv_n2;   // 1 / ||J_i||_2
 };
 
+template <int VEC>
+using csr_vec = float __attribute__((ext_vector_type(VEC)));
+
+// The update of VEC consecutive replicas of row i (at `base` in the state) with field u.
+template <int VEC, bool FIELD_ONLY>
+__device__ __forceinline__ void csr_update(const CsrArgs &a, int64_t q, int i, int64_t base,
+                                           const csr_vec<VEC> &u, const csr_vec<VEC> &x, csr_vec<VEC> p) {
+    typedef csr_vec<VEC> fv;
+    if constexpr (FIELD_ONLY) {
+        *(fv *)(a.u_out + base) = u;
+        return;
+    } else {
+        const StepCoef cf = step_coef(a.a32, a.b32, q, a.rg, a.M);
+        const float hi = a.h[i];
+        fv xn;
+        bool bad = false;
+#pragma unroll
+        for (int v = 0; v < VEC; v++) {
+            float pv = p[v], nv;
+            leapfrog(cf, x[v], u[v], hi, pv, nv);
+            p[v] = pv;
+            xn[v] = nv;
+            bad |= !isfinite(nv) || !isfinite(pv);
+        }
+        if (a.st) {
+            const float in2 = a.inv_n2[i];
+#pragma unroll
+            for (int v = 0; v < VEC; v++) es_accumulate(a.st, a.sst, base + v, x[v], xn[v], u[v], p[v], in2);
+        }
+        *(fv *)(a.phi_out + base) = xn;
+        *(fv *)(a.p + base) = p;
+        if (q + 1 >= a.T - a.W + 1) {
+            fv s = *(const fv *)(a.S + base);
+#pragma unroll
+            for (int v = 0; v < VEC; v++) s[v] = s[v] + xn[v];
+            *(fv *)(a.S + base) = s;
+        }
+        if (bad) atomicOr(a.err, ERR_NONFINITE);
+    }
+}
+
 // One wavefront per (row, chunk of 64 VEC replicas), VEC consecutive replicas a lane; the
 // row's couplings are walked in ascending column order.
 //
@@ -49,7 +91,7 @@ struct CsrArgs {
 // G(2000, 12) R = 128: 10.6 -> 4.6; the 16^3 lattice R = 128, 1024: 5.3, 16.9 -> 5.0, 16.7.
 template <int VEC, bool FIELD_ONLY, typename O>
 __global__ __launch_bounds__(256) void k_step_csr(CsrArgs a, int64_t q, uint32_t nchunk, int sliced) {
-    typedef float fv __attribute__((ext_vector_type(VEC)));
+    typedef csr_vec<VEC> fv;
     typedef int32_t i32x8 __attribute__((ext_vector_type(8), aligned(4)));
     typedef float f32x8 __attribute__((ext_vector_type(8), aligned(4)));
     // read-only for the whole launch and uniform: scalar loads
@@ -85,7 +127,7 @@ __global__ __launch_bounds__(256) void k_step_csr(CsrArgs a, int64_t q, uint32_t
     const O pitch = 4 * (O)Rp, off = 4 * (O)c;
     const char *X = (const char *)a.phi_in;
     const int64_t base = (int64_t)i * Rp + c;
-    fv u = 0.f, x, p;
+    fv u = 0.f, x = 0.f, p = 0.f;
     if constexpr (!FIELD_ONLY) {
         x = *(const fv *)(a.phi_in + base);
         p = *(const fv *)(a.p + base);
@@ -130,37 +172,64 @@ __global__ __launch_bounds__(256) void k_step_csr(CsrArgs a, int64_t q, uint32_t
                 for (int v = 0; v < VEC; v++) u[v] = fmaf(wv[e + k], g[k][v], u[v]);
             }
     }
-    if constexpr (FIELD_ONLY) {
-        *(fv *)(a.u_out + base) = u;
-        return;
-    } else {
-        const StepCoef cf = step_coef(a.a32, a.b32, q, a.rg, a.M);
-        const float hi = a.h[i];
-        fv xn;
-        bool bad = false;
-#pragma unroll
-        for (int v = 0; v < VEC; v++) {
-            float pv = p[v], nv;
-            leapfrog(cf, x[v], u[v], hi, pv, nv);
-            p[v] = pv;
-            xn[v] = nv;
-            bad |= !isfinite(nv) || !isfinite(pv);
-        }
-        if (a.st) {
-            const float in2 = a.inv_n2[i];
-#pragma unroll
-            for (int v = 0; v < VEC; v++) es_accumulate(a.st, a.sst, base + v, x[v], xn[v], u[v], p[v], in2);
-        }
-        *(fv *)(a.phi_out + base) = xn;
-        *(fv *)(a.p + base) = p;
-        if (q + 1 >= a.T - a.W + 1) {
-            fv s = *(const fv *)(a.S + base);
-#pragma unroll
-            for (int v = 0; v < VEC; v++) s[v] = s[v] + xn[v];
-            *(fv *)(a.S + base) = s;
-        }
-        if (bad) atomicOr(a.err, ERR_NONFINITE);
+    csr_update<VEC, FIELD_ONLY>(a, q, i, base, u, x, p);
+}
+
+// A thread per (row, four replicas), rows side by side in a wavefront; column indices and values
+// come through vector loads, and a row's couplings are walked in ascending column order with B
+// gathers in flight.  The last batch reads the last coupling again in place of those past the end
+// and does not use it.  Bound by the gathers' bytes and the state's: the 100^3 lattice, R = 64,
+// 260 us a step, 1.0 GB of state at 4 TB/s and its gathers from L2 beside it.
+template <int B, bool FIELD_ONLY, typename O>
+__global__ __launch_bounds__(256) void k_step_csr_rows(CsrArgs a, int64_t q) {
+    typedef csr_vec<4> fv;
+    // workgroup b runs on XCD b mod 8: XCD x takes the threads' x-th eighth (the last nb mod 8
+    // workgroups keep their index)
+    const int64_t nb = gridDim.x, per = nb / 8, b = blockIdx.x;
+    const int64_t t = (b < per * 8 ? (b % 8) * per + b / 8 : b) * 256 + threadIdx.x;
+    if (t >= (int64_t)a.N * a.Rq) return;
+    const int i = (int)(t / a.Rq), c4 = (int)(t - (int64_t)i * a.Rq);
+    const int64_t base = 4 * t;
+    const O pitch = 16 * (O)a.Rq, off = 16 * (O)c4;
+    const char *X = (const char *)a.phi_in;
+    fv u = 0.f, x = 0.f, p = 0.f;
+    if constexpr (!FIELD_ONLY) {
+        x = *(const fv *)(a.phi_in + base);
+        p = *(const fv *)(a.p + base);
     }
+    const int e1 = a.rp[i + 1];
+    int e = a.rp[i];
+    for (; e1 - e >= B; e += B) {
+        fv g[B];
+        float w[B];
+#pragma unroll
+        for (int k = 0; k < B; k++) {
+            g[k] = *(const fv *)(X + ((O)a.ci[e + k] * pitch + off));
+            w[k] = a.v[e + k];
+        }
+#pragma unroll
+        for (int k = 0; k < B; k++)
+#pragma unroll
+            for (int v = 0; v < 4; v++) u[v] = fmaf(w[k], g[k][v], u[v]);
+    }
+    const int left = e1 - e;
+    if (left > 0) {
+        fv g[B - 1];
+        float w[B - 1];
+#pragma unroll
+        for (int k = 0; k < B - 1; k++) {
+            const int ek = e + min(k, left - 1);
+            g[k] = *(const fv *)(X + ((O)a.ci[ek] * pitch + off));
+            w[k] = a.v[ek];
+        }
+#pragma unroll
+        for (int k = 0; k < B - 1; k++)
+            if (k < left) {
+#pragma unroll
+                for (int v = 0; v < 4; v++) u[v] = fmaf(w[k], g[k][v], u[v]);
+            }
+    }
+    csr_update<4, FIELD_ONLY>(a, q, i, base, u, x, p);
 }
 
 static CsrArgs csr_args(hqa_md *md, Instance &I) {
@@ -175,38 +244,29 @@ static CsrArgs csr_args(hqa_md *md, Instance &I) {
 }
 
 template <int VEC, bool FO>
-static void launch_vec(const CsrArgs &a, int64_t q, uint32_t nchunk, bool sliced, hipStream_t st) {
-    const uint32_t nrb = ((uint32_t)a.N + 3) / 4;
-    uint32_t grid = nrb * nchunk;
-    if (sliced && nchunk < 8) grid = 8 * ((nrb + 8 / nchunk - 1) / (8 / nchunk));
+static void launch_vec(const CsrArgs &a, int64_t q, const CsrPlan &p, hipStream_t st) {
+    const unsigned grid = (unsigned)csr_wave_blocks(a.N, p);
     if ((uint64_t)a.N * a.Rq * 16 < (1ull << 32))
-        k_step_csr<VEC, FO, uint32_t><<<grid, 256, 0, st>>>(a, q, nchunk, sliced);
+        k_step_csr<VEC, FO, uint32_t><<<grid, 256, 0, st>>>(a, q, p.chunks, p.sliced);
     else
-        k_step_csr<VEC, FO, uint64_t><<<grid, 256, 0, st>>>(a, q, nchunk, sliced);
+        k_step_csr<VEC, FO, uint64_t><<<grid, 256, 0, st>>>(a, q, p.chunks, p.sliced);
 }
 
-// Chunks and their XCDs, by what was fastest (us per step, one / two / four replicas a lane):
-//  * up to 64 replicas: one a lane (G(10^4, 30) R = 64: 9.9 / 14.4 / 14.8; 16^3: 4.0 / 4.5 / 4.6);
-//  * few couplings a row (mean degree below 10): wide lanes, the step being state traffic
-//    (16^3, R = 128: 5.5 / 5.0 / 5.1; R = 1024: 23.0 / - / 16.7; G(3000, 5) R = 256: 8.2 / - / 7.0);
-//  * else 64-replica chunks, sliced over the XCDs when the chunks fill them evenly (G(10^4, 30)
-//    R = 256: 24.3, unsliced 35.0, four a lane 34.6; R = 128: 14.6, 16.0, two a lane 16.2);
-//    an uneven number of chunks above three takes four a lane.
+template <int B, bool FO>
+static void launch_rows(const CsrArgs &a, int64_t q, hipStream_t st) {
+    const unsigned grid = (unsigned)(((int64_t)a.N * a.Rq + 255) / 256);
+    if ((uint64_t)a.N * a.Rq * 16 < (1ull << 32)) k_step_csr_rows<B, FO, uint32_t><<<grid, 256, 0, st>>>(a, q);
+    else k_step_csr_rows<B, FO, uint64_t><<<grid, 256, 0, st>>>(a, q);
+}
+
 template <bool FO>
 static void launch_csr(const CsrArgs &a, int64_t nnz, int64_t q, hipStream_t st) {
-    const uint32_t Rp = 4u * (uint32_t)a.Rq, nc = (Rp + 63) / 64;
-    if (nc == 1) {
-        launch_vec<1, FO>(a, q, 1, false, st);
-    } else if (nnz < 10 * (int64_t)a.N) {
-        if (Rp <= 128) launch_vec<2, FO>(a, q, 1, false, st);
-        else launch_vec<4, FO>(a, q, (Rp + 255) / 256, false, st);
-    } else if (nc == 2 || nc == 4 || nc % 8 == 0) {
-        launch_vec<1, FO>(a, q, nc, true, st);
-    } else if (nc == 3) {
-        launch_vec<1, FO>(a, q, nc, false, st);
-    } else {
-        launch_vec<4, FO>(a, q, (Rp + 255) / 256, false, st);
-    }
+    const CsrPlan p = csr_plan(a.N, nnz, 4u * (uint32_t)a.Rq);
+    if (p.rows == 2) launch_rows<2, FO>(a, q, st);
+    else if (p.rows) launch_rows<6, FO>(a, q, st);
+    else if (p.vec == 1) launch_vec<1, FO>(a, q, p, st);
+    else if (p.vec == 2) launch_vec<2, FO>(a, q, p, st);
+    else launch_vec<4, FO>(a, q, p, st);
 }
 
 hipError_t launch_md_steps_csr(hqa_md *md, Instance &I, int64_t q0, int64_t q1) {

@@ -1,0 +1,65 @@
+"""The form of the sparse per-step kernel over all sizes (host code, compiled here): every launch
+stays within 2^32 threads, covers every row and replica, and slices only whole chunks of replicas
+over the XCDs of a large graph."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2004_03972_amd", "csrc")
+SHIM = """
+#include "csr_plan.h"
+extern "C" uint64_t plan(int N, int64_t nnz, uint32_t Rp, int *out) {
+    const hqa::CsrPlan p = hqa::csr_plan(N, nnz, Rp);
+    out[0] = p.rows; out[1] = p.vec; out[2] = (int)p.chunks; out[3] = p.sliced;
+    return p.rows ? ((uint64_t)N * (Rp / 4) + 255) / 256 : hqa::csr_wave_blocks(N, p);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def L(tmp_path_factory):
+    d = tmp_path_factory.mktemp("csr_plan")
+    (d / "shim.cc").write_text(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I" + CSRC,
+                    "-o", str(d / "shim.so"), str(d / "shim.cc")], check=True)
+    lib = C.CDLL(str(d / "shim.so"))
+    lib.plan.restype = C.c_uint64
+    lib.plan.argtypes = [C.c_int, C.c_int64, C.c_uint32, C.c_void_p]
+    return lib
+
+
+def test_every_size(L):
+    out = (C.c_int * 4)()
+    for N in (1, 3, 64, 511, 4096, 10000, 100003, 1 << 20, (1 << 26) - 1, 1 << 26, 1 << 28, 2 ** 31 - 1):
+        for d in (0, 1, 6, 9.9, 10, 12, 20, 30, 700):
+            nnz = min(int(N * d), 2 ** 31 - 2)
+            for Rp in (4, 8, 16, 32, 36, 48, 64, 68, 96, 124, 128, 132, 192, 196, 256, 260, 320, 512, 516,
+                       1024, 2048, 65536):
+                if N * (Rp // 4) >= 2 ** 32 - 256:        # beyond what the state's set-up launches
+                    continue
+                blocks = L.plan(N, nnz, Rp, out)
+                rows, vec, chunks, sliced = out
+                where = (N, nnz, Rp, rows, vec, chunks, sliced)
+                assert blocks * 256 < 2 ** 32, where
+                if rows:
+                    assert rows in (2, 6), where
+                    continue
+                assert vec in (1, 2, 4), where
+                assert 64 * vec * chunks >= Rp > 64 * vec * (chunks - 1), where
+                assert not sliced or (vec == 1 and (chunks in (2, 4) or chunks % 8 == 0)), where
+                if N * N >= (600 if Rp > 4 else 900) * nnz:   # many rows: no half-empty chunks
+                    assert Rp <= 64 or Rp % (64 * vec) == 0, where
+                    assert Rp > 32 or nnz >= 20 * N or Rp % 256 == 0, where
+
+
+@pytest.mark.parametrize("N,d,Rp,form", [
+    (1000000, 6, 4, "rows"), (1000000, 6, 64, "rows"), (100000, 30, 16, "rows"), (100000, 30, 68, "rows"),
+    (1 << 26, 0, 4, "rows"), (10000, 30, 128, "wave"), (100000, 30, 256, "wave"), (4096, 6, 1024, "wave"),
+    (2000, 12, 64, "wave")])
+def test_named_sizes(L, N, d, Rp, form):
+    out = (C.c_int * 4)()
+    L.plan(N, N * d, Rp, out)
+    assert (out[0] > 0) == (form == "rows")
