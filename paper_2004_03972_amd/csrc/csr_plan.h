@@ -1,4 +1,4 @@
-// csr_plan.h -- which form of the sparse per-step kernel a size takes (host code, plain C++).
+// csr_plan.h -- which kernels a sparse instance's size takes (host code, plain C++).
 #pragma once
 #include <stdint.h>
 
@@ -61,6 +61,14 @@ inline CsrPlan csr_plan(int N, int64_t nnz, uint32_t Rp) {
     }
     // a launch has fewer than 2^32 threads; rows side by side are N Rp / 4 of them
     return csr_wave_blocks(N, p) * 256 < ((uint64_t)1 << 32) ? p : rows;
+}
+
+// Whether the grids of the kernels that turn a replica-minor state in LDS (tiles of 32 spins x 32
+// replicas in k_export_turn, 16 x 32 in k_features_turn) stay within 2^32 threads and 65,535 blocks
+// in the second dimension; larger states take the kernels that do not.
+inline bool export_turn_fits(int N) { return ((uint64_t)N + 31) / 32 * 256 < ((uint64_t)1 << 32); }
+inline bool features_turn_fits(int N, int R) {
+    return ((uint64_t)N + 15) / 16 * 512 < ((uint64_t)1 << 32) && ((int64_t)R + 31) / 32 <= 65535;
 }
 
 }  // namespace hqa

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/hqa.h"
+#include "csr_plan.h"
 #include "energy_plan.h"
 
 namespace hqa {

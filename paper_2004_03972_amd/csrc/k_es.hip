@@ -170,7 +170,7 @@ hipError_t launch_features(const Instance &I, int R, int64_t K, float tau, float
     a.K = (float)K; a.tau = tau; a.mean_n1 = mean_n1;
     a.phi = I.phi32[I.cur]; a.st = I.st; a.n1 = I.n1; a.feat = feat;
     a.scale = I.st + 9 * a.sst;
-    if (I.smaj && (R + 31) / 32 <= 65535) {
+    if (I.smaj && features_turn_fits(I.N, R)) {
         k_feature_scales<<<(R + 3) / 4, 1024, 0, st>>>(a);
         k_features_turn<<<dim3((I.N + 15) / 16, (R + 31) / 32), 512, 0, st>>>(a);
         return hipGetLastError();

@@ -5,7 +5,6 @@
 // of 4): row i holds spin i of every replica, so a neighbour's fluxes are one
 // contiguous run.  Per spin update the kernel moves 16 bytes of state (read phi,
 // read and write p, write phi') and gathers 4 bytes per coupling.
-#include "csr_plan.h"
 #include "hqa_internal.h"
 #include "md_epilogue.h"
 

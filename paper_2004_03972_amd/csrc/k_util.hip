@@ -435,7 +435,7 @@ hipError_t launch_export(const Instance &I, int R, int prec, int what, double *d
         a.x64 = I.S64; a.x32 = I.S32;
     }
     int64_t n = (int64_t)I.N * R;
-    if (a.smaj && !a.f64 && !import && R > 1) {
+    if (a.smaj && !a.f64 && !import && R > 1 && export_turn_fits(I.N)) {
         k_export_turn<<<dim3((I.N + 31) / 32, std::min((R + 31) / 32, 65535)), 256, 0, st>>>(a);
         return hipGetLastError();
     }

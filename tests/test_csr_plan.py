@@ -1,6 +1,6 @@
 """The form of the sparse per-step kernel over all sizes (host code, compiled here): every launch
 stays within 2^32 threads, covers every row and replica, and slices only whole chunks of replicas
-over the XCDs of a large graph."""
+over the XCDs of a large graph; the turned copies of a state likewise."""
 import ctypes as C
 import os
 import subprocess
@@ -16,6 +16,8 @@ extern "C" uint64_t plan(int N, int64_t nnz, uint32_t Rp, int *out) {
     out[0] = p.rows; out[1] = p.vec; out[2] = (int)p.chunks; out[3] = p.sliced;
     return p.rows ? ((uint64_t)N * (Rp / 4) + 255) / 256 : hqa::csr_wave_blocks(N, p);
 }
+extern "C" int export_turn(int N) { return hqa::export_turn_fits(N); }
+extern "C" int features_turn(int N, int R) { return hqa::features_turn_fits(N, R); }
 """
 
 
@@ -63,3 +65,11 @@ def test_named_sizes(L, N, d, Rp, form):
     out = (C.c_int * 4)()
     L.plan(N, N * d, Rp, out)
     assert (out[0] > 0) == (form == "rows")
+
+
+def test_turned_copies_stay_within_a_launch(L):
+    for N in (1, 31, 32, 4096, (1 << 27) - 16, (1 << 27) - 15, 1 << 27, (1 << 29) - 32, (1 << 29) - 31,
+              1 << 29, 2 ** 31 - 1):
+        assert bool(L.export_turn(N)) == (-(-N // 32) * 256 < 2 ** 32), N
+        for R in (1, 33, 32 * 65535, 32 * 65535 + 1, 2 ** 31 - 1):
+            assert bool(L.features_turn(N, R)) == (-(-N // 16) * 512 < 2 ** 32 and -(-R // 32) <= 65535), (N, R)
