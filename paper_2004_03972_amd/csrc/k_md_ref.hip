@@ -325,9 +325,14 @@ hipError_t launch_hamiltonian(hqa_md *md, Instance &I, double *H, void *scratch,
     RefArgs a = ref_args(md, I);
     F64View xv = make_view(md, I, true), pv = make_view(md, I, false);
     if (!a.csr) {
-        // J is read once per replica block: as wide a block as the replicas fill
-        if (a.R > 32) launch_hmd<4>(a, xv, pv, md->q, (double *)scratch, st);
-        else if (a.R > 16) launch_hmd<2>(a, xv, pv, md->q, (double *)scratch, st);
+        // J is read once per replica block: as wide a block as the replicas fill, while the blocks
+        // give every CU one (whole call, wide / by this rule, R = 64: N = 8 32.9 / 30.7 us,
+        // N = 500 39.0 / 32.9, N = 3000 84 / 76; R = 500: N = 8 35.8 / 32.9; a workgroup a replica
+        // N = 8 29.1, 31.1, N = 500 105, 183)
+        const int tiles = (a.N + 15) / 16;
+        auto fills = [&](int reps) { return (int64_t)((a.R + reps - 1) / reps) * tiles >= 256; };
+        if (a.R > 32 && fills(64)) launch_hmd<4>(a, xv, pv, md->q, (double *)scratch, st);
+        else if (a.R > 16 && fills(32)) launch_hmd<2>(a, xv, pv, md->q, (double *)scratch, st);
         else launch_hmd<1>(a, xv, pv, md->q, (double *)scratch, st);
         k_hmd_sum<<<a.R, 256, 0, st>>>(a, md->q, (a.N + 15) / 16, (const double *)scratch, H);
         return hipGetLastError();
