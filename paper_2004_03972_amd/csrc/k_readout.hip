@@ -57,31 +57,31 @@ __device__ __forceinline__ uint64_t sel_key(const SelArgs &a, int r, int i, int8
 // state and one thread walking the bins, 54 us now.
 constexpr int SEL_KEYS = 8192;
 
-__device__ __forceinline__ void select_body(const SelArgs &a, const int bx_) {
+template <bool KEPT>
+__device__ __forceinline__ void select_keys(const SelArgs &a, const int bx_) {
     __shared__ uint32_t hist[256];
     __shared__ uint64_t s_prefix;
     __shared__ int s_k;
     __shared__ int wsum[2][4];
-    __shared__ uint64_t s_keys[SEL_KEYS / 2];
+    __shared__ uint64_t s_keys[KEPT ? SEL_KEYS / 2 : 1];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     // workgroup b runs on XCD b mod 8 as a rule: whole groups of 256 replicas are dealt by lines
     const int r = a.smaj && bx_ < (a.R & ~255)
                       ? (bx_ & ~255) + 32 * (bx_ & 7) + ((bx_ >> 3) & 31) : bx_;
-    const bool kept = a.N <= (a.f64 ? SEL_KEYS / 2 : SEL_KEYS);
     uint32_t *const k32 = (uint32_t *)s_keys;
     auto key = [&](int i) -> uint64_t {
-        if (!kept) return sel_key(a, r, i, nullptr);
+        if constexpr (!KEPT) return sel_key(a, r, i, nullptr);
         return a.f64 ? s_keys[i] : (uint64_t)k32[i];
     };
     // spins
-    if (kept || !a.keys)
+    if (KEPT || !a.keys)
 #pragma unroll 4
         for (int i = tid; i < a.N; i += 256) {
             int8_t s;
             const uint64_t k = sel_key(a, r, i, &s);
             if (!a.keys) a.spins[(int64_t)r * a.N + i] = s;
-            if (kept && a.f64) s_keys[i] = k;
-            else if (kept) k32[i] = (uint32_t)k;
+            if (KEPT && a.f64) s_keys[i] = k;
+            else if (KEPT) k32[i] = (uint32_t)k;
         }
     if (a.n == 0) return;
     uint64_t prefix = 0, pmask = 0;
@@ -145,6 +145,11 @@ __device__ __forceinline__ void select_body(const SelArgs &a, const int bx_) {
         for (int v = 0; v < 4; v++) { eq_run += wsum[0][v]; out_run += wsum[1][v]; }
         __syncthreads();
     }
+}
+
+__device__ __forceinline__ void select_body(const SelArgs &a, const int bx_) {
+    if (a.N <= (a.f64 ? SEL_KEYS / 2 : SEL_KEYS)) select_keys<true>(a, bx_);
+    else select_keys<false>(a, bx_);
 }
 
 __global__ __launch_bounds__(256) void k_select(SelArgs a) { select_body(a, blockIdx.x); }
