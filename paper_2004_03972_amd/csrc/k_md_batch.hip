@@ -3,11 +3,11 @@
 // A batch of uneven instances (sizes N_k, one shared schedule and replica count)
 // advances step by step; each step is one launch over a tile table of (instance, 128
 // rows, 64 replicas) tiles (32 or 16 replicas in small batches), whatever the storage type
-// (FP32, BF16, FP8), so with 64 replicas each J row block is read once per step.  An FP8 instance whose couplings are
-// all 0 or 1 (unit-weight MAX-CUT) is streamed from a copy with one bit per coupling,
-// expanded in registers to the same BF16 operands.  In large batches the tiles of an
-// instance share one XCD; tiles are placed longest-first (LPT by padded size), so the
-// largest instances start first and the short tiles fill the tail of the step.  The field
+// (FP32, BF16, FP8), so with 64 replicas each J row block is read once per step.  An FP8
+// instance whose couplings are all 0 or 1 (unit-weight MAX-CUT) is streamed from a copy with
+// one bit per coupling, expanded in registers to the same BF16 operands.  Tile shape, kernel
+// and placement follow the sizes (batch_plan.h); tiles are placed longest-first (LPT by padded
+// size), so the largest instances start first and the short tiles fill the tail.  The field
 // uses the chunk-to-chain decomposition of the other dense kernels, and the update
 // the same binary32 sequence, so a batched instance evolves bit-identically to the
 // same instance run alone.
@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "hqa_internal.h"
+#include "batch_plan.h"
 #include "md_epilogue.h"
 
 namespace hqa {
@@ -41,10 +42,6 @@ struct BatchInst {
     float *phi[2];
     bf16 *xb[2];
     float *p, *S;
-};
-
-struct BatchTile {
-    int inst, i0, r0, pad;
 };
 
 struct BatchArgs {
@@ -74,7 +71,7 @@ struct BatchArgs {
 // would then also wait for the next group's prefetch, and every group would pay the
 // whole memory latency.  Global loads count only against the vector-memory counter,
 // so the prefetch stays in flight across the group's MFMAs and its barrier.
-constexpr int BL_ROWS = 128, BL_REPS = 64, BL_LDB = 128 + 8;   // LDS row: 272 bytes
+constexpr int BL_REPS = 64, BL_LDB = 128 + 8;   // LDS row: 272 bytes
 
 template <typename T>
 __device__ __forceinline__ const __attribute__((address_space(1))) T *gld(const void *p) {
@@ -114,7 +111,7 @@ __device__ __forceinline__ bf16x8 a_chunk(const W *g, int j) {
     }
 }
 
-// RT replica tiles of 16 per workgroup (4, 2 or 1; see build_plan): 512 threads stage
+// RT replica tiles of 16 per workgroup (4, 2 or 1; see batch_form_for): 512 threads stage
 // 16 RT replicas x 128 columns, 8 RT bytes each.
 template <int RT>
 struct FluxStage {
@@ -318,7 +315,7 @@ __device__ __forceinline__ void batch_lds_tile(const BatchArgs &a, int64_t q, co
     }
 }
 
-// State accesses of the epilogue, past the last-level cache if STREAM (see build_plan).
+// State accesses of the epilogue, past the last-level cache if STREAM (see batch_form_for).
 template <bool STREAM, typename T>
 __device__ __forceinline__ T ld_state(const __attribute__((address_space(1))) T *p) {
     if constexpr (STREAM) return __builtin_nontemporal_load(p);
@@ -754,9 +751,7 @@ struct BatchPlan {
     BatchInst *dinst = nullptr;
     BatchTile *dtiles[3] = {nullptr, nullptr, nullptr};
     int ntiles[3] = {0, 0, 0};
-    bool stream = false;                // the state passes the last-level cache by
-    bool wide = false;                  // four wavefronts of 32-row tiles
-    int rt = 4;                         // replica tiles of 16 per BF16 / FP8 workgroup
+    BatchForm form = {4, false, false}; // of the BF16 and FP8 instances
     std::vector<BatchGraph> graphs;     // most recently used last
     hipStream_t cap = nullptr;          // capture-only stream (no work runs on it)
 };
@@ -815,137 +810,18 @@ static hipError_t build_plan(hqa_md *md, BatchPlan *&out) {
     std::stable_sort(dense.begin(), dense.end(), [&](int x, int y) {
         return md->inst[x].Np > md->inst[y].Np;
     });
-    std::vector<BatchTile> ht[3];
-    // Every tile of an instance on one XCD (workgroup b of a launch runs on XCD b mod 8),
-    // so the instance's flux operand is fetched into one L2; instances go to the
-    // least-loaded XCD, largest first (LPT on the tile count, i.e. on N^2 R work); the
-    // per-XCD lists are interleaved into the launch order and padded with placeholder
-    // tiles.  An instance with at
-    // least an eighth of all the work is split instead: its row blocks are cut into
-    // eight contiguous ranges, one per XCD, each with all replica tiles, so every XCD
-    // reads an eighth of J and the 64-replica tiles of a row block share its J lines in
-    // one L2.
     // one launch for the FP32 instances, one for the BF16 and FP8 ones
-    for (int fam = 0; fam < 2; fam++) {
-        auto member = [&](const Instance &I) { return (I.jt == JT_F32) == (fam == 0); };
-        constexpr int NX = 8;
-        std::vector<BatchTile> xl[NX];
-        int64_t load[NX] = {0};
-        int64_t total = 0;
-        // Shape and placement by the number of 64-replica tiles, all of which are resident
-        // at once up to 512 (two per CU).  Few tiles leave a step waiting on its longest one,
-        // whose groups run at the latency of one or two workgroups per CU, so
-        //  * replicas narrower than a tile take a narrower tile, up to 320 tiles are halved
-        //    (32 replicas) and up to 96 quartered: more workgroups, each with less to stage and
-        //    multiply per group (us per step, R = 64, 64 / 32 / 16 replicas a tile: 88 tiles
-        //    30.5 / 18.8 / 16.3; 191 tiles 38.8 / 28.6 / 30.5; 374 tiles 40.2 / 43.8; R = 16, 8
-        //    instances, 64 / 16: 20.5 / 14.5); past that, R = 65 .. 96 takes three 32s rather
-        //    than two 64s (374 x 2 tiles, R = 96: 66.2 / 61.8);
-        //  * up to 1024 tiles go to the XCDs one by one instead of an instance at a time: even
-        //    loads matter more than one L2 per flux operand (374 tiles 55.4 -> 44.0, 640 tiles
-        //    59.3 -> 49.8; 1700 tiles 157 / 158).
-        int64_t count = 0;
-        for (int k : dense)
-            if (member(md->inst[k]))
-                count += (int64_t)((md->inst[k].N + BL_ROWS - 1) / BL_ROWS) * ((md->R + 63) / 64);
-        int reps = 64;
-        if (fam == 1) {
-            bp->rt = md->R <= 16 ? 1 : md->R <= 32 ? 2 : 4;
-            if (bp->rt == 4 && (count <= 320 || (md->R > 64 && md->R <= 96))) bp->rt = 2;
-            if (bp->rt == 2 && count <= 96) bp->rt = 1;
-            reps = 16 * bp->rt;
-            // Four wavefronts of 32-row tiles multiply faster, eight of 16-row tiles have the
-            // shorter way through a group when a CU holds one workgroup: they take batches whose
-            // tiles are all resident at once but uneven (24 instances, 374 tiles: 23.07 ms a
-            // pass, 23.34 with four; 40 instances 51.3 / 49.6 us a step) and BF16 couplings of
-            // few groups (N = 2048, R = 2048, 16 groups: 43 / 47 us; N = 4096, R = 1024 64 / 65;
-            // N = 8192, R = 512 111 / 102).
-            int members = 0;
-            bool few = false;
-            for (int k : dense)
-                if (member(md->inst[k])) {
-                    members++;
-                    few |= md->inst[k].jt == JT_BF16 && md->inst[k].Np < 4096;
-                }
-            bp->wide = count > 512 || (members == 1 && !few);
-        }
-        const bool spread = count <= 1024;
-        // work of a tile: the bytes it streams (its couplings and the staged flux
-        // block) plus a fixed cost of its first loads and epilogue (about the time of
-        // 256 KB)
-        auto tile_work = [&](const Instance &I) -> int64_t {
-            const int64_t jb = I.jt == JT_F32 ? 512 : I.jt == JT_BF16 ? 256 : I.jbits > 0 ? 16 : 128;
-            return (jb + 2 * reps) * (int64_t)I.Np + 262144;
-        };
-        for (int k : dense) {
-            const Instance &I = md->inst[k];
-            if (!member(I)) continue;
-            total += (int64_t)((I.N + BL_ROWS - 1) / BL_ROWS) * ((md->R + reps - 1) / reps) * tile_work(I);
-        }
-        for (int k : dense) {
-            const Instance &I = md->inst[k];
-            if (!member(I)) continue;
-            const int nrb = (I.N + BL_ROWS - 1) / BL_ROWS;
-            const int64_t tw = tile_work(I);
-            const int64_t work = (int64_t)nrb * ((md->R + reps - 1) / reps) * tw;
-            if (nrb >= NX && NX * work >= total) {
-                for (int x = 0; x < NX; x++) {
-                    for (int rb = x * nrb / NX; rb < (x + 1) * nrb / NX; rb++)
-                        for (int r0 = 0; r0 < md->R; r0 += reps) {
-                            xl[x].push_back({k, rb * BL_ROWS, r0, 0});
-                            load[x] += tw;
-                        }
-                }
-                continue;
-            }
-            if (spread) {
-                for (int i0 = 0; i0 < I.N; i0 += BL_ROWS)
-                    for (int r0 = 0; r0 < md->R; r0 += reps) {
-                        int x = 0;
-                        for (int y = 1; y < NX; y++)
-                            if (load[y] < load[x]) x = y;
-                        xl[x].push_back({k, i0, r0, 0});
-                        load[x] += tw;
-                    }
-                continue;
-            }
-            int x = 0;
-            for (int y = 1; y < NX; y++)
-                if (load[y] < load[x]) x = y;
-            for (int i0 = 0; i0 < I.N; i0 += BL_ROWS)
-                for (int r0 = 0; r0 < md->R; r0 += reps) {
-                    xl[x].push_back({k, i0, r0, 0});
-                    load[x] += tw;
-                }
-        }
-        // an XCD's first 32 tiles get a CU each, the others join them from the first CU on:
-        // longest tiles last among the first, so that they are not joined by long ones
-        // (374 tiles: 44.0 -> 40.3)
-        if (spread)
-            for (int x = 0; x < NX; x++)
-                if (xl[x].size() > 32) std::reverse(xl[x].begin(), xl[x].begin() + 32);
-        size_t longest = 0;
-        for (int x = 0; x < NX; x++) longest = std::max(longest, xl[x].size());
-        std::vector<BatchTile> &dst = ht[fam == 0 ? JT_F32 : JT_BF16];
-        for (size_t j = 0; j < longest; j++)
-            for (int x = 0; x < NX; x++)
-                dst.push_back(j < xl[x].size() ? xl[x][j] : BatchTile{-1, 0, 0, 0});
-    }
-    // What a step reads and writes: the couplings, and per spin two copies of phi and of its
-    // BF16 operand, p and S.  Up to the 256 MB of last-level cache it stays there from step to
-    // step; beyond, the state passes that cache by, which leaves it to the couplings and
-    // operands (us per step, kept / passed by: 24 instances R = 64, 102 MB 40.6 / 42.2; 40
-    // instances, 162 MB 49.6 / 54.0; N = 8192, R = 768, 190 MB 128 / 150; 24 instances R = 256,
-    // 271 MB 125 / 120; 60 instances, 294 MB 104 / 93; 100 instances, 464 MB 152 / 138; couplings
-    // passed by as well: 60 instances 141).
-    int64_t bytes = 0;
+    std::vector<BatchShape> all, fam[2];
     for (int k : dense) {
         const Instance &I = md->inst[k];
-        const int64_t cells = (int64_t)I.Np * I.Np;
-        bytes += (I.jt == JT_F32 ? 4 * cells : I.jt == JT_BF16 ? 2 * cells : I.jbits > 0 ? cells / 8 : cells) +
-                 20ll * I.N * md->R;
+        const BatchShape s = {k, I.N, I.Np, I.jt == JT_F32 ? 0 : I.jt == JT_BF16 ? 1 : I.jbits > 0 ? 3 : 2};
+        all.push_back(s);
+        fam[I.jt != JT_F32].push_back(s);
     }
-    bp->stream = bytes > ((int64_t)256 << 20);
+    bp->form = batch_form_for(fam[1], md->R, batch_bytes(all, md->R));
+    std::vector<BatchTile> ht[3];
+    ht[JT_F32] = batch_place(fam[0], md->R, BL_REPS, true);
+    ht[JT_BF16] = batch_place(fam[1], md->R, 16 * bp->form.rt, false);
     hipError_t e = dev_malloc((void **)&bp->dinst, sizeof(BatchInst) * hi.size());
     if (e == hipSuccess)
         e = hipMemcpy(bp->dinst, hi.data(), sizeof(BatchInst) * hi.size(), hipMemcpyHostToDevice);
@@ -980,10 +856,10 @@ static void enqueue_steps(hqa_md *md, const BatchPlan *bp, int64_t q0, int64_t q
             a.tiles = bp->dtiles[t];
             a.ntiles = bp->ntiles[t];
             if (t == JT_F32) k_step_batch_f32<<<a.ntiles, 512, 0, st>>>(a, q);
-            else if (bp->rt == 4 && bp->stream) k_step_batch_lds<<<a.ntiles, 256, 0, st>>>(a, q);
-            else if (bp->rt == 4 && bp->wide) k_step_batch_cached<<<a.ntiles, 256, 0, st>>>(a, q);
-            else if (bp->rt == 4) k_step_batch_narrow<4><<<a.ntiles, 512, 0, st>>>(a, q);
-            else if (bp->rt == 2) k_step_batch_narrow<2><<<a.ntiles, 512, 0, st>>>(a, q);
+            else if (bp->form.stream) k_step_batch_lds<<<a.ntiles, 256, 0, st>>>(a, q);
+            else if (bp->form.wide) k_step_batch_cached<<<a.ntiles, 256, 0, st>>>(a, q);
+            else if (bp->form.rt == 4) k_step_batch_narrow<4><<<a.ntiles, 512, 0, st>>>(a, q);
+            else if (bp->form.rt == 2) k_step_batch_narrow<2><<<a.ntiles, 512, 0, st>>>(a, q);
             else k_step_batch_narrow<1><<<a.ntiles, 512, 0, st>>>(a, q);
         }
         cur ^= 1;
