@@ -11,7 +11,7 @@
 // vectors of the state.
 //
 // Workgroup: a block of TM x TN output tiles (16 TM rows x 16 TN replicas, TM in
-// {1, 2} and TN in {1, 2, 4}, by the tuner or by default_block), K split over the
+// {1, 2} and TN in {1, 2, 4}, by the tuner or by step_block), K split over the
 // four wavefronts by accumulation chain.  The dense field is accumulated in four chains (K chunk c
 // of 32 columns for BF16 operands, 16 for FP32, feeds chain c mod 4; see
 // combine4), and wavefront w computes chain w of every tile of the block:
@@ -22,6 +22,7 @@
 // kernels, which accumulate the same chains.
 #include <type_traits>
 
+#include "dense_plan.h"
 #include "hqa_internal.h"
 #include "md_epilogue.h"
 
@@ -323,25 +324,6 @@ static hipError_t ensure_tiled_x(Instance &I, hipStream_t st) {
     return hipSuccess;
 }
 
-// Block shape of an instance that was neither tuned nor pinned: the largest of 2 x 4, 2 x 2,
-// 2 x 1 tiles that divides the replicas and still gives 180 workgroups, else 1 x 1 (two rows
-// beat two replica tiles of the same count).  Larger blocks reuse operands, but below some three quarters of the 256 CUs the
-// emptier chip costs more than the reuse saves (us per step, 2 x widest -> this rule: binary32
-// N = 509, R = 33 6.2 -> 5.0; N = 800, R = 64 16.4 -> 6.5; BF16 N = 400, R = 64 8.2 -> 4.3;
-// N = 2000, R = 64 17.0 -> 9.5; N = 4000, R = 128 29.6 both); it names the fastest untiled
-// shape at all 29 (size, storage) pairs it was checked on.
-static void default_block(const Instance &I, int &tm, int &tn) {
-    static const int shapes[][2] = {{2, 4}, {2, 2}, {2, 1}};
-    for (const auto &s : shapes)
-        if (I.Rp % (16 * s[1]) == 0 &&
-            (int64_t)(I.Np / (16 * s[0])) * (I.Rp / (16 * s[1])) >= 180) {
-            tm = s[0];
-            tn = s[1];
-            return;
-        }
-    tm = tn = 1;
-}
-
 // Blocks of tm x tn output tiles: 16 tm rows x 16 tn replicas per workgroup; cb
 // chunks of each chain's loads in flight together (8: a chain of up to eight chunks
 // costs one round trip to L2).
@@ -383,15 +365,11 @@ static void launch_one(const DenseArgs &a, int tm, int tn, int cb, int64_t q, hi
 }
 
 hipError_t launch_md_steps_dense(hqa_md *md, Instance &I, int64_t q0, int64_t q1) {
-    // the tuner's or the caller's shape, else by size; eight chunks of 16-bit operands in
-    // flight cost the registers of four binary32 ones
-    int tm, tn;
-    default_block(I, tm, tn);
-    if (I.step_tm) {
-        tm = I.step_tm;                        // Np is a multiple of 128: both divide it
-        tn = I.step_tn;
-    }
-    const int cb = I.step_cb ? I.step_cb : I.jt == JT_F32 ? 4 : 8;
+    // the tuner's or the caller's shape, else by size
+    const StepBlock by_size = step_block(I.Np, I.Rp, I.jt == JT_F32);
+    const int tm = I.step_tm ? I.step_tm : by_size.tm;      // Np is a multiple of 128: both divide it
+    const int tn = I.step_tm ? I.step_tn : by_size.tn;
+    const int cb = I.step_cb ? I.step_cb : by_size.cb;
     if (I.step_tj && q0 < q1) {
         hipError_t e = ensure_tiled_j(I, md->stream);
         if (e == hipSuccess) e = ensure_tiled_x(I, md->stream);
@@ -419,9 +397,8 @@ hipError_t launch_md_steps_dense(hqa_md *md, Instance &I, int64_t q0, int64_t q1
 hipError_t launch_field_dense(hqa_md *md, Instance &I, float *u, hipStream_t st) {
     DenseArgs a = dense_args(md, I);
     a.u_out = u;
-    int tm, tn;
-    default_block(I, tm, tn);
-    launch_one<true>(a, tm, tn, 4, 0, st);
+    const StepBlock b = step_block(I.Np, I.Rp, I.jt == JT_F32);
+    launch_one<true>(a, b.tm, b.tn, 4, 0, st);
     return hipGetLastError();
 }
 

@@ -50,3 +50,14 @@ def test_tiled_runs_in_pieces(H, N, R):
     for cb in (4, 8):
         got = _run(H, prob, 10, R, "bf16", (1, 1, cb, True), (1, 4, 10))
         assert all(np.array_equal(x, y) for x, y in zip(got, want))
+
+
+# the smallest sizes of a larger block, and of binary32's deeper one (2x1, 2x2 and 2x4)
+@pytest.mark.parametrize("prec", ["f32", "bf16", "fp8"])
+@pytest.mark.parametrize("N,R", [(4097, 16), (2049, 64), (4097, 64), (1100, 240), (1409, 1248), (3970, 256)])
+def test_default_block_at_the_lines(H, N, R, prec):
+    J = np.sign(inst.sk(N, 3)) if prec == "fp8" else inst.sk(N, 3)
+    prob = H.Problem(J)
+    a = _run(H, prob, 5, R, prec, None, (5,))
+    b = _run(H, prob, 5, R, prec, (1, 1, 4, False), (5,))
+    assert all(np.array_equal(x, y) for x, y in zip(a, b))
