@@ -1,5 +1,5 @@
-// dense_plan.h -- block shape of the dense per-step kernel for a size that was neither tuned nor
-// pinned (host code, plain C++).
+// dense_plan.h -- form of the dense per-step kernel by size: block shape where it was neither tuned
+// nor pinned, and the tiled form's copies (host code, plain C++).
 #pragma once
 #include <stdint.h>
 
@@ -47,5 +47,13 @@ inline StepBlock step_block(int Np, int Rp, bool f32) {
     if (f32 && Np >= 1024 && best.tm == 2 && step_blocks(Np, Rp, best.tm, best.tn) >= 512) best.cb = 8;
     return best;
 }
+
+// Whether a run of some steps by the tiled form reads the operand-order copies.  Setting the fluxes'
+// copy up is a launch more on each run, some 2.4 us, and a step gains about 0.9 us per 1000 columns
+// by it; shorter runs read the row-major state and couplings, bit for bit the same (us per step of
+// runs of one step, tiled / row-major: N = 387 6.2 / 4.4, N = 1000 6.6 / 5.3, N = 2048 7.5 / 6.9,
+// N = 4000 9.7 / 10.2; of two: N = 1000 5.5 / 5.3, N = 1500 6.0 / 6.1; of four: N = 387 4.4 / 4.4,
+// N = 1000 4.9 / 5.2).
+inline bool step_reads_tiles(int Np, int64_t steps) { return steps >= 2560 || steps * Np >= 2560; }
 
 }  // namespace hqa

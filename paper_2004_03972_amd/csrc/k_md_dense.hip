@@ -370,16 +370,21 @@ hipError_t launch_md_steps_dense(hqa_md *md, Instance &I, int64_t q0, int64_t q1
     const int tm = I.step_tm ? I.step_tm : by_size.tm;      // Np is a multiple of 128: both divide it
     const int tn = I.step_tm ? I.step_tn : by_size.tn;
     const int cb = I.step_cb ? I.step_cb : by_size.cb;
-    if (I.step_tj && q0 < q1) {
+    bool tiled = I.step_tj && q0 < q1;
+    if (tiled) {
+        // made by a short run as well: a longer one may follow in a stream capture
         hipError_t e = ensure_tiled_j(I, md->stream);
         if (e == hipSuccess) e = ensure_tiled_x(I, md->stream);
         if (e != hipSuccess) return e;
+        tiled = step_reads_tiles(I.Np, q1 - q0);
+    }
+    if (tiled) {
         const int64_t n = (int64_t)I.Rp * (I.ld / 8);
         k_tile_x<<<(unsigned)((n + 255) / 256), 256, 0, md->stream>>>(I.phib[I.cur], I.Rp, I.ld, I.xt[0]);
     }
     for (int64_t q = q0; q < q1; q++) {
         DenseArgs a = dense_args(md, I);
-        if (I.step_tj) {
+        if (tiled) {
             // the steps pass the operand copy on between the two tiled buffers; the last
             // one also leaves the row-major copy the other plans start from
             a.Jt = I.Jt;

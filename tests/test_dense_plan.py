@@ -15,6 +15,7 @@ extern "C" int64_t plan(int Np, int Rp, int f32, int *out) {
     out[0] = b.tm; out[1] = b.tn; out[2] = b.cb;
     return hqa::step_blocks(Np, Rp, b.tm, b.tn);
 }
+extern "C" int tiles(int Np, int64_t steps) { return hqa::step_reads_tiles(Np, steps); }
 """
 
 
@@ -31,6 +32,7 @@ def plan(tmp_path_factory):
         out = (C.c_int * 3)()
         n = lib.plan(-(-N // 128) * 128, -(-R // 16) * 16, int(f32), out)
         return n, tuple(out)
+    f.tiles = lambda Np, steps: bool(lib.tiles(Np, C.c_int64(steps)))
     return f
 
 
@@ -55,3 +57,8 @@ def test_every_size(plan):
 def test_line_between_shapes(plan, N, R, shape):
     for f32 in (False, True):
         assert plan(N, R, f32)[1][:2] == shape, plan(N, R, f32)
+
+
+def test_short_runs_of_small_problems_set_up_no_copies(plan):
+    for Np, line in ((128, 20), (512, 5), (640, 4), (1024, 3), (1280, 2), (2432, 2), (2560, 1), (10112, 1)):
+        assert [plan.tiles(Np, s) for s in (line - 1, line, 2 ** 62)] == [False, True, True], Np

@@ -61,3 +61,15 @@ def test_default_block_at_the_lines(H, N, R, prec):
     a = _run(H, prob, 5, R, prec, None, (5,))
     b = _run(H, prob, 5, R, prec, (1, 1, 4, False), (5,))
     assert all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+# short runs, which read the row-major state, between long ones, which read the copies
+@pytest.mark.parametrize("prec", ["bf16", "fp8"])
+@pytest.mark.parametrize("N,R", [(300, 5), (1300, 33), (2432, 17), (2433, 3)])
+def test_tiled_short_and_long_runs(H, N, R, prec):
+    J = np.sign(inst.sk(N, 2)) if prec == "fp8" else inst.sk(N, 2)
+    prob = H.Problem(J)
+    cuts = (1, 8, 9, 10, 32, 34, 35)
+    want = _run(H, prob, 35, R, prec, (1, 1, 4, False), cuts)
+    got = _run(H, prob, 35, R, prec, (1, 1, 8, True), cuts)
+    assert all(np.array_equal(x, y) for x, y in zip(got, want))
