@@ -1049,6 +1049,7 @@ hqa_status hqa_md_tune(hqa_md *md, int32_t steps) {
         float best = 1e30f;
         TuneCand pick{HQA_PLAN_STEP, 0, 0, 0, 0};
         const int tn0 = I.step_tn, tm0 = I.step_tm, cb0 = I.step_cb, tj0 = I.step_tj;
+        const bool had_xt = I.xt[0];
         const char *stage = "snapshot";
         hipError_t he = copy(true);
         // the error word as the caller left it: a candidate that raises a flag is
@@ -1130,6 +1131,10 @@ hqa_status hqa_md_tune(hqa_md *md, int32_t steps) {
         I.step_tm = pick.tm;
         I.step_cb = pick.cb;
         I.step_tj = pick.tj;
+        // the candidates' operand-order copies of the state, where the choice does not read them
+        // (a run captured under an earlier pin may read those that were there)
+        if (!pick.tj && !had_xt)
+            for (bf16 *&x : I.xt) { dfree(x); x = nullptr; }
         cache.store(key, pick);
     }
     if (rs == HQA_OK) rs = tune_multi(md, steps, e0, e1, cache);

@@ -307,21 +307,23 @@ __global__ __launch_bounds__(256) void k_tile_x(const bf16 *x, int Rp, int ld, b
     *(bf16x8 *)(xt + x_tiled(ld / 128, r, k)) = *(const bf16x8 *)(x + (int64_t)r * ld + k);
 }
 
-// Both buffers of the operand-order copy, zero where no flux is ever written (padding).
+static void tile_x(const Instance &I, bf16 *xt, hipStream_t st) {
+    const int64_t n = (int64_t)I.Rp * (I.ld / 8);
+    k_tile_x<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(I.phib[I.cur], I.Rp, I.ld, xt);
+}
+
+// Both buffers of the operand-order copy; no step writes their padding, zero as the state's.
 static hipError_t ensure_tiled_x(Instance &I, hipStream_t st) {
-    const size_t n = (size_t)I.Rp * I.ld;
     for (int b = 0; b < 2; b++) {
         if (I.xt[b]) continue;
-        hipError_t e = dev_malloc((void **)&I.xt[b], n * sizeof(bf16));
-        if (e != hipSuccess) return e;
-        e = hipMemsetAsync(I.xt[b], 0, n * sizeof(bf16), st);
+        hipError_t e = dev_malloc((void **)&I.xt[b], (size_t)I.Rp * I.ld * sizeof(bf16));
         if (e != hipSuccess) {
-            (void)hipFree(I.xt[b]);
             I.xt[b] = nullptr;
             return e;
         }
+        tile_x(I, I.xt[b], st);
     }
-    return hipSuccess;
+    return hipGetLastError();
 }
 
 // Blocks of tm x tn output tiles: 16 tm rows x 16 tn replicas per workgroup; cb
@@ -378,10 +380,7 @@ hipError_t launch_md_steps_dense(hqa_md *md, Instance &I, int64_t q0, int64_t q1
         if (e != hipSuccess) return e;
         tiled = step_reads_tiles(I.Np, q1 - q0);
     }
-    if (tiled) {
-        const int64_t n = (int64_t)I.Rp * (I.ld / 8);
-        k_tile_x<<<(unsigned)((n + 255) / 256), 256, 0, md->stream>>>(I.phib[I.cur], I.Rp, I.ld, I.xt[0]);
-    }
+    if (tiled) tile_x(I, I.xt[0], md->stream);
     for (int64_t q = q0; q < q1; q++) {
         DenseArgs a = dense_args(md, I);
         if (tiled) {
