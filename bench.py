@@ -528,9 +528,9 @@ def bench_batch(args, hqa, torch):
     launch_s = float(np.mean(md_ms)) / 1e3 / Tt       # one launch per MD step
     out["roofline"] = {"bound": "hbm", "achieved": bytes_step / launch_s / 1e9, "peak": 8000.0,
                        "unit": "GB/s", "frac": bytes_step / launch_s / 8.0e12,
-                       "traffic": measured_traffic("k_step_batch_lds_batch512_pmc.txt", "batch",
-                                                   "k_step_batch_lds"),
-                       "kernel": "k_step_batch_lds", "launches_per_run": Tt,
+                       "traffic": measured_traffic("k_step_batch_narrow_batch512_pmc.txt", "batch",
+                                                   "k_step_batch_narrow<4>"),
+                       "kernel": "k_step_batch_narrow<4>", "launches_per_run": Tt,
                        "bytes_per_launch": bytes_step, "j_bytes_per_launch": jbytes,
                        "launch_us": launch_s * 1e6,
                        "mfma_tflops": flop_step / launch_s / 1e12,

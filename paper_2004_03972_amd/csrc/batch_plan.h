@@ -35,13 +35,14 @@ inline int64_t batch_row_tiles(int N) { return ((int64_t)N + BL_ROWS - 1) / BL_R
 
 // What a step reads and writes: the couplings, and per spin two copies of phi and of its BF16
 // operand, p and S.
+inline int64_t batch_coupling_bytes(const BatchShape &s) {
+    const int64_t cells = (int64_t)s.Np * s.Np;
+    return s.form == 0 ? 4 * cells : s.form == 1 ? 2 * cells : s.form == 2 ? cells : cells / 8;
+}
+
 inline int64_t batch_bytes(const std::vector<BatchShape> &inst, int R) {
     int64_t b = 0;
-    for (const BatchShape &s : inst) {
-        const int64_t cells = (int64_t)s.Np * s.Np;
-        b += (s.form == 0 ? 4 * cells : s.form == 1 ? 2 * cells : s.form == 2 ? cells : cells / 8) +
-             20ll * s.N * R;
-    }
+    for (const BatchShape &s : inst) b += batch_coupling_bytes(s) + 20ll * s.N * R;
     return b;
 }
 
@@ -62,7 +63,12 @@ inline int64_t batch_bytes(const std::vector<BatchShape> &inst, int R) {
 // Beyond that cache the state passes it by, which leaves it to the couplings and operands (kept /
 // passed by: 24 instances R = 64, 102 MB 40.6 / 42.2; N = 8192, R = 768, 190 MB 128 / 150; 265 MB
 // 137.6 / 144.9; 271 MB 125 / 120; 60 instances, 294 MB 104 / 93; 100 instances, 464 MB 152 / 138;
-// couplings passed by as well: 60 instances 141).
+// couplings passed by as well: 60 instances 141).  From 1400 MB on the cache holds little of the
+// couplings either way, and where they are few beside the state (at most 0.4 of it, or one bit each
+// in two tiles of three) eight wavefronts cover its reads better (state kept, eight wavefronts /
+// passed by, four: one bit, 1115 of 1351 642 / 692, 265 of 3686 691 / 724; FP8, R = 256, 227 of
+// 1376 559 / 601; 512 of the uneven batch 724 / 729; but BF16 310 of 1276 .. 1658 287 / 265).  66
+// large batches are 0.1% off the better of the two in the mean, 2% at worst.
 // Four wavefronts of 32-row tiles multiply faster, eight of 16-row tiles have the shorter way
 // through a tile.  So four take batches of more than 512 tiles whose mean tile passes at least 2400
 // columns (eight / four: 20 instances of 3792 267 / 257, 22 of 2827 120 / 115; 26 of 1632 164 / 163,
@@ -70,12 +76,15 @@ inline int64_t batch_bytes(const std::vector<BatchShape> &inst, int R) {
 // couplings pass few groups (N = 8192, R = 512, FP8 92 / 80, BF16 111 / 102; BF16 N = 2048, R = 2048
 // 43 / 47).
 inline BatchForm batch_form_for(const std::vector<BatchShape> &inst, int R, int64_t bytes) {
-    int64_t rows = 0, cols = 0;
+    int64_t rows = 0, cols = 0, bit_rows = 0, coupling = 0, state = 0;
     bool bits = true, few = false;
     for (const BatchShape &s : inst) {
         const int64_t n = batch_row_tiles(s.N);
         rows += n;
         cols += n * s.Np;
+        if (s.form == 3) bit_rows += n;
+        coupling += batch_coupling_bytes(s);
+        state += 20ll * s.N * R;
         bits &= s.form == 3;
         few |= s.form == 1 && s.Np < 4096;
     }
@@ -86,8 +95,10 @@ inline BatchForm batch_form_for(const std::vector<BatchShape> &inst, int R, int6
     else if (R <= 32 || (c32 <= (bits ? 1280 : 560) && bytes <= 150 * MB) ||
              (R > 64 && R <= 96 && bytes <= 256 * MB)) f.rt = 2;
     if (f.rt == 4) {
-        f.stream = bytes > 256 * MB;
-        f.wide = f.stream || (c64 > 512 && cols >= 2400 * rows) || (inst.size() == 1 && !few);
+        const bool light = inst.size() > 1 && bytes > 1400 * MB &&
+                           (5 * coupling <= 2 * state || 3 * bit_rows >= 2 * rows);
+        f.stream = bytes > 256 * MB && !light;
+        f.wide = f.stream || (c64 > 512 && cols >= 2400 * rows && !light) || (inst.size() == 1 && !few);
     }
     return f;
 }

@@ -721,7 +721,8 @@ __global__ __launch_bounds__(256, 2) void k_step_batch_cached(BatchArgs a, int64
     batch_wide_body<false>(a, q);
 }
 
-// Eight wavefronts of 16-row tiles: small batches and few replicas.
+// Eight wavefronts of 16-row tiles: small batches, few replicas, and large batches whose couplings
+// are few beside the state.
 template <int RT>
 __global__ __launch_bounds__(512, 4) void k_step_batch_narrow(BatchArgs a, int64_t q) {
     batch_lds_body<RT>(a, q);

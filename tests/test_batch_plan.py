@@ -50,3 +50,15 @@ def test_placement_by_balance():
         return [{b % 8 for b, t in enumerate(tiles) if t[0] == k} for k in range(len(sizes))]
     assert all(len(x) == 1 for x in xcds([148] * 32, 256))
     assert all(len(x) == 8 for x in xcds([1947] * 9, 256))
+
+
+@pytest.mark.parametrize("sizes,kinds,R,want", [
+    ([1351] * 1115, ["bit"] * 1115, 64, "narrow 4"),     # 1.9 GB of state, 0.2 of couplings
+    ([1351] * 500, ["bit"] * 500, 64, "streamed"),       # 0.9 GB
+    ([1376] * 227, ["fp8"] * 227, 256, "narrow 4"),      # couplings 0.29 of the state
+    ([1376] * 227, ["bf16"] * 227, 256, "streamed"),     # 0.57 of it
+    ([600] * 2400, ["bf16", "bit"] * 1200, 64, "streamed"),   # one bit in half of the tiles
+    ([1000] * 200 + [2750] * 220, ["bf16"] * 200 + ["bit"] * 220, 64, "narrow 4"),   # in three of four
+    ([8192], ["bit"], 64 * 200, "streamed")])            # one instance
+def test_kernel_of_large_batches(sizes, kinds, R, want):
+    assert form(sizes, kinds, R) == want
