@@ -259,8 +259,8 @@ static void launch_rows(const CsrArgs &a, int64_t q, hipStream_t st) {
 }
 
 template <bool FO>
-static void launch_csr(const CsrArgs &a, int64_t nnz, int64_t q, hipStream_t st) {
-    const CsrPlan p = csr_plan(a.N, nnz, 4u * (uint32_t)a.Rq);
+static void launch_csr(const CsrArgs &a, const Instance &I, int64_t q, hipStream_t st) {
+    const CsrPlan p = csr_plan(a.N, I.nnz, I.max_deg, (uint32_t)I.Rp);
     if (p.rows == 2) launch_rows<2, FO>(a, q, st);
     else if (p.rows) launch_rows<6, FO>(a, q, st);
     else if (p.vec == 1) launch_vec<1, FO>(a, q, p, st);
@@ -272,7 +272,7 @@ hipError_t launch_md_steps_csr(hqa_md *md, Instance &I, int64_t q0, int64_t q1) 
     for (int64_t q = q0; q < q1; q++) {
         CsrArgs a = csr_args(md, I);
         if (I.st && stats_step(md, q)) a.st = I.st;
-        launch_csr<false>(a, I.nnz, q, md->stream);
+        launch_csr<false>(a, I, q, md->stream);
         I.cur ^= 1;
     }
     return hipGetLastError();
@@ -281,7 +281,7 @@ hipError_t launch_md_steps_csr(hqa_md *md, Instance &I, int64_t q0, int64_t q1) 
 hipError_t launch_field_csr(hqa_md *md, Instance &I, float *u, hipStream_t st) {
     CsrArgs a = csr_args(md, I);
     a.u_out = u;
-    launch_csr<true>(a, I.nnz, 0, st);
+    launch_csr<true>(a, I, 0, st);
     return hipGetLastError();
 }
 

@@ -11,8 +11,8 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
                     "paper_2004_03972_amd", "csrc")
 SHIM = """
 #include "csr_plan.h"
-extern "C" uint64_t plan(int N, int64_t nnz, uint32_t Rp, int *out) {
-    const hqa::CsrPlan p = hqa::csr_plan(N, nnz, Rp);
+extern "C" uint64_t plan(int N, int64_t nnz, int max_deg, uint32_t Rp, int *out) {
+    const hqa::CsrPlan p = hqa::csr_plan(N, nnz, max_deg, Rp);
     out[0] = p.rows; out[1] = p.vec; out[2] = (int)p.chunks; out[3] = p.sliced;
     return p.rows ? ((uint64_t)N * (Rp / 4) + 255) / 256 : hqa::csr_wave_blocks(N, p);
 }
@@ -29,7 +29,7 @@ def L(tmp_path_factory):
                     "-o", str(d / "shim.so"), str(d / "shim.cc")], check=True)
     lib = C.CDLL(str(d / "shim.so"))
     lib.plan.restype = C.c_uint64
-    lib.plan.argtypes = [C.c_int, C.c_int64, C.c_uint32, C.c_void_p]
+    lib.plan.argtypes = [C.c_int, C.c_int64, C.c_int, C.c_uint32, C.c_void_p]
     return lib
 
 
@@ -42,29 +42,40 @@ def test_every_size(L):
                        1024, 2048, 65536):
                 if N * (Rp // 4) >= 2 ** 32 - 256:        # beyond what the state's set-up launches
                     continue
-                blocks = L.plan(N, nnz, Rp, out)
-                rows, vec, chunks, sliced = out
-                where = (N, nnz, Rp, rows, vec, chunks, sliced)
-                assert blocks * 256 < 2 ** 32, where
-                if rows:
-                    assert rows in (2, 6), where
-                    continue
-                assert vec in (1, 2, 4), where
-                assert 64 * vec * chunks >= Rp > 64 * vec * (chunks - 1), where
-                assert not sliced or (vec == 1 and (chunks in (2, 4) or chunks % 8 == 0)), where
-                if N * N >= (600 if Rp > 4 else 900) * nnz:   # many rows: no half-empty chunks
-                    assert Rp <= 64 or Rp % (64 * vec) == 0, where
-                    assert Rp > 32 or nnz >= 20 * N or Rp % 256 == 0, where
+                for max_deg in (6, 100):
+                    blocks = L.plan(N, nnz, max_deg, Rp, out)
+                    rows, vec, chunks, sliced = out
+                    where = (N, nnz, max_deg, Rp, rows, vec, chunks, sliced)
+                    assert blocks * 256 < 2 ** 32, where
+                    if rows:
+                        assert rows in (2, 6), where
+                        continue
+                    assert vec in (1, 2, 4), where
+                    assert 64 * vec * chunks >= Rp > 64 * vec * (chunks - 1), where
+                    assert not sliced or (vec == 1 and (chunks in (2, 4) or chunks % 8 == 0)
+                                          and Rp >= 57.6 * chunks), where
+                    if N >= 6500 and N * N >= (600 if Rp > 4 else 900) * nnz:   # many: no half-empty chunks
+                        assert Rp <= 64 or Rp >= 57.6 * vec * chunks, where
+                        assert Rp > 32 or nnz >= 20 * N or Rp % 256 == 0, where
 
 
 @pytest.mark.parametrize("N,d,Rp,form", [
     (1000000, 6, 4, "rows"), (1000000, 6, 64, "rows"), (100000, 30, 16, "rows"), (100000, 30, 68, "rows"),
     (1 << 26, 0, 4, "rows"), (10000, 30, 128, "wave"), (100000, 30, 256, "wave"), (4096, 6, 1024, "wave"),
-    (2000, 12, 64, "wave")])
+    (2000, 12, 64, "wave"), (3388, 5, 8, "wave"), (6499, 5, 8, "wave"), (6500, 5, 8, "rows"),
+    (4096, 5, 100, "rows"), (13186, 12, 1000, "wave"), (13186, 12, 900, "rows"), (7329, 30, 768, "rows"),
+    (7278, 30, 100, "wave")])
 def test_named_sizes(L, N, d, Rp, form):
     out = (C.c_int * 4)()
-    L.plan(N, N * d, Rp, out)
+    L.plan(N, N * d, 3 * d + 7, Rp, out)
     assert (out[0] > 0) == (form == "rows")
+
+
+def test_short_rows_of_a_lattice(L):
+    out = (C.c_int * 4)()
+    for N, deg, rows in ((4096, 6, True), (4096, 7, False), (3375, 6, False), (6859, 7, True)):
+        L.plan(N, 6 * N, deg, 8, out)
+        assert (out[0] > 0) == rows, (N, deg)
 
 
 def test_turned_copies_stay_within_a_launch(L):

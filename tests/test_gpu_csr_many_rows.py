@@ -41,7 +41,7 @@ def test_copies(H, kind, R):
     d = len(ci) / N0
     lo, hi = {"few": (0, 10), "some": (10, 20), "many": (20, 60)}[kind]
     assert lo <= d < hi
-    K = int(600 * d / N0) + 2                            # copies: at least 600 d rows
+    K = max(int(600 * d / N0), 6500 // N0) + 2           # copies: at least 600 d rows, and 6500
     ci_k = (ci[None, :] + N0 * np.arange(K)[:, None]).astype(np.int32).ravel()
     rp_k = np.concatenate([[0], (rp[None, 1:] + len(ci) * np.arange(K)[:, None]).ravel()]).astype(np.int32)
     p0 = inst.random_pm1((R, N0), 5)
