@@ -480,7 +480,8 @@ hqa_status hqa_classify_probs(hqa_md *md, int32_t instance, const float *prob, i
 typedef struct hqa_es hqa_es;
 
 /* New classifier: weights uniform in +-1/sqrt(fan_in) from the counter hash of the
- * seed, biases 0, Adam moments 0.  All work on the given stream. */
+ * seed, biases 0, Adam moments 0.  All work on the given stream.  Allocates what the
+ * training steps need (13.6 MB), so that a step on device data allocates nothing. */
 hqa_status hqa_es_create(uint64_t seed, void *hip_stream, hqa_es **out);
 
 /* Copy the HQA_ES_NPARAM parameters out, or in with import != 0 (which also resets

@@ -16,11 +16,11 @@ inline int64_t step_blocks(int Np, int Rp, int tm, int tn) {
 
 // Np rows (a multiple of 128), Rp replicas (a multiple of 16).
 //
-// Shape: workgroups come in rounds of 256, one a CU, and a workgroup of 2 x 4, 2 x 2, 2 x 1 tiles
-// lasts about 3.8, 2.2, 1.5 times as long as one of 1 x 1; the least sum of rounds wins, the larger
+// Shape: workgroups come in turns of 256, one a CU, and a workgroup of 2 x 4, 2 x 2, 2 x 1 tiles
+// lasts about 3.8, 2.2, 1.5 times as long as one of 1 x 1; the least sum of turns wins, the larger
 // shape at equal sums.  Over 240 random sizes (N 60 ... 9000, R 1 ... 1500, three storage types) it
 // is within 0.5% of the fastest of six shapes and two depths in the mean; the largest shape that
-// gives 180 workgroups is 4.5% off, since a chip filled by 130 ... 180 large blocks beats two rounds
+// gives 180 workgroups is 4.5% off, since a chip filled by 130 ... 180 large blocks beats two turns
 // of smaller ones (us per step, this / 180: BF16 N = 5445, R = 13: 18.3 / 22.9; binary32 N = 4469,
 // R = 19: 36.3 / 55.4; N = 5035, R = 60: 65.5 / 99.3; FP8 N = 1415, R = 44: 7.7 / 9.1).
 //

@@ -61,8 +61,8 @@ __device__ __forceinline__ StepCoef csr_res_coef(const CsrResArgs &a, int64_t q)
 // Bound by vector instructions, four wavefronts a SIMD: 24 multiply-adds and 56 operations of the
 // leapfrog a spin and four replicas at D = 6.  So the two flux buffers are interleaved (a
 // buffer is an offset in the instruction, steps go in pairs), couplings keep LDS addresses, the
-// initial half kick is a step of its own, and rows of one length need no masks and no spilled
-// registers.  N = 4096, R = 1024: 3.35 us a step without these, 2.95 with.
+// initial half kick is a step of its own, and rows of one length need no masks.  (Four spins a
+// thread at D = 6 spill 60 bytes a lane; two of the accesses are in the loop, a pair of steps.)  N = 4096, R = 1024: 3.35 us a step without these, 2.95 with.
 template <int SPT, int MP, int D>
 __global__ __launch_bounds__(CSR_RES_THREADS) void k_csr_resident(CsrResArgs a) {
     constexpr int DM = D ? D : CSR_RES_DMAX;
