@@ -987,6 +987,7 @@ hqa_status hqa_md_tune(hqa_md *md, int32_t steps) {
     HIPCHK(hipStreamSynchronize(md->stream));
     const int64_t k0 = md->stats_k0, k1 = md->stats_k1;
     md->stats_k0 = md->stats_k1 = 0;   // candidates accumulate no statistics
+    md->tuning = true;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hqa_status rs = HQA_OK;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
@@ -1140,6 +1141,7 @@ hqa_status hqa_md_tune(hqa_md *md, int32_t steps) {
     if (rs == HQA_OK) rs = tune_multi(md, steps, e0, e1, cache);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
+    md->tuning = false;
     md->stats_k0 = k0;
     md->stats_k1 = k1;
     return rs;

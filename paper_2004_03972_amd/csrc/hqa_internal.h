@@ -131,6 +131,7 @@ struct hqa_md {
                                              // graphs of hqa_md_pass
     void *keep = nullptr;                    // read-out scratch kept between calls
     int64_t stats_k0 = 0, stats_k1 = 0;      // early-stop statistics window [k0, k1)
+    bool tuning = false;                     // candidates are being timed: tiled ones use their copies
     int64_t stats_every = 1;                 // ... sampling steps k0, k0 + every, ...
 };
 

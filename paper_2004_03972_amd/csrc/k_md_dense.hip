@@ -378,7 +378,7 @@ hipError_t launch_md_steps_dense(hqa_md *md, Instance &I, int64_t q0, int64_t q1
         hipError_t e = ensure_tiled_j(I, md->stream);
         if (e == hipSuccess) e = ensure_tiled_x(I, md->stream);
         if (e != hipSuccess) return e;
-        tiled = step_reads_tiles(I.Np, q1 - q0);
+        tiled = md->tuning || step_reads_tiles(I.Np, q1 - q0);
     }
     if (tiled) tile_x(I, I.xt[0], md->stream);
     for (int64_t q = q0; q < q1; q++) {
