@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "hqa_internal.h"
+#include "tune_times.h"
 
 using namespace hqa;
 
@@ -934,10 +935,11 @@ static hqa_status tune_multi(hqa_md *md, int32_t steps, hipEvent_t e0, hipEvent_
     float best = 1e30f;
     int pick = HQA_PLAN_BATCH;
     for (int cand : {HQA_PLAN_BATCH, HQA_PLAN_CLUSTER, HQA_PLAN_STEP}) {
-        float t[3] = {0.f, 0.f, 0.f};
-        for (int pass = 0; pass < 3 && he == hipSuccess; pass++) {
-            const int64_t q1 = md->q + (pass == 2 ? 2 * (int64_t)steps : steps);
+        TuneTimes times;
+        for (int pass = 0; pass < TUNE_PASSES && he == hipSuccess && !tune_done(pass, times, best); pass++) {
+            const int64_t q1 = md->q + (tune_pass_twice(pass) ? 2 * (int64_t)steps : steps);
             int used = 0;
+            float t = 0.f;
             he = hipEventRecord(e0, md->stream);
             if (he == hipSuccess) {
                 if (cand == HQA_PLAN_BATCH) {
@@ -952,10 +954,11 @@ static hqa_status tune_multi(hqa_md *md, int32_t steps, hipEvent_t e0, hipEvent_
             }
             if (he == hipSuccess) he = hipEventRecord(e1, md->stream);
             if (he == hipSuccess) he = hipEventSynchronize(e1);
-            if (he == hipSuccess) he = hipEventElapsedTime(&t[pass], e0, e1);
+            if (he == hipSuccess) he = hipEventElapsedTime(&t, e0, e1);
             if (he == hipSuccess) he = copy(false);
+            if (pass > 0) times.add(tune_pass_twice(pass), t);
         }
-        float ms = std::max(t[2] - t[1], 0.0f);
+        float ms = times.slope();
         int32_t errc = err0;
         if (he == hipSuccess)
             he = hipMemcpyAsync(&errc, md->err, sizeof errc, hipMemcpyDeviceToHost, md->stream);
@@ -1067,13 +1070,12 @@ hqa_status hqa_md_tune(hqa_md *md, int32_t steps) {
             I.step_tm = c.tm;
             I.step_cb = c.cb;
             I.step_tj = c.tj;
-            // pass 0 warms up; passes 1 and 2 run `steps` and 2 `steps` steps, and the
-            // difference is the cost of `steps` steps without the plan's fixed per-run
-            // cost (state staging of the one-launch plans, first-use set-up)
-            float ms = 0.f, t[3] = {0.f, 0.f, 0.f};
-            for (int pass = 0; pass < 3 && he == hipSuccess; pass++) {
-                const int64_t len = pass == 2 ? 2 * (int64_t)steps : steps;
+            TuneTimes times;
+            bool applies = true;
+            for (int pass = 0; pass < TUNE_PASSES && he == hipSuccess && !tune_done(pass, times, best); pass++) {
+                const int64_t len = tune_pass_twice(pass) ? 2 * (int64_t)steps : steps;
                 int used = 0;
+                float t = 0.f;
                 stage = "event record";
                 he = hipEventRecord(e0, md->stream);
                 if (he == hipSuccess) {
@@ -1091,15 +1093,16 @@ hqa_status hqa_md_tune(hqa_md *md, int32_t steps) {
                 }
                 if (he == hipSuccess) {
                     stage = "elapsed time";
-                    he = hipEventElapsedTime(&t[pass], e0, e1);
+                    he = hipEventElapsedTime(&t, e0, e1);
                 }
                 if (he == hipSuccess) {
                     stage = "restore";
                     he = copy(false);
                 }
-                if (he == hipSuccess && used != c.plan) t[pass] = 1e30f;   // not applicable
+                if (pass > 0) times.add(tune_pass_twice(pass), t);
+                if (used != c.plan) applies = false;
             }
-            ms = t[2] >= 1e30f || t[1] >= 1e30f ? 1e30f : std::max(t[2] - t[1], 0.0f);
+            float ms = applies ? times.slope() : 1e30f;
             int32_t errc = err0;
             if (he == hipSuccess) {
                 stage = "error word";
