@@ -42,6 +42,13 @@ inline size_t energy_part_bytes(int N, int V) {
 // Vectors of a wavefront: up to 64 while the 4 D accumulators per 16 of them fit the registers.
 inline int energy_mv_vec(int V, int D) { return V <= 16 || D > 12 ? 16 : D > 8 ? 32 : 64; }
 
+// Whether k_energy scores V vectors of N spins sooner than digit products do.  At 16 spins a vector
+// is one term a thread, and the products' merge, a digit at a time, is what a call waits for (us per
+// call, digits / k_energy, N = 8: V = 100, 500, 2000, 8000 with D = 20 98, 105, 113, 137 / 71, 74, 89,
+// 148; D = 10 82, 88, 95, 106 / 71, 73, 89, 150; D = 1 72, 78, 86, 93 / 62, 62, 65, 77; N = 16 and V =
+// 2000 112, 92, 84 / 93, 92, 66; N = 32 and V = 2000 92, 92, 86 / 104, 104, 68).
+inline bool energy_by_vector(int N, int V) { return N <= 16 && V <= 2048; }
+
 struct EnergyPlan {
     int vec;      // vectors of a wavefront
     int P;        // slices

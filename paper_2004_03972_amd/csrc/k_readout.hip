@@ -1620,7 +1620,8 @@ static void energy_mv_dispatch(int vec, int D, F f) {
 hipError_t launch_energy(const Instance &I, int V, const int8_t *spins, double *E, double *cut,
                          void *part, hipStream_t st) {
     if (V == 0) return hipSuccess;
-    if (const int D = energy_digits(I)) {
+    const int D = energy_by_vector(I.N, V) ? 0 : energy_digits(I);
+    if (D) {
         const EnergyPlan pl = energy_plan(I.N, V, D);
         for (int v0 = 0; v0 < V; v0 += pl.piece) {
             const int n = std::min(pl.piece, V - v0);

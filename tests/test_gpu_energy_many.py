@@ -59,3 +59,17 @@ def test_readouts(H, spread, R):
         torch.cuda.synchronize()
         assert np.array_equal(Ep[k].cpu().numpy(), Eo) and np.array_equal(Cp[k].cpu().numpy(), Co)
     md.close()
+
+
+@pytest.mark.parametrize("N", [1, 2, 15, 16, 17])
+@pytest.mark.parametrize("spread", [None, 0, 80])
+def test_few_spins(H, N, spread):
+    """The vector counts on both sides of the line between a workgroup a vector and the products."""
+    J, h = glass(N, spread or 0, N)
+    if spread is None:
+        J, h = np.sign(J), None
+    for V in (1, 17, 2048, 2049):
+        s = np.where(np.random.default_rng(V).random((V, N)) < 0.5, -1, 1).astype(np.int8)
+        E, C = H.ising_energy(H.Problem(J, h=h), s)
+        Eo, Co = orc.energy(orc.Problem(N, J=J, h=h), s)
+        assert np.array_equal(E, Eo) and np.array_equal(C, Co), V
